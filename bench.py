@@ -87,7 +87,7 @@ def kernel_digest():
 
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_1312_6127_amd", "csrc")
-    for f in ("dual.h", "common.h", "physics.h", "invert.h", "implicit.h"):
+    for f in ("dual.h", "common.h", "physics.h", "invert.h", "implicit.h", "pointwise.h"):
         with open(os.path.join(d, f), "rb") as fh:
             h.update(fh.read())
     with open(os.path.join(d, "kernels.h"), encoding="utf-8") as fh:

@@ -53,13 +53,14 @@ DEV void interior_cell(const Ctx& C, long t, int& i, int& j, int& k) {
 // ---------------------------------------------------------------------------
 // U^n = U(P^n): lamP += (dU/dP)^T lamU at interior cells
 // ---------------------------------------------------------------------------
+template <class Geo>
 DEV void adj_p2u_at(Ctx C, const double* __restrict__ P,
                                   const double* __restrict__ lamU, double* __restrict__ lamP, long t) {
   if (t >= (long)C.n[0] * C.n[1] * C.n[2]) return;
   int i, j, k;
   interior_cell(C, t, i, j, k);
   const long c = cell_index(C, i, j, k);
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   double p[12], lu[12];
 #pragma unroll
@@ -81,9 +82,10 @@ DEV void adj_p2u_at(Ctx C, const double* __restrict__ P,
   }
 }
 
+template <class Geo>
 __global__ void LB(128) k_adj_p2u(Ctx C, const double* __restrict__ P,
                                   const double* __restrict__ lamU, double* __restrict__ lamP) {
-  adj_p2u_at(C, P, lamU, lamP, (long)blockIdx.x * blockDim.x + threadIdx.x);
+  adj_p2u_at<Geo>(C, P, lamU, lamP, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -94,8 +96,8 @@ __global__ void LB(128) k_adj_p2u(Ctx C, const double* __restrict__ P,
 // (eq. source6 with G_S of eq. GS, weighted by T_gas as the forward) with
 // the explicit tracer Se = sqrt(-g) [S u^t]_(i); P and U as for PMHD.
 // ---------------------------------------------------------------------------
-template <class T>
-DEV void pmhd_map(const Metric& m, const Phys& ph, double dtc, const T& chi_abs, const T& chi_es,
+template <class T, class M>
+DEV void pmhd_map(const M& m, const Phys& ph, double dtc, const T& chi_abs, const T& chi_es,
                   const T x[4], const T th[12], T E[4], T P[12], T U[12], bool ent = false,
                   const T& Se = T(0.0)) {
   const double igd = 1.0 / m.gdet;
@@ -180,7 +182,7 @@ DEV void pmhd_map(const Metric& m, const Phys& ph, double dtc, const T& chi_abs,
 // [S u^t]_(i); lamS [Ntot] out: its cotangent at interior cells (zero where
 // the solution is not an entropy-method one).  Without ENT both are unused
 // and the entropy row is not compiled in.
-template <bool ENT>
+template <class Geo, bool ENT>
 DEV void adj_implicit_at(Ctx C, double scale, const double* __restrict__ dt_dev,
                                       const double* __restrict__ Ue, const double* __restrict__ Pk,
                                       const int* __restrict__ status,
@@ -206,7 +208,7 @@ DEV void adj_implicit_at(Ctx C, double scale, const double* __restrict__ dt_dev,
   const double se = ent ? Se[c] : 0.0;
   if (ENT) lamS[c] = 0.0;
   double mu[4];
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   Phys ph;
   ph.gam = C.gam;
@@ -303,7 +305,7 @@ DEV void adj_implicit_at(Ctx C, double scale, const double* __restrict__ dt_dev,
   }
 }
 
-template <bool ENT>
+template <class Geo, bool ENT>
 __global__ void LB(64) k_adj_implicit(Ctx C, double scale, const double* __restrict__ dt_dev,
                                       const double* __restrict__ Ue, const double* __restrict__ Pk,
                                       const int* __restrict__ status,
@@ -313,7 +315,7 @@ __global__ void LB(64) k_adj_implicit(Ctx C, double scale, const double* __restr
                                       const double* __restrict__ lamU, double* __restrict__ lamUe,
                                       double* __restrict__ gchi, const double* __restrict__ Se,
                                       double* __restrict__ lamS) {
-  adj_implicit_at<ENT>(C, scale, dt_dev, Ue, Pk, status, chi_abs, chi_es, lamP, lamU, lamUe, gchi,
+  adj_implicit_at<Geo, ENT>(C, scale, dt_dev, Ue, Pk, status, chi_abs, chi_es, lamP, lamU, lamUe, gchi,
                        Se, lamS, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
@@ -365,8 +367,8 @@ DEV bool fixed_at(const Ctx& C, const int* st, const int idx[3]) {
 }
 
 // the fix-up's floors on primitives p, in place (as the forward fix-up)
-template <class T>
-DEV void floor_map(const Ctx& C, const Metric& m, T p[12]) {
+template <class T, class M>
+DEV void floor_map(const Ctx& C, const M& m, T p[12]) {
   Gas<T> s;
   make_gas(m, C.gam, p[0], p[1], p + 2, p + 5, s);
   const T br = s.bsq / C.bsq_rho_max, bu = s.bsq / C.bsq_u_max;
@@ -384,6 +386,7 @@ DEV bool touched_at(const Ctx& C, const int* st, const int idx[3], bool exact_fl
          (exact_floors && (st[cell_index(C, idx[0], idx[1], idx[2])] & GRRMHD_ST_FLOOR));
 }
 
+template <class Geo>
 DEV void adj_fixup_own_at(Ctx C, const double* __restrict__ P, const double* __restrict__ Ppre,
                           const int* __restrict__ st, const double* __restrict__ lamP,
                           const double* __restrict__ lamU, double* __restrict__ Lam, long t) {
@@ -394,7 +397,7 @@ DEV void adj_fixup_own_at(Ctx C, const double* __restrict__ P, const double* __r
   const bool fixed = fixed_at(C, st, idx);
   const bool floored = Ppre && (st[c] & GRRMHD_ST_FLOOR);
   if (!fixed && !floored) return;
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, idx[0] + C.N[0] * idx[1], m);
   double p[12], lu[12], lo[12];
 #pragma unroll
@@ -463,11 +466,12 @@ DEV void adj_fixup_own_at(Ctx C, const double* __restrict__ P, const double* __r
 }
 
 // Ppre (nullable): the state before the fix-ups (the floors' transpose)
+template <class Geo>
 __global__ void LB(128) k_adj_fixup_own(Ctx C, const double* __restrict__ P,
                                         const double* __restrict__ Ppre,
                                         const int* __restrict__ st, const double* __restrict__ lamP,
                                         const double* __restrict__ lamU, double* __restrict__ Lam) {
-  adj_fixup_own_at(C, P, Ppre, st, lamP, lamU, Lam, (long)blockIdx.x * blockDim.x + threadIdx.x);
+  adj_fixup_own_at<Geo>(C, P, Ppre, st, lamP, lamU, Lam, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 DEV void adj_fixup_at(Ctx C, int exact_floors, const int* __restrict__ st,
@@ -515,7 +519,7 @@ DEV void adj_fixup_at(Ctx C, int exact_floors, const int* __restrict__ st,
 }
 
 // exact_floors: Lam holds the floors' transpose (k_adj_fixup_own with Ppre)
-__global__ void LB(256) k_adj_fixup(Ctx C, int exact_floors, const int* __restrict__ st,
+static __global__ void LB(256) k_adj_fixup(Ctx C, int exact_floors, const int* __restrict__ st,
                                     const double* __restrict__ Lam,
                                     const double* __restrict__ lamP, const double* __restrict__ lamU,
                                     double* __restrict__ lamPpre, double* __restrict__ lamUpre) {
@@ -540,7 +544,7 @@ DEV void adj_stage_at(Ctx C, double a, double b, const double* __restrict__ lamU
   }
 }
 
-__global__ void LB(256) k_adj_stage(Ctx C, double a, double b, const double* __restrict__ lamUe,
+static __global__ void LB(256) k_adj_stage(Ctx C, double a, double b, const double* __restrict__ lamUe,
                                     double* __restrict__ lamUn, double* __restrict__ lamUprev) {
   adj_stage_at(C, a, b, lamUe, lamUn, lamUprev, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
@@ -582,7 +586,7 @@ DEV void adj_emf_at(Ctx C, int a, FaceRange R, double scale,
   lamE[(long)a * C.Ntot + e] = acc;
 }
 
-__global__ void LB(256) k_adj_emf(Ctx C, int a, FaceRange R, double scale,
+static __global__ void LB(256) k_adj_emf(Ctx C, int a, FaceRange R, double scale,
                                   const double* __restrict__ dt_dev,
                                   const double* __restrict__ lamUe, double* __restrict__ lamE) {
   adj_emf_at(C, a, R, scale, dt_dev, lamUe, lamE, (long)blockIdx.x * blockDim.x + threadIdx.x);
@@ -600,8 +604,8 @@ struct FaceSums {
   T gm, gp, rm, rp;
 };
 
-template <class T>
-DEV void face_sums(const Ctx& C, const Metric& m, int d, const T* P, T chi_tot, const double lF[12],
+template <class T, class M>
+DEV void face_sums(const Ctx& C, const M& m, int d, const T* P, T chi_tot, const double lF[12],
                    FaceSums<T>& o, double lFs = 0.0) {
   Gas<T> s;
   make_gas(m, C.gam, P[0], P[1], P + 2, P + 5, s);
@@ -680,8 +684,8 @@ DEV void flux_contract(const Ctx& C, const FaceSums<TL>& L, const FaceSums<TR>& 
 // statement on each input makes the values opaque per pass, so each pass
 // recomputes them in registers (measured: the 96x48x24 disk adjoint step
 // 5.7 ms -> 3.0 ms).  Two seeds per pass spill least at equal speed.
-template <int S>
-DEV void adj_face_side(const Ctx& C, const Metric& m, int D, const double PLR[24], double chiL,
+template <int S, class M>
+DEV void adj_face_side(const Ctx& C, const M& m, int D, const double PLR[24], double chiL,
                        double chiR, const double lF[12], double lS[12], double* gx,
                        double lFs = 0.0) {
   constexpr int NS = 2;
@@ -740,7 +744,7 @@ DEV void adj_face_side(const Ctx& C, const Metric& m, int D, const double PLR[24
 // those four values (gas and radiation of the left cell, then of the right)
 // go to GF[4][face].
 // ---------------------------------------------------------------------------
-template <int D, bool PPM>
+template <class Geo, int D, bool PPM>
 DEV void adj_flux_at(Ctx C, FaceRange R, double scale,
                                                  const double* __restrict__ dt_dev,
                                                  const double* __restrict__ P,
@@ -786,7 +790,7 @@ DEV void adj_flux_at(Ctx C, FaceRange R, double scale,
   // Kerr-Schild along r the sqrt(-g) weights of the vector primitives
   double fgL = 0.0, frL = 0.0, fgR = 0.0, frR = 0.0, gc[6] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0};
   double gface = 1.0;
-  const bool wgt = PPM && (D == 1) && C.metric == GRRMHD_KERR_SCHILD;
+  const bool wgt = PPM && (D == 1) && Geo::curved(C);
   if (PPM) {
     const double* fg = fl + (long)(2 * d) * C.Ntot;
     const double* fr = fg + C.Ntot;
@@ -821,7 +825,7 @@ DEV void adj_flux_at(Ctx C, FaceRange R, double scale,
       PLR[12 + q] = e - 0.5 * mc_slope(e - b, ff - e);
     }
   }
-  Metric m;
+  typename Geo::template M<double> m;
   const double* tab = (D == 1) ? C.geo_f1 : ((D == 2) ? C.geo_f2 : C.geo_c);
   load_metric(tab, C.npos, i + C.N[0] * j, m);
   const double chiL = chi_abs[f - st] + chi_es[f - st], chiR = chi_abs[f] + chi_es[f];
@@ -880,7 +884,7 @@ DEV void adj_flux_at(Ctx C, FaceRange R, double scale,
   }
 }
 
-template <int D, bool PPM>
+template <class Geo, int D, bool PPM>
 __global__ void __launch_bounds__(64) k_adj_flux(Ctx C, FaceRange R, double scale,
                                                  const double* __restrict__ dt_dev,
                                                  const double* __restrict__ P,
@@ -892,7 +896,7 @@ __global__ void __launch_bounds__(64) k_adj_flux(Ctx C, FaceRange R, double scal
                                                  const double* __restrict__ fl,
                                                  double* __restrict__ GF,
                                                  const double* __restrict__ lamS) {
-  adj_flux_at<D, PPM>(C, R, scale, dt_dev, P, chi_abs, chi_es, lamUe, lamE, G, Gx, fl, GF, lamS,
+  adj_flux_at<Geo, D, PPM>(C, R, scale, dt_dev, P, chi_abs, chi_es, lamUe, lamE, G, Gx, fl, GF, lamS,
                       (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
@@ -948,6 +952,7 @@ __global__ void LB(256) k_adj_gather(Ctx C, FaceRanges FR, const double* __restr
 
 // Interior cell t (curved metric): lamPb += c dt (dS/dP)^T lamUe, the
 // geometric source's Jacobian by Dual<4> passes over the 12 primitives.
+template <class Geo>
 DEV void adj_geom_at(Ctx C, double scale, const double* __restrict__ dt_dev,
                      const double* __restrict__ P, const double* __restrict__ lamUe,
                      double* __restrict__ lamPb, long t) {
@@ -956,7 +961,7 @@ DEV void adj_geom_at(Ctx C, double scale, const double* __restrict__ dt_dev,
   interior_cell(C, t, i, j, k);
   const long c = cell_index(C, i, j, k);
   const int pos = i + C.N[0] * j;
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, pos, m);
   double p[12], lu[12], dg[2][10];
 #pragma unroll
@@ -964,7 +969,7 @@ DEV void adj_geom_at(Ctx C, double scale, const double* __restrict__ dt_dev,
     p[q] = P[q * C.Ntot + c];
     lu[q] = lamUe[q * C.Ntot + c];
   }
-  load_dg(C, pos, dg);
+  load_dg<typename Geo::template M<double>>(C, pos, dg);
   const double cdt = scale * (*dt_dev);
   // values kept opaque per pass (empty asm), as in the face passes
 #pragma unroll 1
@@ -988,16 +993,17 @@ DEV void adj_geom_at(Ctx C, double scale, const double* __restrict__ dt_dev,
   }
 }
 
+template <class Geo>
 __global__ void LB(64) k_adj_geom(Ctx C, double scale, const double* __restrict__ dt_dev,
                                   const double* __restrict__ P, const double* __restrict__ lamUe,
                                   double* __restrict__ lamPb) {
-  adj_geom_at(C, scale, dt_dev, P, lamUe, lamPb, (long)blockIdx.x * blockDim.x + threadIdx.x);
+  adj_geom_at<Geo>(C, scale, dt_dev, P, lamUe, lamPb, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // Opacity cotangents through the fluxes: per allocated cell, the faces that
 // read its total opacity (as left cell of face c + e_d, right cell of face c);
 // chi_abs and chi_es receive the same amount.  Gx_d: [2][Ntot] per direction.
-__global__ void LB(256) k_adj_gather_chi(Ctx C, FaceRanges FR, const double* __restrict__ Gx1,
+static __global__ void LB(256) k_adj_gather_chi(Ctx C, FaceRanges FR, const double* __restrict__ Gx1,
                                          const double* __restrict__ Gx2,
                                          const double* __restrict__ Gx3,
                                          double* __restrict__ gchi) {
@@ -1032,6 +1038,7 @@ __global__ void LB(256) k_adj_gather_chi(Ctx C, FaceRanges FR, const double* __r
 // whose tracer the forward left undefined (rho0 or u_g not positive) gets
 // nothing.
 // ---------------------------------------------------------------------------
+template <class Geo>
 DEV void adj_entropy_at(const Ctx& C, int i, int j, long c, const double* __restrict__ P,
                        double l, double* __restrict__ lamP) {
   typedef Dual<5> D5;
@@ -1039,7 +1046,7 @@ DEV void adj_entropy_at(const Ctx& C, int i, int j, long c, const double* __rest
 #pragma unroll
   for (int q = 0; q < 5; q++) pd[q] = D5::var(P[q * C.Ntot + c], q);
   if (!(pd[0].v > 0.0) || !(pd[1].v > 0.0)) return;
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   Vel<D5> v;
   make_vel(m, pd + 2, v);
@@ -1050,6 +1057,7 @@ DEV void adj_entropy_at(const Ctx& C, int i, int j, long c, const double* __rest
   for (int q = 0; q < 5; q++) lamP[q * C.Ntot + c] += l * U.d[q];
 }
 
+template <class Geo>
 __global__ void LB(128) k_adj_entropy_field(Ctx C, double b, const double* __restrict__ P,
                                             const double* __restrict__ lamS,
                                             double* __restrict__ lamP) {
@@ -1057,11 +1065,11 @@ __global__ void LB(128) k_adj_entropy_field(Ctx C, double b, const double* __res
   if (!interior_ijk(C, (long)blockIdx.x * blockDim.x + threadIdx.x, i, j, k)) return;
   const long c = cell_index(C, i, j, k);
   const double l = b * lamS[c];
-  if (l != 0.0) adj_entropy_at(C, i, j, c, P, l, lamP);
+  if (l != 0.0) adj_entropy_at<Geo>(C, i, j, c, P, l, lamP);
 }
 
 // y += alpha x at interior cells, one field
-__global__ void LB(256) k_adj_axpy1(Ctx C, double alpha, const double* __restrict__ x,
+static __global__ void LB(256) k_adj_axpy1(Ctx C, double alpha, const double* __restrict__ x,
                                     double* __restrict__ y) {
   int i, j, k;
   if (!interior_ijk(C, (long)blockIdx.x * blockDim.x + threadIdx.x, i, j, k)) return;
@@ -1074,6 +1082,7 @@ __global__ void LB(256) k_adj_axpy1(Ctx C, double alpha, const double* __restric
 // the cells whose solve did not fail, side 0 lamP[q] += dU_S/dP_q lamMS /
 // (g dt) (P_out, before the implicit solve's transpose), side 1 lamS -=
 // lamMS / (g dt) (Se, after it).
+template <class Geo>
 __global__ void LB(128) k_adj_stage_ms(Ctx C, int side, double g, const double* __restrict__ dt_dev,
                                        const int* __restrict__ st, const double* __restrict__ P,
                                        const double* __restrict__ lamMS,
@@ -1087,11 +1096,11 @@ __global__ void LB(128) k_adj_stage_ms(Ctx C, int side, double g, const double* 
   if (side)
     lamS[c] -= l;
   else
-    adj_entropy_at(C, i, j, c, P, l, lamP);
+    adj_entropy_at<Geo>(C, i, j, c, P, l, lamP);
 }
 
 // y += m dt x at interior cells, one field (a bracket's dt m_k M_S^k term)
-__global__ void LB(256) k_adj_axpy1_dt(Ctx C, double m, const double* __restrict__ dt_dev,
+static __global__ void LB(256) k_adj_axpy1_dt(Ctx C, double m, const double* __restrict__ dt_dev,
                                        const double* __restrict__ x, double* __restrict__ y) {
   int i, j, k;
   if (!interior_ijk(C, (long)blockIdx.x * blockDim.x + threadIdx.x, i, j, k)) return;
@@ -1111,7 +1120,7 @@ __global__ void LB(256) k_adj_axpy1_dt(Ctx C, double m, const double* __restrict
 // compression test failed or the ramp is clamped at zero).  prev: fl_{k-1},
 // null at the first evaluation.  GF_d: [4][Ntot] per direction.
 // ---------------------------------------------------------------------------
-__global__ void LB(256) k_adj_flat_cot(Ctx C, FaceRanges FR, const double* __restrict__ GF,
+static __global__ void LB(256) k_adj_flat_cot(Ctx C, FaceRanges FR, const double* __restrict__ GF,
                                        const double* __restrict__ fl,
                                        const double* __restrict__ prev,
                                        double* __restrict__ LamFl, double* __restrict__ Lf2) {
@@ -1161,7 +1170,7 @@ __global__ void LB(256) k_adj_flat_cot(Ctx C, FaceRanges FR, const double* __res
 // rho and total opacity; added to lamPb and (non-null) to both opacity
 // cotangents gchi [2][Ntot].  mf: the mass fluxes of P (k_mass_flux) on a
 // Kerr-Schild grid, null in flat space.
-__global__ void LB(128) k_adj_flat(Ctx C, const double* __restrict__ P,
+static __global__ void LB(128) k_adj_flat(Ctx C, const double* __restrict__ P,
                                    const double* __restrict__ chi_abs,
                                    const double* __restrict__ chi_es,
                                    const double* __restrict__ mf,
@@ -1254,11 +1263,11 @@ DEV void adj_bc_at(Ctx C, int d, double* lam, long t) {
   }
 }
 
-__global__ void LB(256) k_adj_bc(Ctx C, int d, double* lam) {
+static __global__ void LB(256) k_adj_bc(Ctx C, int d, double* lam) {
   adj_bc_at(C, d, lam, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-__global__ void LB(256) k_fill_d(double* p, long n, double v) {
+static __global__ void LB(256) k_fill_d(double* p, long n, double v) {
   for (long t = (long)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (long)gridDim.x * blockDim.x)
     p[t] = v;
 }
@@ -1269,7 +1278,7 @@ __global__ void LB(256) k_fill_d(double* p, long n, double v) {
 // ---------------------------------------------------------------------------
 
 // y += alpha x, 12 fields at interior cells
-__global__ void LB(256) k_adj_axpy12(Ctx C, double alpha, const double* __restrict__ x,
+static __global__ void LB(256) k_adj_axpy12(Ctx C, double alpha, const double* __restrict__ x,
                                      double* __restrict__ y) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (long)C.n[0] * C.n[1] * C.n[2]) return;
@@ -1284,7 +1293,7 @@ __global__ void LB(256) k_adj_axpy12(Ctx C, double alpha, const double* __restri
 DEV int mslot(int r) { return (r < 4) ? 1 + r : 4 + r; }
 
 // a bracket's dt m_k M^k term: lamM += dt m lamUe (rows of the 8 slots)
-__global__ void LB(256) k_adj_mterm(Ctx C, double m, const double* __restrict__ dt_dev,
+static __global__ void LB(256) k_adj_mterm(Ctx C, double m, const double* __restrict__ dt_dev,
                                     const double* __restrict__ lamUe, double* __restrict__ lamM) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (long)C.n[0] * C.n[1] * C.n[2]) return;
@@ -1299,7 +1308,7 @@ __global__ void LB(256) k_adj_mterm(Ctx C, double m, const double* __restrict__ 
 // M = (U_out - U_e)/(g dt) at cells whose solve did not fail: its transpose
 // spread into one side, tgt[slot] += scale/dt lamM (scale = 1/g for U_out,
 // -1/g for U_e)
-__global__ void LB(256) k_adj_mscatter(Ctx C, double scale, const double* __restrict__ dt_dev,
+static __global__ void LB(256) k_adj_mscatter(Ctx C, double scale, const double* __restrict__ dt_dev,
                                        const int* __restrict__ st, const double* __restrict__ lamM,
                                        double* __restrict__ tgt) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1373,6 +1382,7 @@ DEV int solve_t(const double A[N][N], const double b[N], double x[N]) {
 // Jacobian is that map's inverse); the radiation block through the limited
 // inversion itself.  Where the MHD inversion failed the cell's P_mhd was the
 // guess: its cotangent goes to lamPg instead.
+template <class Geo>
 DEV void adj_c2p_at(Ctx C, const double* __restrict__ Ue, const double* __restrict__ P,
                     const int* __restrict__ st, const double* __restrict__ lamP,
                     double* __restrict__ lamUe, double* __restrict__ lamPg, long t) {
@@ -1380,7 +1390,7 @@ DEV void adj_c2p_at(Ctx C, const double* __restrict__ Ue, const double* __restri
   int i, j, k;
   interior_cell(C, t, i, j, k);
   const long c = cell_index(C, i, j, k);
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   const double igd = 1.0 / m.gdet;
   double lp[12], lu[12];
@@ -1439,10 +1449,11 @@ DEV void adj_c2p_at(Ctx C, const double* __restrict__ Ue, const double* __restri
   for (int q = 0; q < 12; q++) lamUe[q * C.Ntot + c] += lu[q];
 }
 
+template <class Geo>
 __global__ void LB(64) k_adj_c2p(Ctx C, const double* __restrict__ Ue, const double* __restrict__ P,
                                  const int* __restrict__ st, const double* __restrict__ lamP,
                                  double* __restrict__ lamUe, double* __restrict__ lamPg) {
-  adj_c2p_at(C, Ue, P, st, lamP, lamUe, lamPg, (long)blockIdx.x * blockDim.x + threadIdx.x);
+  adj_c2p_at<Geo>(C, Ue, P, st, lamP, lamUe, lamPg, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 DEV void copy_interior_at(Ctx C, const double* __restrict__ src, double* __restrict__ dst, long c) {
@@ -1456,6 +1467,6 @@ DEV void copy_interior_at(Ctx C, const double* __restrict__ src, double* __restr
   for (int q = 0; q < 12; q++) dst[q * C.Ntot + c] = in ? src[q * C.Ntot + c] : 0.0;
 }
 
-__global__ void LB(256) k_copy_interior(Ctx C, const double* __restrict__ src, double* __restrict__ dst) {
+static __global__ void LB(256) k_copy_interior(Ctx C, const double* __restrict__ src, double* __restrict__ dst) {
   copy_interior_at(C, src, dst, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }

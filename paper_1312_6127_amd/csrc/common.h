@@ -65,23 +65,120 @@ struct RealOf<float> {
   using type = float;
 };
 
-// Metric at one point, loaded from a table (rounded to R on the FP32 path).
+// Metric at one point.  lo, up: g_ab, g^ab; gam(i, j): the normal observer's
+// spatial inverse metric g^{ij} - g^{ti} g^{tj}/g^{tt}; zlo, zup, zgam: known
+// at compile time to vanish.  Three forms, and a kernel is compiled for the
+// ones it needs:
+//   DenseMetric  every component, for either space-time.  The adjoint, the
+//                FP32 face path and the batched solve: their results amplify
+//                the last bit of an intermediate (the 96x48x24 disk's gradient
+//                moves by 1e-6 when its input moves by one ulp; a batch's
+//                iteration counts and failed cells move likewise), so they
+//                keep one order of operations;
+//   KSMetric     Kerr-Schild without the components that vanish there;
+//   FlatMetric   Minkowski.
+// The FP64 step runs on the last two: products with a vanishing component are
+// never formed (a contraction keeps 10 of its 16 terms on Kerr-Schild, 4 in
+// flat space) and a point takes 16 registers or none instead of 22.
 template <class R>
-struct MetricT {
+struct DenseMetric {
+  static constexpr bool dense = true, diagonal = false;
   R gcov[10], gcon[10], gdet, alpha;
+  DEV static constexpr bool zlo(int, int) { return false; }
+  DEV static constexpr bool zup(int, int) { return false; }
+  DEV static constexpr bool zgam(int, int) { return false; }
   DEV R lo(int a, int b) const { return gcov[sym(a, b)]; }
   DEV R up(int a, int b) const { return gcon[sym(a, b)]; }
+  DEV R gam(int i, int j) const { return up(i + 1, j + 1) - up(0, i + 1) * up(0, j + 1) / up(0, 0); }
+  DEV void load(const double* tab, int npos, int pos) {
+#pragma unroll
+    for (int q = 0; q < 10; q++) gcov[q] = (R)tab[(GE_GCOV + q) * npos + pos];
+#pragma unroll
+    for (int q = 0; q < 10; q++) gcon[q] = (R)tab[(GE_GCON + q) * npos + pos];
+    gdet = (R)tab[GE_GDET * npos + pos];
+    alpha = (R)tab[GE_ALPHA * npos + pos];
+  }
 };
-using Metric = MetricT<double>;
 
 template <class R>
-DEV void load_metric(const double* tab, int npos, int pos, MetricT<R>& m) {
-#pragma unroll
-  for (int q = 0; q < 10; q++) m.gcov[q] = (R)tab[(GE_GCOV + q) * npos + pos];
-#pragma unroll
-  for (int q = 0; q < 10; q++) m.gcon[q] = (R)tab[(GE_GCON + q) * npos + pos];
-  m.gdet = (R)tab[GE_GDET * npos + pos];
-  m.alpha = (R)tab[GE_ALPHA * npos + pos];
+struct FlatMetric {
+  static constexpr bool dense = false, diagonal = true;
+  static constexpr R gdet = R(1.0), alpha = R(1.0);
+  DEV static constexpr bool zlo(int a, int b) { return a != b; }
+  DEV static constexpr bool zup(int a, int b) { return a != b; }
+  DEV static constexpr bool zgam(int i, int j) { return i != j; }
+  DEV static constexpr R lo(int a, int b) { return a != b ? R(0.0) : (a == 0 ? R(-1.0) : R(1.0)); }
+  DEV static constexpr R up(int a, int b) { return lo(a, b); }
+  DEV static constexpr R gam(int i, int j) { return lo(i + 1, j + 1); }
+  DEV void load(const double*, int, int) {}
+};
+
+template <class R>
+struct KSMetric {
+  static constexpr bool dense = false, diagonal = false;
+  R g00, g01, g03, g11, g13, g22, g33;
+  R u00, u01, u11, u13, u22, u33;
+  R gdet, alpha;
+  R gam11;
+  // tt, tr, t phi, rr, r phi, theta theta, phi phi; inverse: no t phi
+  DEV static constexpr bool zlo(int a, int b) { return (a == 2) != (b == 2); }
+  DEV static constexpr bool zup(int a, int b) { return zlo(a, b) || (a + b == 3 && a * b == 0); }
+  DEV static constexpr bool zgam(int i, int j) { return zlo(i + 1, j + 1); }
+  DEV R lo(int a, int b) const {
+    const int s = sym(a, b);
+    return s == 0 ? g00 : s == 1 ? g01 : s == 3 ? g03 : s == 4 ? g11 : s == 6 ? g13
+           : s == 7 ? g22 : s == 9 ? g33 : R(0.0);
+  }
+  DEV R up(int a, int b) const {
+    const int s = sym(a, b);
+    return s == 0 ? u00 : s == 1 ? u01 : s == 4 ? u11 : s == 6 ? u13 : s == 7 ? u22
+           : s == 9 ? u33 : R(0.0);
+  }
+  // g^{t theta} = g^{t phi} = 0: only the rr component differs from g^{ij}
+  DEV R gam(int i, int j) const { return (i == 0 && j == 0) ? gam11 : up(i + 1, j + 1); }
+  DEV void load(const double* tab, int npos, int pos) {
+    auto at = [&](int f) { return (R)tab[f * npos + pos]; };
+    g00 = at(GE_GCOV + sym(0, 0));
+    g01 = at(GE_GCOV + sym(0, 1));
+    g03 = at(GE_GCOV + sym(0, 3));
+    g11 = at(GE_GCOV + sym(1, 1));
+    g13 = at(GE_GCOV + sym(1, 3));
+    g22 = at(GE_GCOV + sym(2, 2));
+    g33 = at(GE_GCOV + sym(3, 3));
+    u00 = at(GE_GCON + sym(0, 0));
+    u01 = at(GE_GCON + sym(0, 1));
+    u11 = at(GE_GCON + sym(1, 1));
+    u13 = at(GE_GCON + sym(1, 3));
+    u22 = at(GE_GCON + sym(2, 2));
+    u33 = at(GE_GCON + sym(3, 3));
+    gdet = at(GE_GDET);
+    alpha = at(GE_ALPHA);
+    gam11 = u11 - u01 * u01 / u00;
+  }
+};
+
+// What a kernel is compiled for.
+struct KS {
+  DEV static constexpr bool curved(const Ctx&) { return true; }
+  template <class R>
+  using M = KSMetric<R>;
+};
+struct Flat {
+  DEV static constexpr bool curved(const Ctx&) { return false; }
+  template <class R>
+  using M = FlatMetric<R>;
+};
+struct Dense {
+  DEV static bool curved(const Ctx& C) { return C.metric == GRRMHD_KERR_SCHILD; }
+  template <class R>
+  using M = DenseMetric<R>;
+};
+
+using Metric = DenseMetric<double>;
+
+template <class M>
+DEV void load_metric(const double* tab, int npos, int pos, M& m) {
+  m.load(tab, npos, pos);
 }
 
 DEV void flat_metric(Metric& m) {

@@ -9,7 +9,7 @@
 #include <mutex>
 #include <string>
 
-#include "adjoint.h"
+#include "instances.h"
 #include "stag.h"
 
 struct grrmhd_grid {
@@ -78,6 +78,17 @@ static int fail(int code, const std::string& msg) {
     hipError_t e_ = hipGetLastError();                                                  \
     if (e_ != hipSuccess) return fail(GRRMHD_EHIP, std::string("launch: ") + hipGetErrorString(e_)); \
   } while (0)
+
+// Form of the arithmetic a caller needs: the step's closed forms, or the dense
+// order of operations that the adjoint and the Courant step keep.
+enum Form { STEP_FORM, DENSE_FORM };
+
+// the instance of a kernel for the form and the grid's space-time (further
+// template arguments after its name)
+#define GEO_KERNEL(g, form, kernel, ...)                                          \
+  ((form) == DENSE_FORM ? kernel<Dense __VA_OPT__(, ) __VA_ARGS__>                \
+   : (g)->C.metric == GRRMHD_KERR_SCHILD ? kernel<KS __VA_OPT__(, ) __VA_ARGS__>  \
+                                         : kernel<Flat __VA_OPT__(, ) __VA_ARGS__>)
 
 static inline unsigned nblocks(long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 
@@ -507,7 +518,7 @@ static int launch_flattener(grrmhd_grid* g, const double* P, const double* ca, c
   double* mf = nullptr;
   if (C.metric == GRRMHD_KERR_SCHILD) {
     mf = g->flat + 6 * (size_t)C.Ntot;
-    hipLaunchKernelGGL(k_mass_flux, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, g->stream, C, P, mf);
+    hipLaunchKernelGGL(k_mass_flux<Dense>, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, g->stream, C, P, mf);
     LAUNCHCHK();
   }
   long nb = 1;   // (cell, active direction) pairs
@@ -524,12 +535,18 @@ static int launch_flattener(grrmhd_grid* g, const double* P, const double* ca, c
   return 0;
 }
 
-static int launch_fluxes(grrmhd_grid* g, const double* P, const double* ca, const double* ce,
+// The faces that set a step's dt keep the dense form: a gradient taken at that
+// dt moves by 1e-6 with its last bit.
+#define STAG_KERNEL(g, ENTF)                                                   \
+  ((g)->C.metric == GRRMHD_KERR_SCHILD ? k_flux_all_stag<KS, double, ENTF>     \
+                                       : k_flux_all_stag<Flat, double, ENTF>)
+static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const double* ca, const double* ce,
                          double* F, double* emf, double* vch,
                          unsigned long long* dtmin = nullptr, int keep_flat = 0,
                          double* Fs = nullptr, const double* Bf = nullptr, double* VF = nullptr,
                          double* SP = nullptr) {
   const Ctx& C = g->C;
+  if (dtmin) form = DENSE_FORM;
   if (C.recon == GRRMHD_RECON_PPM) {
     const int rc = launch_flattener(g, P, ca, ce, keep_flat);
     if (rc) return rc;
@@ -555,19 +572,19 @@ static int launch_fluxes(grrmhd_grid* g, const double* P, const double* ca, cons
     const double* flp = (const double*)g->flat;
     if (S64.total > 0) {
       if (Fs)
-        hipLaunchKernelGGL((k_flux_all_stag<double, true>), dim3(nblocks(S64.total, 128)), dim3(128),
+        hipLaunchKernelGGL(STAG_KERNEL(g, true), dim3(nblocks(S64.total, 128)), dim3(128),
                            0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL((k_flux_all_stag<double, false>), dim3(nblocks(S64.total, 128)),
+        hipLaunchKernelGGL(STAG_KERNEL(g, false), dim3(nblocks(S64.total, 128)),
                            dim3(128), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
     if (S32.total > 0) {
       if (Fs)
-        hipLaunchKernelGGL((k_flux_all_stag<float, true>), dim3(nblocks(S32.total, 128)), dim3(128),
+        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, true>), dim3(nblocks(S32.total, 128)), dim3(128),
                            0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL((k_flux_all_stag<float, false>), dim3(nblocks(S32.total, 128)),
+        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, false>), dim3(nblocks(S32.total, 128)),
                            dim3(128), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
@@ -592,19 +609,19 @@ static int launch_fluxes(grrmhd_grid* g, const double* P, const double* ca, cons
   }
   if (S64.total > 0) {
     if (Fs)
-      hipLaunchKernelGGL(k_flux_all_s<double>, dim3(nblocks(S64.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all_s, double), dim3(nblocks(S64.total, 128)), dim3(128), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL(k_flux_all<double>, dim3(nblocks(S64.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all, double), dim3(nblocks(S64.total, 128)), dim3(128), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }
   if (S32.total > 0) {
     if (Fs)
-      hipLaunchKernelGGL(k_flux_all_s<float>, dim3(nblocks(S32.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL((k_flux_all_s<Dense, float>), dim3(nblocks(S32.total, 128)), dim3(128), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL(k_flux_all<float>, dim3(nblocks(S32.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL((k_flux_all<Dense, float>), dim3(nblocks(S32.total, 128)), dim3(128), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }
@@ -647,7 +664,7 @@ static int launch_timestep(grrmhd_grid* g, const double* vch, double* dt_dev) {
 }
 
 // dtmin set: dt = courant x *dtmin, stored in *dt_dev; *dtnext reset to +inf
-static int launch_update(grrmhd_grid* g, double a, double b, double c, const double* dt_dev,
+static int launch_update(grrmhd_grid* g, Form form, double a, double b, double c, const double* dt_dev,
                          const double* P, const double* Un, const double* Up, const double* F,
                          const double* emf, double* Ue, const unsigned long long* dtmin = nullptr,
                          unsigned long long* dtnext = nullptr, const MTerms* mt = nullptr,
@@ -655,7 +672,7 @@ static int launch_update(grrmhd_grid* g, double a, double b, double c, const dou
   MTerms MT;
   memset(&MT, 0, sizeof(MT));
   if (mt) MT = *mt;
-  hipLaunchKernelGGL(k_update, dim3(nblocks(n_interior(g->C), 256)), dim3(256), 0, g->stream,
+  hipLaunchKernelGGL(GEO_KERNEL(g, form, k_update), dim3(nblocks(n_interior(g->C), 256)), dim3(256), 0, g->stream,
                      g->C, a, b, c, const_cast<double*>(dt_dev), dtmin, dtnext, P, Un, Up, F, emf,
                      MT, Ue, Bface);
   LAUNCHCHK();
@@ -665,7 +682,7 @@ static int launch_update(grrmhd_grid* g, double a, double b, double c, const dou
 // fallback grid: enough waves to spread a long list, grid-stride beyond
 static unsigned list_blocks(long n) { return (unsigned)std::min<long>(nblocks(n, 64), 8192); }
 
-static int launch_implicit(grrmhd_grid* g, const double* Ue, const double* Pg, double scale,
+static int launch_implicit(grrmhd_grid* g, Form form, const double* Ue, const double* Pg, double scale,
                            const double* dt_dev, const double* ca, const double* ce, double* P,
                            double* U, int* it, int* st, double* err,
                            const double* Sexp = nullptr) {
@@ -681,7 +698,7 @@ static int launch_implicit(grrmhd_grid* g, const double* Ue, const double* Pg, d
                      (const int*)g->tkeys, g->torder);
   LAUNCHCHK();
   if (timed) HIPCHK(hipEventRecord(g->ev[2 * g->nt], g->stream));
-  hipLaunchKernelGGL(k_implicit, dim3((unsigned)g->ntiles), dim3(64), 0, g->stream, g->C,
+  hipLaunchKernelGGL(GEO_KERNEL(g, form, k_implicit), dim3((unsigned)g->ntiles), dim3(64), 0, g->stream, g->C,
                      g->tile_i, Ue, Pg, scale, dt_dev, ca, ce, P, U, it, st, err, W,
                      (const int*)g->torder, g->tkeys);
   LAUNCHCHK();
@@ -690,10 +707,10 @@ static int launch_implicit(grrmhd_grid* g, const double* Ue, const double* Pg, d
     g->nt++;
   }
   if (g->C.cascade)
-    hipLaunchKernelGGL(k_implicit_list<true>, dim3(list_blocks(n)), dim3(64), 0, g->stream, g->C,
+    hipLaunchKernelGGL((k_implicit_list<Dense, true>), dim3(list_blocks(n)), dim3(64), 0, g->stream, g->C,
                        Ue, Pg, scale, dt_dev, ca, ce, P, U, it, st, err, W, Sexp);
   else
-    hipLaunchKernelGGL(k_implicit_list<false>, dim3(list_blocks(n)), dim3(64), 0, g->stream, g->C,
+    hipLaunchKernelGGL(GEO_KERNEL(g, form, k_implicit_list, false), dim3(list_blocks(n)), dim3(64), 0, g->stream, g->C,
                        Ue, Pg, scale, dt_dev, ca, ce, P, U, it, st, err, W, Sexp);
   LAUNCHCHK();
   g->W.counter = W.counter;
@@ -701,12 +718,12 @@ static int launch_implicit(grrmhd_grid* g, const double* Ue, const double* Pg, d
   return 0;
 }
 
-static int launch_fixup(grrmhd_grid* g, double* P, double* U, int* st, double* scr, int* st_acc,
+static int launch_fixup(grrmhd_grid* g, Form form, double* P, double* U, int* st, double* scr, int* st_acc,
                         const int* it_stage, int* it_acc, int accumulate) {
   const long n = n_interior(g->C);
   hipLaunchKernelGGL(k_fixup_avg, dim3(nblocks(n, 256)), dim3(256), 0, g->stream, g->C, P, st, scr);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_fixup_apply, dim3(nblocks(n, 256)), dim3(256), 0, g->stream, g->C, P, U, st,
+  hipLaunchKernelGGL(GEO_KERNEL(g, form, k_fixup_apply), dim3(nblocks(n, 256)), dim3(256), 0, g->stream, g->C, P, U, st,
                      scr, st_acc, it_stage, it_acc, accumulate);
   LAUNCHCHK();
   return 0;
@@ -724,7 +741,7 @@ static int launch_fixup(grrmhd_grid* g, double* P, double* U, int* st, double* s
 extern "C" int grrmhd_prim_to_cons(grrmhd_grid* g, const double* P, double* U) {
   NEEDG();
   if (!P || !U) return fail(GRRMHD_EINVAL, "NULL array");
-  hipLaunchKernelGGL(k_p2u, dim3(nblocks(g->C.Ntot, 256)), dim3(256), 0, g->stream, g->C, P, U);
+  hipLaunchKernelGGL(k_p2u<Dense>, dim3(nblocks(g->C.Ntot, 256)), dim3(256), 0, g->stream, g->C, P, U);
   LAUNCHCHK();
   return 0;
 }
@@ -743,7 +760,7 @@ extern "C" int grrmhd_fluxes(grrmhd_grid* g, const double* P, const double* chi_
   HIPCHK(hipMemsetAsync(F, 0, sizeof(double) * 36 * N, g->stream));
   HIPCHK(hipMemsetAsync(emf, 0, sizeof(double) * 3 * N, g->stream));
   HIPCHK(hipMemsetAsync(vchar, 0, sizeof(double) * 3 * N, g->stream));
-  return launch_fluxes(g, P, chi_abs, chi_es, F, emf, vchar);
+  return launch_fluxes(g, STEP_FORM, P, chi_abs, chi_es, F, emf, vchar);
 }
 
 extern "C" int grrmhd_timestep(grrmhd_grid* g, const double* vchar, double* dt_dev) {
@@ -759,14 +776,14 @@ extern "C" int grrmhd_explicit_update(grrmhd_grid* g, double a, double b, double
   NEEDG();
   if (!dt_dev || !P || !Un || !F || !emf || !Uexp || (b != 0.0 && !Uprev))
     return fail(GRRMHD_EINVAL, "NULL array");
-  return launch_update(g, a, b, c, dt_dev, P, Un, Uprev, F, emf, Uexp);
+  return launch_update(g, STEP_FORM, a, b, c, dt_dev, P, Un, Uprev, F, emf, Uexp);
 }
 
 extern "C" int grrmhd_con2prim(grrmhd_grid* g, const double* U, const double* Pguess, double* P,
                                int* status) {
   NEEDG();
   if (!U || !Pguess || !P) return fail(GRRMHD_EINVAL, "NULL array");
-  hipLaunchKernelGGL(k_con2prim, dim3(nblocks(n_interior(g->C), 128)), dim3(128), 0, g->stream,
+  hipLaunchKernelGGL(GEO_KERNEL(g, STEP_FORM, k_con2prim), dim3(nblocks(n_interior(g->C), 128)), dim3(128), 0, g->stream,
                      g->C, U, Pguess, P, status, 0);
   LAUNCHCHK();
   return 0;
@@ -780,13 +797,20 @@ extern "C" int grrmhd_implicit_grid(grrmhd_grid* g, const double* Uexp, const do
   if (!Uexp || !Pguess || !dt_dev || !chi_abs || !chi_es || !P || !U)
     return fail(GRRMHD_EINVAL, "NULL array");
   if (U == Uexp) return fail(GRRMHD_EINVAL, "U may not alias Uexp");
-  return launch_implicit(g, Uexp, Pguess, dt_scale, dt_dev, chi_abs, chi_es, P, U, iters, status, err);
+  return launch_implicit(g, STEP_FORM, Uexp, Pguess, dt_scale, dt_dev, chi_abs, chi_es, P, U, iters, status, err);
 }
 
 extern "C" int grrmhd_fixup(grrmhd_grid* g, double* P, double* U, int* status, double* scratch) {
   NEEDG();
   if (!P || !U || !status || !scratch) return fail(GRRMHD_EINVAL, "NULL array");
-  return launch_fixup(g, P, U, status, scratch, nullptr, nullptr, nullptr, 0);
+  return launch_fixup(g, STEP_FORM, P, U, status, scratch, nullptr, nullptr, nullptr, 0);
+}
+
+// A step at a given dt gives what the adjoint's forward step gives, bit for
+// bit (an autograd forward can be either); one that sets its own dt is free of
+// that, as is the staggered field, which has no adjoint.
+static Form step_form(int dt_fixed, const double* Bf) {
+  return (dt_fixed && !Bf) ? DENSE_FORM : STEP_FORM;
 }
 
 // One step of an IMEX scheme (stage table above).  The latest primitives
@@ -800,6 +824,7 @@ static int imex_step(grrmhd_grid* g, double* P, double* U, double* Bf, const dou
                      const double* chi_es, double* dt_dev, int dt_fixed, int* status, int* iters,
                      char* base, const WsLayout& w) {
   const Ctx& C = g->C;
+  const Form form = step_form(dt_fixed, Bf);
   const Scheme S = make_scheme(g->p.scheme);
   const size_t N = (size_t)C.Ntot;
   double* F = (double*)(base + w.F);
@@ -842,7 +867,7 @@ static int imex_step(grrmhd_grid* g, double* P, double* U, double* Bf, const dou
   const size_t b1 = round256(sizeof(double) * N);
   auto MSk = [&](int k) { return (double*)(base + w.MS + k * b1); };
   if (C.cascade) {
-    hipLaunchKernelGGL(k_entropy_field, dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C, P, Sn);
+    hipLaunchKernelGGL(GEO_KERNEL(g, form, k_entropy_field), dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C, P, Sn);
     LAUNCHCHK();
   }
   double* Pcur = P;
@@ -863,7 +888,7 @@ static int imex_step(grrmhd_grid* g, double* P, double* U, double* Bf, const dou
                            Bcur);
         LAUNCHCHK();
       }
-      if ((rc = launch_fluxes(g, Pcur, chi_abs, chi_es, F, emf, vch, dmin, nflux > 0, Fs, Bcur,
+      if ((rc = launch_fluxes(g, form, Pcur, chi_abs, chi_es, F, emf, vch, dmin, nflux > 0, Fs, Bcur,
                               VF, SP)))
         return rc;
       nflux++;
@@ -886,13 +911,13 @@ static int imex_step(grrmhd_grid* g, double* P, double* U, double* Bf, const dou
       MT.n++;
     }
     const double* Uj = (x.j >= 0) ? Us[x.j] : U;
-    if ((rc = launch_update(g, x.a, x.b, x.c, dt_dev, Pcur, U, Uj, F, emf, Ue, dmin, dnext, &MT,
+    if ((rc = launch_update(g, form, x.a, x.b, x.c, dt_dev, Pcur, U, Uj, F, emf, Ue, dmin, dnext, &MT,
                             Bf ? Bst(i) : nullptr)))
       return rc;
     if (red) g->dtp ^= 1;
     if (C.cascade && x.g > 0.0) {
       // the b term's stage is the previous one (checked above): Pcur
-      hipLaunchKernelGGL(k_entropy_update, dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_entropy_update), dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C,
                          x.a, x.b, x.c, (const double*)dt_dev, (const double*)Sn,
                          (const double*)Pcur, (const double*)Fs, Sexp);
       LAUNCHCHK();
@@ -908,7 +933,7 @@ static int imex_step(grrmhd_grid* g, double* P, double* U, double* Bf, const dou
     double* Pout = last ? P : Pa;
     double* Uout = last ? U : Us[i];
     if (x.g > 0.0) {
-      if ((rc = launch_implicit(g, Ue, Pcur, x.g, dt_dev, chi_abs, chi_es, Pout, Uout, it, st, err,
+      if ((rc = launch_implicit(g, form, Ue, Pcur, x.g, dt_dev, chi_abs, chi_es, Pout, Uout, it, st, err,
                                 Sexp)))
         return rc;
       if (i < 4 && S.keep_m[i]) {   // the stage's source, before the fix-ups
@@ -916,23 +941,23 @@ static int imex_step(grrmhd_grid* g, double* P, double* U, double* Bf, const dou
                            Uout, st, x.g, dt_dev, Mk[i]);
         LAUNCHCHK();
         if (C.cascade) {
-          hipLaunchKernelGGL(k_stage_ms, dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C,
+          hipLaunchKernelGGL(GEO_KERNEL(g, form, k_stage_ms), dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C,
                              (const double*)Pout, (const double*)Sexp, (const int*)st, x.g,
                              (const double*)dt_dev, MSk(i));
           LAUNCHCHK();
         }
       }
-      if ((rc = launch_fixup(g, Pout, Uout, st, Ue, status, it, iters, i > 0))) return rc;
+      if ((rc = launch_fixup(g, form, Pout, Uout, st, Ue, status, it, iters, i > 0))) return rc;
     } else {
       // final explicit combination: MHD and radiation inversions; a failed
       // MHD inversion makes a failed cell (neighbour average in the fix-up)
-      hipLaunchKernelGGL(k_con2prim, dim3(nblocks(nint, 128)), dim3(128), 0, g->stream, C, Ue,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_con2prim), dim3(nblocks(nint, 128)), dim3(128), 0, g->stream, C, Ue,
                          Pcur, Pout, st, (int)GRRMHD_ST_FAIL);
       LAUNCHCHK();
       hipLaunchKernelGGL(k_copy_interior12, dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C,
                          Ue, Uout);
       LAUNCHCHK();
-      if ((rc = launch_fixup(g, Pout, Uout, st, Ue, status, nullptr, iters, i > 0))) return rc;
+      if ((rc = launch_fixup(g, form, Pout, Uout, st, Ue, status, nullptr, iters, i > 0))) return rc;
     }
     Pcur = Pout;
     Bcur = Bf ? Bst(i) : nullptr;
@@ -946,6 +971,7 @@ static int rk3_step(grrmhd_grid* g, double* P, double* U, double* Bf, const doub
                     const double* chi_es, double* dt_dev, int dt_fixed, int* status, int* iters,
                     char* base, const WsLayout& w) {
   const Ctx& C = g->C;
+  const Form form = step_form(dt_fixed, Bf);
   double* F = (double*)(base + w.F);
   double* emf = (double*)(base + w.emf);
   double* vch = (double*)(base + w.vch);
@@ -967,7 +993,7 @@ static int rk3_step(grrmhd_grid* g, double* P, double* U, double* Bf, const doub
   double* Sexp = C.cascade ? Ue + 12 * N : nullptr;
   const long nint = n_interior(C);
   if (C.cascade) {
-    hipLaunchKernelGGL(k_entropy_field, dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C, P, Sn);
+    hipLaunchKernelGGL(GEO_KERNEL(g, form, k_entropy_field), dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C, P, Sn);
     LAUNCHCHK();
   }
   // staggered field: stage inputs Bf, B1, B2; outputs B1, B2, Bf
@@ -1000,7 +1026,7 @@ static int rk3_step(grrmhd_grid* g, double* P, double* U, double* Bf, const doub
     const bool red = (s == 0 && !dt_fixed);
     unsigned long long* dmin = red ? g->dtstep[g->dtp] : nullptr;
     unsigned long long* dnext = red ? g->dtstep[g->dtp ^ 1] : nullptr;
-    if ((rc = launch_fluxes(g, Pin, chi_abs, chi_es, F, emf, vch, dmin, s > 0, Fs, Bin, VF, SP)))
+    if ((rc = launch_fluxes(g, form, Pin, chi_abs, chi_es, F, emf, vch, dmin, s > 0, Fs, Bin, VF, SP)))
       return rc;
     if (Bf) {
       // the stage's faces (before the cell update, which averages them)
@@ -1011,20 +1037,20 @@ static int rk3_step(grrmhd_grid* g, double* P, double* U, double* Bf, const doub
                          Bst[s]);
       LAUNCHCHK();
     }
-    if ((rc = launch_update(g, A[s], B[s], Cc[s], dt_dev, Pin, U, Uprev, F, emf, Ue, dmin, dnext,
+    if ((rc = launch_update(g, form, A[s], B[s], Cc[s], dt_dev, Pin, U, Uprev, F, emf, Ue, dmin, dnext,
                             nullptr, Bf ? Bst[s] : nullptr)))
       return rc;
     if (red) g->dtp ^= 1;
     if (C.cascade) {
-      hipLaunchKernelGGL(k_entropy_update, dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_entropy_update), dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C,
                          A[s], B[s], Cc[s], (const double*)dt_dev, (const double*)Sn,
                          (const double*)Pin, (const double*)Fs, Sexp);
       LAUNCHCHK();
     }
-    if ((rc = launch_implicit(g, Ue, Pin, Cc[s], dt_dev, chi_abs, chi_es, Pout, Uout, it, st, err,
+    if ((rc = launch_implicit(g, form, Ue, Pin, Cc[s], dt_dev, chi_abs, chi_es, Pout, Uout, it, st, err,
                               Sexp)))
       return rc;
-    if ((rc = launch_fixup(g, Pout, Uout, st, Ue, status, it, iters, s > 0))) return rc;
+    if ((rc = launch_fixup(g, form, Pout, Uout, st, Ue, status, it, iters, s > 0))) return rc;
   }
   return 0;
 }
@@ -1105,7 +1131,7 @@ extern "C" int grrmhd_fluxes_staggered(grrmhd_grid* g, const double* P, const do
   HIPCHK(hipMemsetAsync(emf, 0, sizeof(double) * 3 * N, g->stream));
   HIPCHK(hipMemsetAsync(vchar, 0, sizeof(double) * 3 * N, g->stream));
   char* base = (char*)workspace;
-  return launch_fluxes(g, P, chi_abs, chi_es, F, emf, vchar, nullptr, 0, nullptr, Bf,
+  return launch_fluxes(g, STEP_FORM, P, chi_abs, chi_es, F, emf, vchar, nullptr, 0, nullptr, Bf,
                        (double*)(base + w.VF), (double*)(base + w.SP));
 }
 
@@ -1211,11 +1237,11 @@ static int adj_implicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
   int rc;
   if ((rc = fill_d(g, lamUe, 12 * (size_t)C.Ntot, 0.0))) return rc;
   if (Se && lamS)
-    hipLaunchKernelGGL(k_adj_implicit<true>, dim3(nblocks(n_interior(C), 64)), dim3(64), 0,
+    hipLaunchKernelGGL((k_adj_implicit<Dense, true>), dim3(nblocks(n_interior(C), 64)), dim3(64), 0,
                        g->stream, C, scale, dt_dev, Ue, Pk, st, ca, ce, lamP, lamU, lamUe, gchi, Se,
                        lamS);
   else
-    hipLaunchKernelGGL(k_adj_implicit<false>, dim3(nblocks(n_interior(C), 64)), dim3(64), 0,
+    hipLaunchKernelGGL((k_adj_implicit<Dense, false>), dim3(nblocks(n_interior(C), 64)), dim3(64), 0,
                        g->stream, C, scale, dt_dev, Ue, Pk, st, ca, ce, lamP, lamU, lamUe, gchi,
                        nullptr, nullptr);
   LAUNCHCHK();
@@ -1269,7 +1295,7 @@ static int adj_explicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
     double* GFd = ppm ? GF + (size_t)d * 4 * N : nullptr;
     const dim3 gr(nblocks(R.total, 64)), bl(64);
 #define ADJ_FLUX(D, PPM)                                                                      \
-  hipLaunchKernelGGL((k_adj_flux<D, PPM>), gr, bl, 0, s, C, R, scale, dt_dev, Pb, ca, ce, lamUe, \
+  hipLaunchKernelGGL((k_adj_flux<Dense, D, PPM>), gr, bl, 0, s, C, R, scale, dt_dev, Pb, ca, ce, lamUe, \
                      (const double*)lamE, Gd, Gxd, fl, GFd, lamS)
     if (ppm) {
       if (d == 0) ADJ_FLUX(1, true);
@@ -1294,7 +1320,7 @@ static int adj_explicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
   LAUNCHCHK();
   if (C.metric != GRRMHD_MINKOWSKI) {
     const long ncell = (long)C.n[0] * C.n[1] * C.n[2];
-    hipLaunchKernelGGL(k_adj_geom, dim3(nblocks(ncell, 64)), dim3(64), 0, s, C, scale, dt_dev, Pb,
+    hipLaunchKernelGGL(k_adj_geom<Dense>, dim3(nblocks(ncell, 64)), dim3(64), 0, s, C, scale, dt_dev, Pb,
                        lamUe, lamPb);
     LAUNCHCHK();
   }
@@ -1314,7 +1340,7 @@ static int adj_explicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
     double* mf = nullptr;
     if (C.metric == GRRMHD_KERR_SCHILD) {
       mf = g->flat + 6 * N;
-      hipLaunchKernelGGL(k_mass_flux, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, Pb, mf);
+      hipLaunchKernelGGL(k_mass_flux<Dense>, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, Pb, mf);
       LAUNCHCHK();
     }
     hipLaunchKernelGGL(k_adj_flat, dim3(nblocks(C.Ntot, 128)), dim3(128), 0, s, C, Pb, ca, ce,
@@ -1322,7 +1348,7 @@ static int adj_explicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
     LAUNCHCHK();
   }
   if (lamS && bS != 0.0) {
-    hipLaunchKernelGGL(k_adj_entropy_field, dim3(nblocks(n_interior(C), 128)), dim3(128), 0, s, C,
+    hipLaunchKernelGGL(k_adj_entropy_field<Dense>, dim3(nblocks(n_interior(C), 128)), dim3(128), 0, s, C,
                        bS, Pb, lamS, lamPb);
     LAUNCHCHK();
   }
@@ -1424,7 +1450,7 @@ extern "C" int grrmhd_fixup_vjp(grrmhd_grid* g, const double* P, const int* stat
   const long nint = n_interior(C);
   int rc;
   if ((rc = fill_d(g, gP_pre, N12, 0.0)) || (rc = fill_d(g, gU_pre, N12, 0.0))) return rc;
-  hipLaunchKernelGGL(k_adj_fixup_own, dim3(nblocks(nint, 128)), dim3(128), 0, g->stream, C, P,
+  hipLaunchKernelGGL(k_adj_fixup_own<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, g->stream, C, P,
                      (const double*)nullptr, status, gP, gU, scratch);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_adj_fixup, dim3(nblocks(nint, 256)), dim3(256), 0, g->stream, C, 0, status,
@@ -1443,7 +1469,7 @@ extern "C" int grrmhd_con2prim_vjp(grrmhd_grid* g, const double* U, const double
   const size_t N12 = 12 * (size_t)g->C.Ntot;
   int rc;
   if ((rc = fill_d(g, gU, N12, 0.0)) || (rc = fill_d(g, gPguess, N12, 0.0))) return rc;
-  hipLaunchKernelGGL(k_adj_c2p, dim3(nblocks(n_interior(g->C), 64)), dim3(64), 0, g->stream, g->C,
+  hipLaunchKernelGGL(k_adj_c2p<Dense>, dim3(nblocks(n_interior(g->C), 64)), dim3(64), 0, g->stream, g->C,
                      U, P, status, gP, gU, gPguess);
   LAUNCHCHK();
   return 0;
@@ -1551,11 +1577,11 @@ static int adj_forward(grrmhd_grid* g, const double* P_n, const double* chi_abs,
   hipStream_t s = g->stream;
   int rc;
   HIPCHK(hipMemcpyAsync(a.Pb, P_n, B12, hipMemcpyDeviceToDevice, s));
-  hipLaunchKernelGGL(k_p2u, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, a.Pb, a.Un);
+  hipLaunchKernelGGL(k_p2u<Dense>, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, a.Pb, a.Un);
   LAUNCHCHK();
   const bool ent = C.cascade != 0;
   if (ent) {
-    hipLaunchKernelGGL(k_entropy_field, dim3(nblocks(n_interior(C), 256)), dim3(256), 0, s, C,
+    hipLaunchKernelGGL(k_entropy_field<Dense>, dim3(nblocks(n_interior(C), 256)), dim3(256), 0, s, C,
                        (const double*)a.Pb, a.Sn);
     LAUNCHCHK();
   }
@@ -1567,27 +1593,27 @@ static int adj_forward(grrmhd_grid* g, const double* P_n, const double* chi_abs,
     int* st = a.stk + k * N;
     if (k > 0) HIPCHK(hipMemcpyAsync(Pin, a.Pk + (k - 1) * N12, B12, hipMemcpyDeviceToDevice, s));
     if ((rc = launch_bc(g, Pin))) return rc;
-    if ((rc = launch_fluxes(g, Pin, chi_abs, chi_es, a.F, a.emf, a.vch, nullptr, k > 0,
+    if ((rc = launch_fluxes(g, DENSE_FORM, Pin, chi_abs, chi_es, a.F, a.emf, a.vch, nullptr, k > 0,
                             ent ? a.Fs : nullptr)))
       return rc;
     if ((rc = adj_keep_flat(g, a, k))) return rc;
-    if ((rc = launch_update(g, ADJ_A[k], ADJ_B[k], ADJ_C[k], dt_dev, Pin, a.Un,
+    if ((rc = launch_update(g, DENSE_FORM, ADJ_A[k], ADJ_B[k], ADJ_C[k], dt_dev, Pin, a.Un,
                             k == 0 ? a.Un : a.Uk + (k - 1) * N12, a.F, a.emf, Uek)))
       return rc;
     double* Sek = ent ? a.Se + k * N : nullptr;
     if (ent) {
-      hipLaunchKernelGGL(k_entropy_update, dim3(nblocks(n_interior(C), 256)), dim3(256), 0, s, C,
+      hipLaunchKernelGGL(k_entropy_update<Dense>, dim3(nblocks(n_interior(C), 256)), dim3(256), 0, s, C,
                          ADJ_A[k], ADJ_B[k], ADJ_C[k], dt_dev, (const double*)a.Sn,
                          (const double*)Pin, (const double*)a.Fs, Sek);
       LAUNCHCHK();
     }
     HIPCHK(hipMemcpyAsync(Pout, Pin, B12, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemcpyAsync(Uout, Uek, B12, hipMemcpyDeviceToDevice, s));
-    if ((rc = launch_implicit(g, Uek, Pin, ADJ_C[k], dt_dev, chi_abs, chi_es, Pout, Uout, a.it, st,
+    if ((rc = launch_implicit(g, DENSE_FORM, Uek, Pin, ADJ_C[k], dt_dev, chi_abs, chi_es, Pout, Uout, a.it, st,
                               a.err, Sek)))
       return rc;
     HIPCHK(hipMemcpyAsync(a.Pq + k * N12, Pout, B12, hipMemcpyDeviceToDevice, s));
-    if ((rc = launch_fixup(g, Pout, Uout, st, a.scr, nullptr, a.it, nullptr, 0))) return rc;
+    if ((rc = launch_fixup(g, DENSE_FORM, Pout, Uout, st, a.scr, nullptr, a.it, nullptr, 0))) return rc;
   }
   if (P_next) HIPCHK(hipMemcpyAsync(P_next, a.Pk + 2 * N12, B12, hipMemcpyDeviceToDevice, s));
   if (U_next) {   // interior of the last stage over U(P_n) (ghost entries kept)
@@ -1622,7 +1648,7 @@ static int adj_reverse(grrmhd_grid* g, const double* chi_abs, const double* chi_
     const double* Pin = a.Pb + k * N12;
     // fix-up of failed and cold cells, then the implicit solve
     const double* Pq = a.Pq + k * N12;   // the solve's output
-    hipLaunchKernelGGL(k_adj_fixup_own, dim3(nblocks(nint, 128)), dim3(128), 0, s, C,
+    hipLaunchKernelGGL(k_adj_fixup_own<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C,
                        (const double*)(a.Pk + k * N12), Pq, (const int*)(a.stk + k * N),
                        (const double*)a.lamP, (const double*)a.lamU, a.Lam);
     LAUNCHCHK();
@@ -1651,11 +1677,11 @@ static int adj_reverse(grrmhd_grid* g, const double* chi_abs, const double* chi_
     hipLaunchKernelGGL(k_copy_interior, dim3(ga), dim3(256), 0, s, C, (const double*)a.lamPb, a.lamP);
     LAUNCHCHK();
   }
-  hipLaunchKernelGGL(k_adj_p2u, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, (const double*)a.Pb,
+  hipLaunchKernelGGL(k_adj_p2u<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, (const double*)a.Pb,
                      (const double*)a.lamUn, a.lamP);
   LAUNCHCHK();
   if (ent) {   // U_S(P^n) of every stage's tracer
-    hipLaunchKernelGGL(k_adj_entropy_field, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 1.0,
+    hipLaunchKernelGGL(k_adj_entropy_field<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 1.0,
                        (const double*)a.Pb, (const double*)a.lamSn, a.lamP);
     LAUNCHCHK();
   }
@@ -1679,11 +1705,11 @@ static int adj_forward_imex(grrmhd_grid* g, const double* P_n, const double* chi
   hipStream_t s = g->stream;
   int rc;
   HIPCHK(hipMemcpyAsync(a.Pb, P_n, B12, hipMemcpyDeviceToDevice, s));
-  hipLaunchKernelGGL(k_p2u, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, a.Pb, a.Un);
+  hipLaunchKernelGGL(k_p2u<Dense>, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, a.Pb, a.Un);
   LAUNCHCHK();
   const bool ent = C.cascade != 0;
   if (ent) {
-    hipLaunchKernelGGL(k_entropy_field, dim3(nblocks(nint, 256)), dim3(256), 0, s, C,
+    hipLaunchKernelGGL(k_entropy_field<Dense>, dim3(nblocks(nint, 256)), dim3(256), 0, s, C,
                        (const double*)a.Pb, a.Sn);
     LAUNCHCHK();
   }
@@ -1698,7 +1724,7 @@ static int adj_forward_imex(grrmhd_grid* g, const double* P_n, const double* chi
     if (i > 0) HIPCHK(hipMemcpyAsync(Pin, a.Pk + (i - 1) * N12, B12, hipMemcpyDeviceToDevice, s));
     if (x.c != 0.0) {
       if ((rc = launch_bc(g, Pin))) return rc;
-      if ((rc = launch_fluxes(g, Pin, chi_abs, chi_es, a.F, a.emf, a.vch, nullptr, nflux > 0,
+      if ((rc = launch_fluxes(g, DENSE_FORM, Pin, chi_abs, chi_es, a.F, a.emf, a.vch, nullptr, nflux > 0,
                               ent ? a.Fs : nullptr)))
         return rc;
       if ((rc = adj_keep_flat(g, a, i))) return rc;
@@ -1713,12 +1739,12 @@ static int adj_forward_imex(grrmhd_grid* g, const double* P_n, const double* chi
       MT.n++;
     }
     const double* Uj = (x.j >= 0) ? a.Uk + x.j * N12 : a.Un;
-    if ((rc = launch_update(g, x.a, x.b, x.c, dt_dev, Pin, a.Un, Uj, a.F, a.emf, Uei, nullptr,
+    if ((rc = launch_update(g, DENSE_FORM, x.a, x.b, x.c, dt_dev, Pin, a.Un, Uj, a.F, a.emf, Uei, nullptr,
                             nullptr, &MT)))
       return rc;
     double* Sei = (ent && x.g > 0.0) ? a.Se + i * N : nullptr;
     if (Sei) {
-      hipLaunchKernelGGL(k_entropy_update, dim3(nblocks(nint, 256)), dim3(256), 0, s, C, x.a, x.b,
+      hipLaunchKernelGGL(k_entropy_update<Dense>, dim3(nblocks(nint, 256)), dim3(256), 0, s, C, x.a, x.b,
                          x.c, dt_dev, (const double*)a.Sn, (const double*)Pin,
                          (const double*)a.Fs, Sei);
       LAUNCHCHK();
@@ -1734,7 +1760,7 @@ static int adj_forward_imex(grrmhd_grid* g, const double* P_n, const double* chi
     HIPCHK(hipMemcpyAsync(Pout, Pin, B12, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipMemcpyAsync(Uout, Uei, B12, hipMemcpyDeviceToDevice, s));
     if (x.g > 0.0) {
-      if ((rc = launch_implicit(g, Uei, Pin, x.g, dt_dev, chi_abs, chi_es, Pout, Uout, a.it, st,
+      if ((rc = launch_implicit(g, DENSE_FORM, Uei, Pin, x.g, dt_dev, chi_abs, chi_es, Pout, Uout, a.it, st,
                                 a.err, Sei)))
         return rc;
       HIPCHK(hipMemcpyAsync(a.Pq + i * N12, Pout, B12, hipMemcpyDeviceToDevice, s));
@@ -1743,19 +1769,19 @@ static int adj_forward_imex(grrmhd_grid* g, const double* P_n, const double* chi
                            x.g, dt_dev, a.M + i * 8 * N);
         LAUNCHCHK();
         if (ent) {
-          hipLaunchKernelGGL(k_stage_ms, dim3(nblocks(nint, 256)), dim3(256), 0, s, C,
+          hipLaunchKernelGGL(k_stage_ms<Dense>, dim3(nblocks(nint, 256)), dim3(256), 0, s, C,
                              (const double*)Pout, (const double*)Sei, (const int*)st, x.g, dt_dev,
                              a.MS + i * N);
           LAUNCHCHK();
         }
       }
-      if ((rc = launch_fixup(g, Pout, Uout, st, a.scr, nullptr, a.it, nullptr, 0))) return rc;
+      if ((rc = launch_fixup(g, DENSE_FORM, Pout, Uout, st, a.scr, nullptr, a.it, nullptr, 0))) return rc;
     } else {
-      hipLaunchKernelGGL(k_con2prim, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, Uei,
+      hipLaunchKernelGGL(k_con2prim<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, Uei,
                          (const double*)Pin, Pout, st, (int)GRRMHD_ST_FAIL);
       LAUNCHCHK();
       HIPCHK(hipMemcpyAsync(a.Pq + i * N12, Pout, B12, hipMemcpyDeviceToDevice, s));
-      if ((rc = launch_fixup(g, Pout, Uout, st, a.scr, nullptr, nullptr, nullptr, 0))) return rc;
+      if ((rc = launch_fixup(g, DENSE_FORM, Pout, Uout, st, a.scr, nullptr, nullptr, nullptr, 0))) return rc;
     }
   }
   const int l = S.ns - 1;
@@ -1812,7 +1838,7 @@ static int adj_reverse_imex(grrmhd_grid* g, const double* chi_abs, const double*
     const int* st = a.stk + i * N;
     const double* lamUo = a.lamUs + i * N12;
     const double* Pq = a.Pq + i * N12;   // the solve's or inversion's output
-    hipLaunchKernelGGL(k_adj_fixup_own, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, Pk, Pq, st,
+    hipLaunchKernelGGL(k_adj_fixup_own<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, Pk, Pq, st,
                        (const double*)a.lamP, lamUo, a.Lam);
     LAUNCHCHK();
     hipLaunchKernelGGL(k_adj_fixup, dim3(gi), dim3(256), 0, s, C, 1, st, (const double*)a.Lam,
@@ -1828,7 +1854,7 @@ static int adj_reverse_imex(grrmhd_grid* g, const double* chi_abs, const double*
         LAUNCHCHK();
       }
       if (km && ent) {
-        hipLaunchKernelGGL(k_adj_stage_ms, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 0, x.g,
+        hipLaunchKernelGGL(k_adj_stage_ms<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 0, x.g,
                            dt_dev, st, Pq, (const double*)(a.lamMS + i * N), a.lamPpre, nullptr);
         LAUNCHCHK();
       }
@@ -1841,7 +1867,7 @@ static int adj_reverse_imex(grrmhd_grid* g, const double* chi_abs, const double*
         LAUNCHCHK();
       }
       if (km && ent) {
-        hipLaunchKernelGGL(k_adj_stage_ms, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 1, x.g,
+        hipLaunchKernelGGL(k_adj_stage_ms<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 1, x.g,
                            dt_dev, st, Pq, (const double*)(a.lamMS + i * N), nullptr, a.lamS);
         LAUNCHCHK();
       }
@@ -1850,7 +1876,7 @@ static int adj_reverse_imex(grrmhd_grid* g, const double* chi_abs, const double*
                          a.lamUe);
       LAUNCHCHK();
       if ((rc = fill_d(g, a.lamPg, N12, 0.0))) return rc;
-      hipLaunchKernelGGL(k_adj_c2p, dim3(nblocks(nint, 64)), dim3(64), 0, s, C, Uei,
+      hipLaunchKernelGGL(k_adj_c2p<Dense>, dim3(nblocks(nint, 64)), dim3(64), 0, s, C, Uei,
                          Pq, st, (const double*)a.lamPpre, a.lamUe, a.lamPg);
       LAUNCHCHK();
     }
@@ -1893,7 +1919,7 @@ static int adj_reverse_imex(grrmhd_grid* g, const double* chi_abs, const double*
     } else {
       if ((rc = fill_d(g, a.lamP, N12, 0.0))) return rc;
       if (tr && x.b != 0.0) {   // the tracer's b U_S(P_in) term without a flux
-        hipLaunchKernelGGL(k_adj_entropy_field, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, x.b,
+        hipLaunchKernelGGL(k_adj_entropy_field<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, x.b,
                            Pin, (const double*)a.lamS, a.lamP);
         LAUNCHCHK();
       }
@@ -1904,11 +1930,11 @@ static int adj_reverse_imex(grrmhd_grid* g, const double* chi_abs, const double*
       LAUNCHCHK();
     }
   }
-  hipLaunchKernelGGL(k_adj_p2u, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, (const double*)a.Pb,
+  hipLaunchKernelGGL(k_adj_p2u<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, (const double*)a.Pb,
                      (const double*)a.lamUn, a.lamP);
   LAUNCHCHK();
   if (ent) {   // U_S(P^n) of every stage's tracer
-    hipLaunchKernelGGL(k_adj_entropy_field, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 1.0,
+    hipLaunchKernelGGL(k_adj_entropy_field<Dense>, dim3(nblocks(nint, 128)), dim3(128), 0, s, C, 1.0,
                        (const double*)a.Pb, (const double*)a.lamSn, a.lamP);
     LAUNCHCHK();
   }
@@ -2052,13 +2078,13 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   HIPCHK(hipGetDevice(&dev));
   HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
   if (mode == GRRMHD_IMPLICIT_PER_CELL) {
-    hipLaunchKernelGGL(k_implicit_batch, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
+    hipLaunchKernelGGL(k_implicit_batch<Dense>, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
                        dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W);
     LAUNCHCHK();
   } else if (mode == GRRMHD_IMPLICIT_PERSISTENT) {
     const long waves = (long)ncu * waves_per_cu;
     const long blocks = std::max<long>(1, std::min<long>(waves * 64 / block, nblocks(n, block)));
-    hipLaunchKernelGGL(k_implicit_persist, dim3((unsigned)blocks), dim3(block), 0, s, C, n, U_expl,
+    hipLaunchKernelGGL(k_implicit_persist<Dense>, dim3((unsigned)blocks), dim3(block), 0, s, C, n, U_expl,
                        P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, next, W);
     LAUNCHCHK();
   } else {
@@ -2067,7 +2093,7 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
     int* q1 = (int*)(extra + qb);
     double* sd = (double*)(extra + 2 * qb);
     int* si = (int*)(extra + 2 * qb + round256(sizeof(double) * LS_ND * (size_t)n));
-    hipLaunchKernelGGL(k_iter_start, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
+    hipLaunchKernelGGL(k_iter_start<Dense>, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
                        dt_cell, chi_abs, chi_es, sd, si, qc, q0, W);
     LAUNCHCHK();
     // every attempt ends within max_iter trips (+3 round-off trips are inside it)
@@ -2078,7 +2104,7 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
       int* cout = qc + 1 - (t % 2);
       hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, s, cout, 1);
       LAUNCHCHK();
-      hipLaunchKernelGGL(k_iter_step, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl, dt_cell,
+      hipLaunchKernelGGL(k_iter_step<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl, dt_cell,
                          chi_abs, chi_es, sd, si, (const int*)cin, (const int*)qin, cout, qout,
                          P_out, U_out, iters, status, err, W);
       LAUNCHCHK();
@@ -2088,21 +2114,21 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   // (one wavefront per SIMD: the kernel holds ~470 registers per lane), then
   // the deferred extreme cells one thread each
   const long cwaves = std::max<long>(1, std::min<long>(4L * ncu, nblocks(n, 64)));
-  hipLaunchKernelGGL(k_cascade_urad, dim3((unsigned)cwaves), dim3(64), 0, s, C, n, U_expl, P_guess,
+  hipLaunchKernelGGL(k_cascade_urad<Dense>, dim3((unsigned)cwaves), dim3(64), 0, s, C, n, U_expl, P_guess,
                      dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, cursor, D, K);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_implicit_batch_list, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
+  hipLaunchKernelGGL(k_implicit_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
                      P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, D, K);
   LAUNCHCHK();
   // the full cascade's rest for the cells the PMHD and URAD attempts left
   // unaccepted (K holds their record slots), the cold limit inline
   if (C.cascade) {
-    hipLaunchKernelGGL(k_rest_batch_list, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
+    hipLaunchKernelGGL(k_rest_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
                        P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, K);
     LAUNCHCHK();
   } else if (C.cold && C.u_floor > 0.0) {
     // cells with no energy solution: the cold MHD limit, one thread each
-    hipLaunchKernelGGL(k_cold_batch_list, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
+    hipLaunchKernelGGL(k_cold_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
                        P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, K);
     LAUNCHCHK();
   }

@@ -29,14 +29,16 @@
 
 enum { M_PMHD = 0, M_URAD = 1, M_PRAD = 2 };
 
-struct Cell {
-  Metric m;
+template <class M>
+struct CellT {
+  M m;
   double rhout, B[3];
   double Tgi[4], Ri[4];   // explicit gas (T^t_t + rho u^t, T^t_i) and radiation R^t_nu
   double dt, chi_abs, chi_es;
   int cold;               // cold MHD: energy residuals left out of the errors
   double Si;              // explicit [S u^t]_(i) per sqrt(-g) (NAN: none); entropy methods
 };
+using Cell = CellT<Metric>;
 
 struct Eval {
   double x[4];
@@ -59,12 +61,14 @@ struct Opts {
   double u_floor;   // u_g of the cold limit
 };
 
-DEV double snorm3(const Metric& m, const double V[4]) {
+template <class M>
+DEV double snorm3(const M& m, const double V[4]) {
   double s = 0.0;
 #pragma unroll
   for (int i = 0; i < 3; i++)
 #pragma unroll
-    for (int j = 0; j < 3; j++) s += gamup(m, i, j) * V[1 + i] * V[1 + j];
+    for (int j = 0; j < 3; j++)
+      if (!M::zgam(i, j)) s += m.gam(i, j) * V[1 + i] * V[1 + j];
   return ::sqrt(fmax(s, 0.0));
 }
 
@@ -72,7 +76,8 @@ DEV double snorm3(const Metric& m, const double V[4]) {
 // dt|G|, radiation residual over radiation-scale terms and dt|G|; spatial
 // parts merged in the normal observer's orthonormal basis plus the energy
 // scale; e_T = 1/4 sum over equations of the larger of the two.
-DEV void norm_errors(const Cell& c, const double Tg[4], const double Rr[4], const double G[4],
+template <class M>
+DEV void norm_errors(const CellT<M>& c, const double Tg[4], const double Rr[4], const double G[4],
                      Eval& e, double es = -1.0) {
   double Gdt[4];
 #pragma unroll
@@ -89,7 +94,7 @@ DEV void norm_errors(const Cell& c, const double Tg[4], const double Rr[4], cons
   er[0] = ::fabs(e.Er[0]) / ntr;
 #pragma unroll
   for (int i = 0; i < 3; i++) {
-    const double w = ::sqrt(gamup(c.m, i, i));
+    const double w = ::sqrt(c.m.gam(i, i));
     eg[1 + i] = ::fabs(e.Eg[1 + i]) * w / nsg;
     er[1 + i] = ::fabs(e.Er[1 + i]) * w / nsr;
   }
@@ -118,8 +123,8 @@ DEV void norm_errors(const Cell& c, const double Tg[4], const double Rr[4], cons
 // weighted by T_gas: E_S = T_gas ([S u^t] - [S u^t]_(i)) + dt G^mu u_mu with
 // S = rho0 ln(p^n / rho0^(n+1)), n = 1/(gam - 1); its norm (returned in ns)
 // is the sum of its terms' magnitudes plus the gas energy scale.
-template <class D>
-DEV D entropy_residual(const Cell& c, double gam, const Gas<D>& s, const D G[4], double ntg,
+template <class D, class M>
+DEV D entropy_residual(const CellT<M>& c, double gam, const Gas<D>& s, const D G[4], double ntg,
                        double& ns) {
   const double n = 1.0 / (gam - 1.0);
   const D S = s.rho * (n * log(s.pg) - (n + 1.0) * log(s.rho));
@@ -134,7 +139,8 @@ DEV D entropy_residual(const Cell& c, double gam, const Gas<D>& s, const D G[4],
 }
 
 // gas energy norm |T^t_t + rho u^t| + |its explicit value| + dt |G_t| (Sec. 4.8)
-DEV double gas_energy_norm(const Cell& c, double Tg0, double G0) {
+template <class M>
+DEV double gas_energy_norm(const CellT<M>& c, double Tg0, double G0) {
   const double n = ::fabs(Tg0) + ::fabs(c.Tgi[0]) + ::fabs(c.dt * G0);
   return (n > 0.0) ? n : 1e-300;
 }
@@ -143,8 +149,8 @@ DEV double gas_energy_norm(const Cell& c, double Tg0, double G0) {
 // T^t_nu from the gas; Delta R = -Delta T; TYPE2 radiation inversion; R
 // recomputed; G; residuals.  With D = Dual<N> one pass seeds Jacobian
 // columns k0..k0+N-1; with D = double it evaluates the residual alone.
-template <class D, bool ENT = false>
-DEV void pmhd_pass(const Cell& c, const Phys& ph, const double x[4], int k0, Eval& e,
+template <class D, bool ENT = false, class M>
+DEV void pmhd_pass(const CellT<M>& c, const Phys& ph, const double x[4], int k0, Eval& e,
                    double J[4][4]) {
   D ug(x[0]), ut[3] = {D(x[1]), D(x[2]), D(x[3])};
   if constexpr (!std::is_same<D, double>::value) {
@@ -224,30 +230,35 @@ DEV void pmhd_pass(const Cell& c, const Phys& ph, const double x[4], int k0, Eva
   }
 }
 
-template <bool ENT = false>
-DEV void eval_pmhd(const Cell& c, const Phys& ph, const double x[4], Eval& e, double J[4][4]) {
+template <bool ENT = false, class M>
+DEV void eval_pmhd(const CellT<M>& c, const Phys& ph, const double x[4], Eval& e, double J[4][4]) {
 #pragma unroll
-  for (int k0 = 0; k0 < 4; k0 += GRRMHD_NJ) pmhd_pass<Dual<GRRMHD_NJ>, ENT>(c, ph, x, k0, e, J);
+  for (int k0 = 0; k0 < 4; k0 += GRRMHD_NJ) {
+    pmhd_pass<Dual<GRRMHD_NJ>, ENT>(c, ph, x, k0, e, J);
+  }
 }
 
 // Residual alone: a Newton step close to the root reuses the factorised
 // Jacobian of the previous evaluation (chord step).
-template <bool ENT = false>
-DEV void eval_pmhd_value(const Cell& c, const Phys& ph, const double x[4], Eval& e) {
+template <bool ENT = false, class M>
+DEV void eval_pmhd_value(const CellT<M>& c, const Phys& ph, const double x[4], Eval& e) {
   pmhd_pass<double, ENT>(c, ph, x, 0, e, nullptr);
 }
 
 // gas (T^t_t + rho u^t, T^t_i) of primitives P, without sqrt(-g)
-DEV void gas_cons4(const Metric& m, double gam, const double* P, double Tg[4]) {
+template <class M>
+DEV void gas_cons4(const M& m, double gam, const double* P, double Tg[4]) {
   Gas<double> s;
   make_gas(m, gam, P[0], P[1], P + 2, P + 5, s);
   double row[8];
-  gas_row(s, P + 5, 0, row);
+  const double pt = ptot_fused(s, gam);
+  gas_row(s, P + 5, 0, row, &pt);
 #pragma unroll
   for (int k = 0; k < 4; k++) Tg[k] = row[1 + k];
 }
 
-DEV void rad_cons4(const Metric& m, const double* P, double Rr[4]) {
+template <class M>
+DEV void rad_cons4(const M& m, const double* P, double Rr[4]) {
   Vel<double> r;
   make_vel(m, P + 9, r);
   rad_row(r, P[8], 0, Rr);
@@ -256,7 +267,8 @@ DEV void rad_cons4(const Metric& m, const double* P, double Rr[4]) {
 // URAD residual (Sec. 4.8, URAD steps): gas from inverting T(i) - Delta R,
 // radiation from TYPE2 inversion of x, both recomputed for consistency.
 // Pgas (rho, u_g, u~^i) is the starting guess of the MHD iteration.
-DEV void eval_urad(const Cell& c, const Phys& ph, const double x[4], const double Pgas[5],
+template <class M>
+DEV void eval_urad(const CellT<M>& c, const Phys& ph, const double x[4], const double Pgas[5],
                    Eval& e) {
   e.ok = 1;
 #pragma unroll
@@ -306,8 +318,8 @@ DEV void eval_urad(const Cell& c, const Phys& ph, const double x[4], const doubl
 // URAD residual and its exact Jacobian dE_rad/dx in one dual-number pass:
 // the same steps as eval_urad, the gas inversion differentiated by the
 // implicit-function theorem (mhd_invert_dual).  Values equal eval_urad's.
-template <bool ENT = false>
-DEV void eval_urad_jac(const Cell& c, const Phys& ph, const double x[4], const double Pgas[5],
+template <bool ENT = false, class M>
+DEV void eval_urad_jac(const CellT<M>& c, const Phys& ph, const double x[4], const double Pgas[5],
                        Eval& e, double J[4][4]) {
   using D = Dual<4>;
   e.ok = 1;
@@ -379,8 +391,8 @@ DEV void eval_urad_jac(const Cell& c, const Phys& ph, const double x[4], const d
 // (Sec. 4.8, PRAD steps): x = (Ebar, u~^i_rad); R^t_nu from the radiation
 // primitives; the gas from the MHD inversion of T(i) - Delta R (Pgas starts
 // it; its derivatives by the implicit-function theorem); G; residuals.
-template <bool ENT = false>
-DEV void eval_prad_jac(const Cell& c, const Phys& ph, const double x[4], const double Pgas[5],
+template <bool ENT = false, class M>
+DEV void eval_prad_jac(const CellT<M>& c, const Phys& ph, const double x[4], const double Pgas[5],
                        Eval& e, double J[4][4]) {
   using D = Dual<4>;
   e.ok = 1;
@@ -551,8 +563,9 @@ DEV int lu_solve4(const double A[4][4], const int piv[4], double b[4], double xo
 #define GRRMHD_CHORD_TOL 1e-4
 #endif
 
-DEV double rad_energy_lab(const Metric& m, const double R[4]) {
-  return -R[0] + m.alpha * m.alpha * (m.up(0, 1) * R[1] + m.up(0, 2) * R[2] + m.up(0, 3) * R[3]);
+template <class M>
+DEV double rad_energy_lab(const M& m, const double R[4]) {
+  return -R[0] + m.alpha * m.alpha * up0(m, R + 1);
 }
 
 struct Best {
@@ -574,8 +587,8 @@ DEV void keep(Best& b, const Eval& e) {
 // record is live: the new iterate is evaluated into it once the step is
 // taken (PMHD needs only x; URAD keeps the five gas values that seed its
 // inner inversion).
-template <int METHOD, bool ENT = false>
-DEV void newton(const Cell& c, const Phys& ph, const Opts& o, const double x0[4],
+template <int METHOD, bool ENT = false, class M>
+DEV void newton(const CellT<M>& c, const Phys& ph, const Opts& o, const double x0[4],
                 const double Pg0[5], Best& best, int& iters) {
   static_assert(METHOD != M_PRAD || GRRMHD_URAD_EXACT, "PRAD uses exact Jacobians only");
   const double tol = (METHOD == M_PMHD) ? o.tol_pmhd : o.tol_urad;
@@ -625,7 +638,7 @@ DEV void newton(const Cell& c, const Phys& ph, const Opts& o, const double x0[4]
       // (|R_t| + |R_t(i)| + dt |G_t|, with R_t = x_0 and dt G_t from the residual)
       const double Nres = ::fabs(x[0]) + ::fabs(c.Ri[0]) + ::fabs(ev.Er[0] - (x[0] - c.Ri[0]));
       for (int j = 0; j < 4 && !jfail; j++) {
-        const double Nx = (j == 0) ? ::fabs(x[0]) : ::fabs(x[j]) + ::fabs(x[0]) / ::sqrt(gamup(c.m, j - 1, j - 1));
+        const double Nx = (j == 0) ? ::fabs(x[0]) : ::fabs(x[j]) + ::fabs(x[0]) / ::sqrt(c.m.gam(j - 1, j - 1));
         const double N = fmax(Nx, 1e4 * DBL_EPSILON * Nres / delta);
         double hh = (j == 0) ? -delta * N : delta * N;
         int got = 0;
@@ -682,7 +695,7 @@ DEV void newton(const Cell& c, const Phys& ph, const Opts& o, const double x0[4]
         const double Erl = rad_energy_lab(c.m, xn);
         if (Erl <= 0.0) {                                     // same for the radiation energy
           const double a2 = c.m.alpha * c.m.alpha;
-          xn[0] = -0.5 * ::fabs(Erl) + a2 * (c.m.up(0, 1) * xn[1] + c.m.up(0, 2) * xn[2] + c.m.up(0, 3) * xn[3]);
+          xn[0] = -0.5 * ::fabs(Erl) + a2 * up0(c.m, xn + 1);
         }
       }
       if (METHOD == M_PRAD) {
@@ -750,8 +763,9 @@ struct Prep {
 };
 
 // The cell's explicit state per sqrt(-g) and its coefficients.
-DEV void cell_setup(const Metric& m, const double Ui[12], double dt, double chi_abs,
-                    double chi_es, Cell& c) {
+template <class M>
+DEV void cell_setup(const M& m, const double Ui[12], double dt, double chi_abs,
+                    double chi_es, CellT<M>& c) {
   c.m = m;
   const double igd = 1.0 / m.gdet;
   c.rhout = Ui[0] * igd;
@@ -769,8 +783,9 @@ DEV void cell_setup(const Metric& m, const double Ui[12], double dt, double chi_
   c.Si = NAN;
 }
 
-DEV void prepare(const Metric& m, const Phys& ph, const double Ui[12], const double Pg[12], double dt,
-                 double chi_abs, double chi_es, Cell& c, Prep& pr) {
+template <class M>
+DEV void prepare(const M& m, const Phys& ph, const double Ui[12], const double Pg[12], double dt,
+                 double chi_abs, double chi_es, CellT<M>& c, Prep& pr) {
   cell_setup(m, Ui, dt, chi_abs, chi_es, c);
   pr.status = 0;
   // extreme radiation sub-dominance: R^t_t against the gas energy, or the
@@ -808,9 +823,10 @@ DEV void prepare(const Metric& m, const Phys& ph, const double Ui[12], const dou
 DEV double accept_threshold(const Opts& o) { return o.roundoff ? 10.0 * o.tol_pmhd : o.tol_accept; }
 
 // Conserved output and status from the best solution (Sec. 4.10-4.11).
-DEV void finalize(const Cell& c, const Phys& ph, const Opts& o, const Best& best, int method,
+template <class M>
+DEV void finalize(const CellT<M>& c, const Phys& ph, const Opts& o, const Best& best, int method,
                   int status, int iters, const double Ui[12], CellOut& out) {
-  const Metric& m = c.m;
+  const M& m = c.m;
   out.iters = iters;
   status |= (method == M_PMHD) ? GRRMHD_ST_PMHD : (method == M_URAD) ? GRRMHD_ST_URAD : GRRMHD_ST_PRAD;
   if (best.eT > o.tol_fail) status |= GRRMHD_ST_FAIL;
@@ -875,7 +891,8 @@ DEV void failed_out(const double Ui[12], const double Pg[12], int status, int it
 // its exact Jacobian, the radiation following from total conservation; the
 // energy residuals leave e_T (c.cold).  The u_g row and column of the 4x4
 // system are pinned (dx_0 = 0); the stopping rules are newton()'s.
-DEV void newton_cold(const Cell& c, const Phys& ph, const Opts& o, const double x0[4], Best& best,
+template <class M>
+DEV void newton_cold(const CellT<M>& c, const Phys& ph, const Opts& o, const double x0[4], Best& best,
                      int& iters) {
   double x[4] = {x0[0], x0[1], x0[2], x0[3]};
   Eval ev;
@@ -932,7 +949,8 @@ DEV void newton_cold(const Cell& c, const Phys& ph, const Opts& o, const double 
 // (the gas cold against its motion, its energy small against its momentum).
 // The paper's condition on R^t_t R^{tt} against R^t_i R^{ti} cannot hold for
 // an M1 state (|F| <= E) and is not applied.
-DEV bool cold_allowed(const Cell& c, const double Pg[12]) {
+template <class M>
+DEV bool cold_allowed(const CellT<M>& c, const double Pg[12]) {
   Vel<double> u;
   make_vel(c.m, Pg + 2, u);
   const double usp = u.ucon[1] * u.ucov[1] + u.ucon[2] * u.ucov[2] + u.ucon[3] * u.ucov[3];
@@ -954,10 +972,11 @@ DEV bool cold_allowed(const Cell& c, const double Pg[12]) {
 // success (e_T within tol_fail) `out` holds
 // the solution with the set-up's status bits (EXTREME, C2P_FAIL) and COLD
 // (TYPE2/BASIC/NOT_ACCEPT as for PMHD); iters accumulates either way.
-DEV bool cold_cell(const Metric& m, const Phys& ph, const Opts& o, const double Ui[12],
+template <class M>
+DEV bool cold_cell(const M& m, const Phys& ph, const Opts& o, const double Ui[12],
                    const double Pg[12], double dt, double chi_abs, double chi_es, int& iters,
                    CellOut& out) {
-  Cell c;
+  CellT<M> c;
   cell_setup(m, Ui, dt, chi_abs, chi_es, c);
   if (!cold_allowed(c, Pg)) return false;
   Prep pr;   // the set-up's status bits (EXTREME, C2P_FAIL) for the output
@@ -975,7 +994,8 @@ DEV bool cold_cell(const Metric& m, const Phys& ph, const Opts& o, const double 
 }
 
 // After the energy cascade: a cell left failed takes the cold limit.
-DEV void cold_fallback(const Metric& m, const Phys& ph, const Opts& o, const double Ui[12],
+template <class M>
+DEV void cold_fallback(const M& m, const Phys& ph, const Opts& o, const double Ui[12],
                        const double Pg[12], double dt, double chi_abs, double chi_es,
                        CellOut& out) {
   if (!(out.status & GRRMHD_ST_FAIL) || !o.cold || !(o.u_floor > 0.0)) return;
@@ -1017,10 +1037,11 @@ DEV void rec_load(const RecBuf& R, long slot, Best& b, int& iters) {
 // Common case: not extreme, first PMHD attempt accepted.  Returns false when
 // the cell needs the full cascade; b and iters then hold the first attempt
 // (none when the cell is extreme), trips the residual evaluations it took.
-DEV bool implicit_fast(const Metric& m, const Phys& ph, const Opts& o, const double Ui[12],
+template <class M>
+DEV bool implicit_fast(const M& m, const Phys& ph, const Opts& o, const double Ui[12],
                        const double Pg[12], double dt, double chi_abs, double chi_es,
                        CellOut& out, Best& b, int& iters, bool& extreme, int& trips) {
-  Cell c;
+  CellT<M> c;
   Prep pr;
   prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr);
   b.eT = INFINITY;
@@ -1041,11 +1062,12 @@ DEV bool implicit_fast(const Metric& m, const Phys& ph, const Opts& o, const dou
 // resumes after its first PMHD attempt, stored at list slot `slot` by the
 // kernel that ran it (that attempt was not accepted, else the cell would not
 // be in the cascade).
-DEV void implicit_cell(const Metric& m, const Phys& ph, const Opts& o, const double Ui[12],
+template <class M>
+DEV void implicit_cell(const M& m, const Phys& ph, const Opts& o, const double Ui[12],
                        const double Pg[12], double dt, double chi_abs, double chi_es,
                        CellOut& out, const RecBuf* R = nullptr, long slot = 0,
                        bool try_cold = true) {
-  Cell c;
+  CellT<M> c;
   Prep pr;
   prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr);
   Best best;
@@ -1106,8 +1128,8 @@ DEV void implicit_cell(const Metric& m, const Phys& ph, const Opts& o, const dou
 
 // residual and exact Jacobian of one method at x (Pn starts the inner MHD
 // inversion of URAD and PRAD)
-template <int METHOD, bool ENT>
-DEV void eval_jac(const Cell& c, const Phys& ph, const double x[4], const double Pn[5], Eval& e,
+template <int METHOD, bool ENT, class M>
+DEV void eval_jac(const CellT<M>& c, const Phys& ph, const double x[4], const double Pn[5], Eval& e,
                   double J[4][4]) {
   if (METHOD == M_PMHD) eval_pmhd<ENT>(c, ph, x, e, J);
   else if (METHOD == M_PRAD) eval_prad_jac<ENT>(c, ph, x, Pn, e, J);
@@ -1124,8 +1146,8 @@ DEV void method_res(const Eval& e, double r[4]) {
 
 // post-step check (Sec. 4.10): a negative u_g (PMHD), lab radiation energy
 // (URAD) or Ebar (PRAD) becomes half its magnitude; true when it acted
-template <int METHOD>
-DEV bool post_step(const Cell& c, double xn[4]) {
+template <int METHOD, class M>
+DEV bool post_step(const CellT<M>& c, double xn[4]) {
   if (METHOD != M_URAD) {
     if (xn[0] < 0.0) {
       xn[0] = 0.5 * ::fabs(xn[0]);
@@ -1136,7 +1158,7 @@ DEV bool post_step(const Cell& c, double xn[4]) {
   const double Erl = rad_energy_lab(c.m, xn);
   if (Erl <= 0.0) {
     const double a2 = c.m.alpha * c.m.alpha;
-    xn[0] = -0.5 * ::fabs(Erl) + a2 * (c.m.up(0, 1) * xn[1] + c.m.up(0, 2) * xn[2] + c.m.up(0, 3) * xn[3]);
+    xn[0] = -0.5 * ::fabs(Erl) + a2 * up0(c.m, xn + 1);
     return true;
   }
   return false;
@@ -1149,8 +1171,8 @@ DEV bool post_step(const Cell& c, double xn[4]) {
 // post-step correction recurring 2 times (4 with the entropy equation)
 // holds the prior value and ends the stage; stage 3 the 4-D Newton for at
 // most 40 steps, the first damped by 1/4, with newton()'s stopping rules.
-template <int METHOD, bool ENT>
-DEV void newton_staged(const Cell& c, const Phys& ph, const Opts& o, const double x0[4],
+template <int METHOD, bool ENT, class M>
+DEV void newton_staged(const CellT<M>& c, const Phys& ph, const Opts& o, const double x0[4],
                        const double Pg0[5], Best& best, int& iters) {
   const double tol = (METHOD == M_PMHD) ? o.tol_pmhd : o.tol_urad;
   const int nmod_max = ENT ? 4 : 2;
@@ -1274,8 +1296,8 @@ DEV void newton_staged(const Cell& c, const Phys& ph, const Opts& o, const doubl
 
 // One attempt of one method, normal or staged (run-time choice over the
 // compile-time forms).
-template <bool ENT>
-DEV void attempt(int method, bool staged, const Cell& c, const Phys& ph, const Opts& o,
+template <bool ENT, class M>
+DEV void attempt(int method, bool staged, const CellT<M>& c, const Phys& ph, const Opts& o,
                  const double x0[4], const double P0[5], Best& b, int& iters) {
   if (staged) {
     if (method == M_PMHD) newton_staged<M_PMHD, ENT>(c, ph, o, x0, P0, b, iters);
@@ -1295,8 +1317,8 @@ DEV void attempt(int method, bool staged, const Cell& c, const Phys& ph, const O
 // attempt starts from the best so far when its e_T < 1e-4, else from its
 // own guess: PMHD the thin-limit primitives (staged: u_g from the explicit
 // entropy at the prior rho0), URAD R(P_n), PRAD the thin-limit radiation.
-template <bool ENT>
-DEV void run_phase(const Cell& c, const Phys& ph, const Opts& o, const Prep& pr,
+template <bool ENT, class M>
+DEV void run_phase(const CellT<M>& c, const Phys& ph, const Opts& o, const Prep& pr,
                    const double Pg[12], const double Pradthin[12], int skip, Best& best, int& bm,
                    int& staged, int& iters) {
   const double acc = accept_threshold(o);
@@ -1345,11 +1367,12 @@ DEV void run_phase(const Cell& c, const Phys& ph, const Opts& o, const Prep& pr,
 // (NAN: no entropy phase).  resume 1: the first PMHD attempt ran (record R
 // at `slot`), 2: PMHD and URAD ran (the record holds the better of the two,
 // its method in the record's ok field); 0 from scratch.
-DEV void implicit_cell_full(const Metric& m, const Phys& ph, const Opts& o, const double Ui[12],
+template <class M>
+DEV void implicit_cell_full(const M& m, const Phys& ph, const Opts& o, const double Ui[12],
                             double Si, const double Pg[12], double dt, double chi_abs,
                             double chi_es, CellOut& out, const RecBuf* R = nullptr,
                             long slot = 0, int resume = 0) {
-  Cell c;
+  CellT<M> c;
   Prep pr;
   prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr);
   c.Si = Si / m.gdet;
@@ -1435,7 +1458,8 @@ enum { TRIP_CONTINUE = 0, TRIP_DONE = 1, TRIP_CASCADE = 2 };
 
 // Part A of a Newton trip: loop-top checks and the step.  Returns true when
 // the attempt ends here.
-DEV bool lane_step(const Cell& c, const Opts& o, Lane& L) {
+template <class M>
+DEV bool lane_step(const CellT<M>& c, const Opts& o, Lane& L) {
   if (L.it >= o.max_iter) return true;
   if (L.eT < o.tol_pmhd) L.conv = 1;
   if (L.conv) {
@@ -1458,7 +1482,8 @@ DEV bool lane_step(const Cell& c, const Opts& o, Lane& L) {
 
 // The evaluation at the lane's new iterate: residual alone on a chord step,
 // else residual and Jacobian.
-DEV void lane_eval(const Cell& c, const Phys& ph, Lane& L, Eval& ev) {
+template <class M>
+DEV void lane_eval(const CellT<M>& c, const Phys& ph, Lane& L, Eval& ev) {
   if (L.chord) {
     eval_pmhd_value(c, ph, L.x, ev);
   } else {
@@ -1531,7 +1556,8 @@ struct UradLane {
 
 // Before the evaluation: STEP's loop-top checks and step (true: the attempt
 // ends here), BACK's half-way point.
-DEV bool urad_before(const Cell& c, const Opts& o, UradLane& L) {
+template <class M>
+DEV bool urad_before(const CellT<M>& c, const Opts& o, UradLane& L) {
   if (L.mode == UM_BACK) {
 #pragma unroll
     for (int i = 0; i < 4; i++) L.p[i] = 0.5 * (L.x[i] + L.p[i]);
@@ -1552,7 +1578,7 @@ DEV bool urad_before(const Cell& c, const Opts& o, UradLane& L) {
   const double Erl = rad_energy_lab(c.m, L.p);
   if (Erl <= 0.0) {
     const double a2 = c.m.alpha * c.m.alpha;
-    L.p[0] = -0.5 * ::fabs(Erl) + a2 * (c.m.up(0, 1) * L.p[1] + c.m.up(0, 2) * L.p[2] + c.m.up(0, 3) * L.p[3]);
+    L.p[0] = -0.5 * ::fabs(Erl) + a2 * up0(c.m, L.p + 1);
   }
   return false;
 }

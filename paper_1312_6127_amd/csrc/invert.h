@@ -10,24 +10,36 @@
 
 #include "physics.h"
 
-// spatial inverse metric of the normal observer: g^{ij} - g^{ti} g^{tj}/g^{tt}
-DEV double gamup(const Metric& m, int i, int j) {
-  return m.up(i + 1, j + 1) - m.up(0, i + 1) * m.up(0, j + 1) / m.up(0, 0);
+// g^{ti} v_i
+template <class T, class M>
+DEV T up0(const M& m, const T v[3]) {
+  if constexpr (M::dense) return m.up(0, 1) * v[0] + m.up(0, 2) * v[1] + m.up(0, 3) * v[2];
+  else if constexpr (M::diagonal) return T(0.0);
+  else return m.up(0, 1) * v[0];
+}
+
+// sum_j gamma^{ij} v_j (gamma^{ij}: the normal observer's spatial inverse
+// metric)
+template <class T, class M>
+DEV T raise3(const M& m, int i, const T v[3]) {
+  if constexpr (M::dense) return m.gam(i, 0) * v[0] + m.gam(i, 1) * v[1] + m.gam(i, 2) * v[2];
+  if (M::diagonal || i == 1) return m.gam(i, i) * v[i];
+  return m.gam(i, 0) * v[0] + m.gam(i, 2) * v[2];
 }
 
 // ---------------------------------------------------------------------------
 // M1 radiation inversion.  Input R^t_nu (no sqrt(-g)).  Output Ebar, u~_rad.
 // Returns bit 0 if E_rad <= 0 was met, bit 1 if y >= y_max.
 // ---------------------------------------------------------------------------
-template <class T>
-DEV int rad_invert(const Metric& m, double gamma_max, double ymax, int type2, const T R[4],
+template <class T, class M>
+DEV int rad_invert(const M& m, double gamma_max, double ymax, int type2, const T R[4],
                    T& Ebar, T ut[3]) {
   const double a = m.alpha, a2 = a * a;
   // E_rad = -eta^mu alpha R^t_mu; U~^i = gamma^{ij} alpha R^t_j (eq. RADPRIM2, RADPRIM3)
-  const T Erad = -R[0] + a2 * (m.up(0, 1) * R[1] + m.up(0, 2) * R[2] + m.up(0, 3) * R[3]);
+  const T Erad = -R[0] + a2 * up0(m, R + 1);
   T Ut[3];
 #pragma unroll
-  for (int i = 0; i < 3; i++) Ut[i] = a * (gamup(m, i, 0) * R[1] + gamup(m, i, 1) * R[2] + gamup(m, i, 2) * R[3]);
+  for (int i = 0; i < 3; i++) Ut[i] = a * raise3(m, i, R + 1);
   const T Ut2 = a * (Ut[0] * R[1] + Ut[1] * R[2] + Ut[2] * R[3]);
   const double G2 = gamma_max * gamma_max;
   const double Ev = val(Erad), U2v = val(Ut2);
@@ -188,19 +200,19 @@ DEV int mhd_bisect(const MhdC& c, double& Wp_out) {
 
 // Constants of eq. EMHD from rho u^t, E_gas = T^t_t + rho u^t, T^t_i, B^i
 // (all without sqrt(-g)), eq. PRIM1 and the normal-observer projections.
-template <class C>
-DEV void mhd_consts(const Metric& m, double gam, double rhout, const C& Eg, const C Tt[3],
+template <class C, class M>
+DEV void mhd_consts(const M& m, double gam, double rhout, const C& Eg, const C Tt[3],
                     const double B[3], MhdCT<C>& c) {
   const double al = m.alpha;
   c.gam = gam;
   c.D = al * rhout;                                                       // eq. PRIM1
-  c.Ep = -Eg + rhout * (1.0 - al) + al * al * (m.up(0, 1) * Tt[0] + m.up(0, 2) * Tt[1] + m.up(0, 3) * Tt[2]);
+  c.Ep = -Eg + rhout * (1.0 - al) + al * al * up0(m, Tt);
   c.Qt2 = C(0.0);
   c.S = C(0.0);
   c.Bsq = 0.0;
 #pragma unroll
   for (int i = 0; i < 3; i++) {
-    c.Qt[i] = al * (gamup(m, i, 0) * Tt[0] + gamup(m, i, 1) * Tt[1] + gamup(m, i, 2) * Tt[2]);
+    c.Qt[i] = al * raise3(m, i, Tt);
     c.Bz[i] = al * B[i];
   }
 #pragma unroll
@@ -208,21 +220,24 @@ DEV void mhd_consts(const Metric& m, double gam, double rhout, const C& Eg, cons
     c.Qt2 = c.Qt2 + c.Qt[i] * al * Tt[i];
     c.S = c.S + al * Tt[i] * c.Bz[i];
 #pragma unroll
-    for (int j = 0; j < 3; j++) c.Bsq += m.lo(i + 1, j + 1) * c.Bz[i] * c.Bz[j];
+    for (int j = 0; j < 3; j++)
+      if (!M::zlo(i + 1, j + 1)) c.Bsq += m.lo(i + 1, j + 1) * c.Bz[i] * c.Bz[j];
   }
 }
 
 // The root W' of eq. EMHD: Newton from the guess primitives (W' = D u~^2/(1+gamma)
 // + chi gamma^2), bracketed bisection when Newton leaves the admissible
 // region or stalls.  0 on success (with chi > 0 at the root), 1 otherwise.
-DEV int mhd_solve(const Metric& m, const MhdC& c, double ug_g, const double ut_g[3], double& Wp) {
+template <class M>
+DEV int mhd_solve(const M& m, const MhdC& c, double ug_g, const double ut_g[3], double& Wp) {
   if (!(c.D > 0.0) || !(c.Ep > 0.0) || !isfinite(c.Ep) || !isfinite(c.Qt2)) return 1;
   {
     double q = 0.0;
 #pragma unroll
     for (int i = 0; i < 3; i++)
 #pragma unroll
-      for (int j = 0; j < 3; j++) q += m.lo(i + 1, j + 1) * ut_g[i] * ut_g[j];
+      for (int j = 0; j < 3; j++)
+        if (!M::zlo(i + 1, j + 1)) q += m.lo(i + 1, j + 1) * ut_g[i] * ut_g[j];
     const double g = ::sqrt(1.0 + q);
     Wp = c.D * q / (1.0 + g) + c.gam * ug_g * (1.0 + q);
   }
@@ -276,7 +291,8 @@ DEV void mhd_prims(const MhdCT<C>& c, const T& Wp, T& rho, T& ug, T ut[3]) {
 // Gas primitives from rho u^t, E_gas = T^t_t + rho u^t, T^t_i, B^i (all
 // without sqrt(-g)).  The guess supplies the starting W'.  Writes rho, u_g,
 // u~^i.  Returns 0 on success, 1 without a physical (u_g > 0) root.
-DEV int mhd_invert(const Metric& m, double gam, double rhout, double Eg, const double Tt[3],
+template <class M>
+DEV int mhd_invert(const M& m, double gam, double rhout, double Eg, const double Tt[3],
                    const double B[3], double& rho_g, double& ug_g, double ut_g[3]) {
   MhdC c;
   mhd_consts(m, gam, rhout, Eg, Tt, B, c);
@@ -290,8 +306,8 @@ DEV int mhd_invert(const Metric& m, double gam, double rhout, double Eg, const d
 // numbers: the root W' in double precision, then its derivative from the
 // implicit-function theorem on eq. EMHD, dW' = -(df/dc . dc) / (df/dW'),
 // and the primitives' derivatives through eq. tveq.
-template <int N>
-DEV int mhd_invert_dual(const Metric& m, double gam, double rhout, const Dual<N>& Eg,
+template <int N, class M>
+DEV int mhd_invert_dual(const M& m, double gam, double rhout, const Dual<N>& Eg,
                         const Dual<N> Tt[3], const double B[3], double ug_g, const double ut_g[3],
                         Dual<N>& rho, Dual<N>& ug, Dual<N> ut[3]) {
   using D = Dual<N>;

@@ -2,7 +2,7 @@
 // All state arrays are field-major SoA over the allocated grid; consecutive
 // threads take consecutive i (x1) so every field access is coalesced.
 #pragma once
-#include "implicit.h"
+#include "pointwise.h"
 
 #define LB(n) __launch_bounds__(n)
 #ifndef GRRMHD_FLUX_LB
@@ -104,7 +104,7 @@ DEV void geometry_at(Ctx C, double a, double R0, double* gc, double* gf1, double
   }
 }
 
-__global__ void LB(256) k_geometry(Ctx C, double a, double R0, double* gc, double* gf1,
+static __global__ void LB(256) k_geometry(Ctx C, double a, double R0, double* gc, double* gf1,
                                    double* gf2) {
   geometry_at(C, a, R0, gc, gf1, gf2, blockIdx.x * blockDim.x + threadIdx.x);
 }
@@ -151,19 +151,24 @@ DEV void bc_all_at(Ctx C, double* P, long c) {
   }
 }
 
-__global__ void LB(256) k_bc_all(Ctx C, double* P) {
+static __global__ void LB(256) k_bc_all(Ctx C, double* P) {
   bc_all_at(C, P, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
 // steps 2-3 helper and P -> U kernel
 // ---------------------------------------------------------------------------
-template <class T>
-DEV void prim_to_cons_cell(const Metric& m, double gam, const T* P, T* U) {
+template <class T, class M>
+DEV void prim_to_cons_cell(const M& m, double gam, const T* P, T* U) {
   Gas<T> s;
   make_gas(m, gam, P[0], P[1], P + 2, P + 5, s);
   T row[8];
-  gas_row(s, P + 5, 0, row);
+  if constexpr (std::is_same<T, double>::value) {
+    const double pt = ptot_fused(s, gam);
+    gas_row(s, P + 5, 0, row, &pt);
+  } else {
+    gas_row(s, P + 5, 0, row);
+  }
   Vel<T> r;
   make_vel(m, P + 9, r);
   T rr[4];
@@ -174,10 +179,11 @@ DEV void prim_to_cons_cell(const Metric& m, double gam, const T* P, T* U) {
   for (int q = 0; q < 4; q++) U[8 + q] = m.gdet * rr[q];
 }
 
+template <class Geo>
 DEV void p2u_at(Ctx C, const double* __restrict__ P, double* __restrict__ U, long c) {
   if (c >= C.Ntot) return;
   const int pos = c % C.npos;
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, pos, m);
   double p[12], u[12];
 #pragma unroll
@@ -187,8 +193,9 @@ DEV void p2u_at(Ctx C, const double* __restrict__ P, double* __restrict__ U, lon
   for (int q = 0; q < 12; q++) U[q * C.Ntot + c] = u[q];
 }
 
+template <class Geo>
 __global__ void LB(256) k_p2u(Ctx C, const double* __restrict__ P, double* __restrict__ U) {
-  p2u_at(C, P, U, (long)blockIdx.x * blockDim.x + threadIdx.x);
+  p2u_at<Geo>(C, P, U, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -241,8 +248,8 @@ struct FaceState {
 
 // Characteristic speeds along d of one face state: gas (gm, gp) and
 // radiation (rm, rp).
-template <class T>
-DEV void face_speeds(const Ctx& C, const MetricT<typename RealOf<T>::type>& m, int d, const T* P,
+template <class T, class M>
+DEV void face_speeds(const Ctx& C, const M& m, int d, const T* P,
                      T chi_tot, const Gas<T>& s, const Vel<T>& r, T& gm, T& gp, T& rm, T& rp) {
   using R = typename RealOf<T>::type;
   // gas: fast magnetosonic speed c_ms^2 = v_A^2 + c_s^2 (1 - v_A^2)
@@ -266,8 +273,8 @@ DEV void face_speeds(const Ctx& C, const MetricT<typename RealOf<T>::type>& m, i
 
 // T = double, float on the FP32 face path (metric rounded to float too), or
 // Dual<N> for the adjoint
-template <class T>
-DEV void face_state(const Ctx& C, const MetricT<typename RealOf<T>::type>& m, int d, const T* P,
+template <class T, class M>
+DEV void face_state(const Ctx& C, const M& m, int d, const T* P,
                     T chi_tot, FaceState<T>& fs) {
   Gas<T> s;
   make_gas(m, C.gam, P[0], P[1], P + 2, P + 5, s);
@@ -301,8 +308,8 @@ struct FaceRange {
 // fl: the PPM flattener [3][gas, radiation][Ntot] (unused for MC)
 // sqrt(-g) S u^t and sqrt(-g) S u^D of the entropy tracer at a face state
 // (S = rho0 ln(p^n / rho0^(n+1)), n = 1/(gam - 1); Sec. 4 lists of U_q, F_q)
-template <int D, class T>
-DEV void entropy_face(const Ctx& C, const MetricT<T>& m, const T* P, T& Us, T& Fs) {
+template <int D, class T, class M>
+DEV void entropy_face(const Ctx& C, const M& m, const T* P, T& Us, T& Fs) {
   Vel<T> v;
   make_vel(m, P + 2, v);
   const T n = T(1.0 / (C.gam - 1.0));
@@ -321,13 +328,13 @@ DEV void entropy_face(const Ctx& C, const MetricT<T>& m, const T* P, T& Us, T& F
 // (the face's own normal field replaced with the staggered field's): face
 // states, wave speeds, HLL / LAXF, the stores.  Shared by flux_at (stencil
 // from global memory) and the LDS-staged flux kernel.
-template <int D, class T, bool ENTF = false, bool STAG = false>
+template <class Geo, int D, class T, bool ENTF = false, bool STAG = false>
 DEV void flux_states(const Ctx& C, int i, int j, long c, long st, T PL[12], T PR[12],
                      const double* __restrict__ chi_abs, const double* __restrict__ chi_es,
                      double* __restrict__ F, double* __restrict__ vchar,
                      double* __restrict__ Fs = nullptr, const double* __restrict__ Bf = nullptr,
                      double* __restrict__ VF = nullptr, double* __restrict__ SP = nullptr) {
-  MetricT<T> m;
+  typename Geo::template M<T> m;
   const double* tab = (D == 1) ? C.geo_f1 : ((D == 2) ? C.geo_f2 : C.geo_c);
   load_metric(tab, C.npos, i + C.N[0] * j, m);
   if constexpr (STAG) {
@@ -374,8 +381,8 @@ DEV void flux_states(const Ctx& C, int i, int j, long c, long st, T PL[12], T PR
   if constexpr (ENTF) {
     // the entropy tracer's flux, with the gas speeds
     T UsL, FsL, UsR, FsR, f;
-    entropy_face<D, T>(C, m, PL, UsL, FsL);
-    entropy_face<D, T>(C, m, PR, UsR, FsR);
+    entropy_face<D>(C, m, PL, UsL, FsL);
+    entropy_face<D>(C, m, PR, UsR, FsR);
     if (C.flux == GRRMHD_FLUX_HLL) {
       const T den = gmin + gmax;
       f = (den > zero) ? (gmin * FsR + gmax * FsL - gmin * gmax * (UsR - UsL)) / den
@@ -389,7 +396,7 @@ DEV void flux_states(const Ctx& C, int i, int j, long c, long st, T PL[12], T PR
 
 // The face velocity states alone (the staggered field's outer faces): u~^1..3
 // reconstructed exactly as in flux_at, v^m = u^m/u^t from the face metric.
-template <int D, class T>
+template <class Geo, int D, class T>
 DEV void stag_face_velocities(const Ctx& C, const double* __restrict__ P,
                               const double* __restrict__ fl, int i, int j, long c, long st,
                               double* __restrict__ VF) {
@@ -397,7 +404,7 @@ DEV void stag_face_velocities(const Ctx& C, const double* __restrict__ P,
   if (C.recon == GRRMHD_RECON_PPM) {
     const double* fg = fl + (long)(2 * (D - 1)) * C.Ntot;
     const T fgL = (T)fg[c - st], fgR = (T)fg[c];
-    const bool wgt = (D == 1) && C.metric == GRRMHD_KERR_SCHILD;
+    const bool wgt = (D == 1) && Geo::curved(C);
     double gc[6] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0}, gface = 1.0;
     if (wgt) {
 #pragma unroll
@@ -427,7 +434,7 @@ DEV void stag_face_velocities(const Ctx& C, const double* __restrict__ P,
       uR[q] = e - T(0.5) * mc_slope(e - b, f - e);
     }
   }
-  MetricT<T> m;
+  typename Geo::template M<T> m;
   const double* tab = (D == 1) ? C.geo_f1 : ((D == 2) ? C.geo_f2 : C.geo_c);
   load_metric(tab, C.npos, i + C.N[0] * j, m);
 #pragma unroll
@@ -440,7 +447,7 @@ DEV void stag_face_velocities(const Ctx& C, const double* __restrict__ P,
   }
 }
 
-template <int D, class T, bool ENTF = false, bool STAG = false>
+template <class Geo, int D, class T, bool ENTF = false, bool STAG = false>
 DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
                                const double* __restrict__ chi_abs,
                                const double* __restrict__ chi_es, double* __restrict__ F,
@@ -465,7 +472,7 @@ DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
       if (e != D - 1 && C.n[e] > 1 && (idx[e] < C.ng[e] - 1 || idx[e] > C.ng[e] + C.n[e]))
         outer = true;
     if (outer) {
-      stag_face_velocities<D, T>(C, P, fl, i, j, c, st, VF);
+      stag_face_velocities<Geo, D, T>(C, P, fl, i, j, c, st, VF);
       return;
     }
   }
@@ -478,7 +485,7 @@ DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
     // Kerr-Schild, along r: the vector primitives interpolated as sqrt(-g)
     // times the value (Sec. 4.3); along phi sqrt(-g) is constant and the
     // weighting the identity
-    const bool wgt = (D == 1) && C.metric == GRRMHD_KERR_SCHILD;
+    const bool wgt = (D == 1) && Geo::curved(C);
     double gc[6] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0}, gface = 1.0;
     if (wgt) {
 #pragma unroll
@@ -509,7 +516,7 @@ DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
       PR[q] = e - T(0.5) * mc_slope(e - b, f - e);
     }
   }
-  flux_states<D, T, ENTF, STAG>(C, i, j, c, st, PL, PR, chi_abs, chi_es, F, vchar, Fs, Bf, VF, SP);
+  flux_states<Geo, D, T, ENTF, STAG>(C, i, j, c, st, PL, PR, chi_abs, chi_es, F, vchar, Fs, Bf, VF, SP);
 }
 
 
@@ -524,7 +531,7 @@ struct FluxSegs {
   long total;
 };
 
-template <class T, bool ENTF = false, bool STAG = false>
+template <class Geo, class T, bool ENTF = false, bool STAG = false>
 DEV void flux_all_at(Ctx C, const FluxSegs& S, const double* __restrict__ P,
                      const double* __restrict__ chi_abs, const double* __restrict__ chi_es,
                      double* __restrict__ F, double* __restrict__ vchar,
@@ -540,13 +547,13 @@ DEV void flux_all_at(Ctx C, const FluxSegs& S, const double* __restrict__ P,
   double* Fd = F + (long)(D - 1) * 12 * C.Ntot;
   double* vd = vchar + (long)(D - 1) * C.Ntot;
   double* Fsd = ENTF ? Fs + (long)(D - 1) * C.Ntot : nullptr;
-  if (D == 1) flux_at<1, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
-  else if (D == 2) flux_at<2, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
-  else flux_at<3, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
+  if (D == 1) flux_at<Geo, 1, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
+  else if (D == 2) flux_at<Geo, 2, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
+  else flux_at<Geo, 3, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
 }
 
 // The same with the staggered field (and, with ENTF, the entropy tracer)
-template <class T, bool ENTF>
+template <class Geo, class T, bool ENTF>
 __global__ void GRRMHD_FLUX_LB k_flux_all_stag(Ctx C, FluxSegs S, const double* __restrict__ P,
                                                const double* __restrict__ chi_abs,
                                                const double* __restrict__ chi_es,
@@ -555,37 +562,38 @@ __global__ void GRRMHD_FLUX_LB k_flux_all_stag(Ctx C, FluxSegs S, const double* 
                                                double* __restrict__ Fs,
                                                const double* __restrict__ Bf,
                                                double* __restrict__ VF, double* __restrict__ SP) {
-  flux_all_at<T, ENTF, true>(C, S, P, chi_abs, chi_es, F, vchar, fl,
+  flux_all_at<Geo, T, ENTF, true>(C, S, P, chi_abs, chi_es, F, vchar, fl,
                              xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x, Fs, Bf,
                              VF, SP);
 }
 
-template <class T>
+template <class Geo, class T>
 __global__ void GRRMHD_FLUX_LB k_flux_all(Ctx C, FluxSegs S, const double* __restrict__ P,
                                           const double* __restrict__ chi_abs,
                                           const double* __restrict__ chi_es,
                                           double* __restrict__ F, double* __restrict__ vchar,
                                           const double* __restrict__ fl) {
-  flux_all_at<T>(C, S, P, chi_abs, chi_es, F, vchar, fl,
+  flux_all_at<Geo, T>(C, S, P, chi_abs, chi_es, F, vchar, fl,
                  xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x);
 }
 
 // The same with the entropy tracer's face fluxes Fs [3][Ntot] (the full
 // implicit cascade's entropy equation)
-template <class T>
+template <class Geo, class T>
 __global__ void GRRMHD_FLUX_LB k_flux_all_s(Ctx C, FluxSegs S, const double* __restrict__ P,
                                             const double* __restrict__ chi_abs,
                                             const double* __restrict__ chi_es,
                                             double* __restrict__ F, double* __restrict__ vchar,
                                             const double* __restrict__ fl,
                                             double* __restrict__ Fs) {
-  flux_all_at<T, true>(C, S, P, chi_abs, chi_es, F, vchar, fl,
+  flux_all_at<Geo, T, true>(C, S, P, chi_abs, chi_es, F, vchar, fl,
                        xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x, Fs);
 }
 
 // sqrt(-g) S u^t of one cell's primitives p (the entropy tracer; NAN where
 // rho0 or u_g is not positive)
-DEV double entropy_cons(double gam, const Metric& m, const double p[5]) {
+template <class M>
+DEV double entropy_cons(double gam, const M& m, const double p[5]) {
   if (!(p[0] > 0.0) || !(p[1] > 0.0)) return NAN;
   Vel<double> v;
   make_vel(m, p + 2, v);
@@ -604,11 +612,12 @@ DEV bool interior_ijk(const Ctx& C, long t, int& i, int& j, int& k) {
 }
 
 // the entropy tracer of P at interior cells
+template <class Geo>
 __global__ void LB(256) k_entropy_field(Ctx C, const double* __restrict__ P, double* __restrict__ S) {
   int i, j, k;
   if (!interior_ijk(C, (long)blockIdx.x * blockDim.x + threadIdx.x, i, j, k)) return;
   const long c = cell_index(C, i, j, k);
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   double p[5];
 #pragma unroll
@@ -619,6 +628,7 @@ __global__ void LB(256) k_entropy_field(Ctx C, const double* __restrict__ P, dou
 // the entropy tracer's explicit stage value at interior cells:
 // a Sn + b U_S(P) + cc dt (-div Fs), Sn = U_S(P^n), P the stage's input (no
 // flux term, and no Fs read, where cc = 0)
+template <class Geo>
 __global__ void LB(256) k_entropy_update(Ctx C, double a, double b, double cc,
                                          const double* __restrict__ dt_dev,
                                          const double* __restrict__ Sn,
@@ -630,7 +640,7 @@ __global__ void LB(256) k_entropy_update(Ctx C, double a, double b, double cc,
   const long c = cell_index(C, i, j, k);
   double sp = 0.0;
   if (b != 0.0) {
-    Metric m;
+    typename Geo::template M<double> m;
     load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
     double p[5];
 #pragma unroll
@@ -692,10 +702,11 @@ DEV Dual<N> third(const Dual<N>& x) {
 // The flattener's velocities on a Kerr-Schild grid, once per cell: the
 // specific mass fluxes sqrt(-g) u^d of the gas (mf[d]) and the radiation
 // (mf[3 + d]), d = 0..2, from the cell's own metric.
+template <class Geo>
 __global__ void LB(256) k_mass_flux(Ctx C, const double* __restrict__ P, double* __restrict__ mf) {
   const long c = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= C.Ntot) return;
-  Metric met;
+  typename Geo::template M<double> met;
   load_metric(C.geo_c, C.npos, (int)(c % C.npos), met);
   double ut[3];
   Vel<double> v;
@@ -801,7 +812,7 @@ DEV void flatten_at(Ctx C, const double* __restrict__ P, const double* __restric
   }
 }
 
-__global__ void LB(256) k_flatten(Ctx C, const double* __restrict__ P,
+static __global__ void LB(256) k_flatten(Ctx C, const double* __restrict__ P,
                                   const double* __restrict__ chi_abs,
                                   const double* __restrict__ chi_es, double* __restrict__ fl,
                                   int keep, const double* __restrict__ mf) {
@@ -848,7 +859,7 @@ DEV void emf_all_at(Ctx C, FaceRange R, const double* __restrict__ F, double* __
   }
 }
 
-__global__ void LB(256) k_emf_all(Ctx C, FaceRange R, const double* __restrict__ F,
+static __global__ void LB(256) k_emf_all(Ctx C, FaceRange R, const double* __restrict__ F,
                                   double* __restrict__ emf) {
   emf_all_at(C, R, F, emf, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
@@ -860,20 +871,22 @@ __global__ void LB(256) k_emf_all(Ctx C, FaceRange R, const double* __restrict__
 // (1/2) sqrt(-g) T^{k m} d_nu g_{k m}; both metrics are independent of t and
 // x3, so only nu = 1, 2 contribute.
 // ---------------------------------------------------------------------------
-template <class T>
-DEV T contract_sym(const double* dg, const T u[4], const T v[4]) {
+// dg_ab u^a u^b, the components that vanish with the metric's left out
+template <class M, class T>
+DEV T contract_sym(const double* dg, const T u[4]) {
   T s = T(0.0);
 #pragma unroll
   for (int a = 0; a < 4; a++)
 #pragma unroll
-    for (int b = 0; b < 4; b++) s = s + u[a] * v[b] * dg[sym(a, b)];
+    for (int b = 0; b < 4; b++)
+      if (!M::zlo(a, b)) s = s + u[a] * u[b] * dg[sym(a, b)];
   return s;
 }
 
 // Geometric source of the cell with primitives p: S[q] = 0 except the
 // x1, x2 momentum slots of gas and radiation (dg: d g_{km}/dx1, d/dx2).
-template <class T>
-DEV void geom_source(const Metric& m, const double dg[2][10], double gam, const T p[12], T S[12]) {
+template <class T, class M>
+DEV void geom_source(const M& m, const double dg[2][10], double gam, const T p[12], T S[12]) {
 #pragma unroll
   for (int q = 0; q < 12; q++) S[q] = T(0.0);
   Gas<T> s;
@@ -887,21 +900,25 @@ DEV void geom_source(const Metric& m, const double dg[2][10], double gam, const 
 #pragma unroll
     for (int a = 0; a < 4; a++)
 #pragma unroll
-      for (int b = 0; b < 4; b++) trace += m.up(a, b) * g[sym(a, b)];
-    const T sg = enth * contract_sym(g, s.v.ucon, s.v.ucon) + ptot * trace -
-                 contract_sym(g, s.bcon, s.bcon);
-    const T sr = (4.0 / 3.0) * p[8] * contract_sym(g, r.ucon, r.ucon) + (1.0 / 3.0) * p[8] * trace;
+      for (int b = 0; b < 4; b++)
+        if (!M::zup(a, b)) trace += m.up(a, b) * g[sym(a, b)];
+    const T sg = enth * contract_sym<M>(g, s.v.ucon) + ptot * trace - contract_sym<M>(g, s.bcon);
+    const T sr = (4.0 / 3.0) * p[8] * contract_sym<M>(g, r.ucon) + (1.0 / 3.0) * p[8] * trace;
     S[1 + nu] = 0.5 * m.gdet * sg;
     S[8 + nu] = 0.5 * m.gdet * sr;
   }
 }
 
+template <class M>
 DEV void load_dg(const Ctx& C, int pos, double dg[2][10]) {
 #pragma unroll
-  for (int q = 0; q < 10; q++) {
-    dg[0][q] = C.geo_c[(GE_DG1 + q) * C.npos + pos];
-    dg[1][q] = C.geo_c[(GE_DG2 + q) * C.npos + pos];
-  }
+  for (int a = 0; a < 4; a++)
+#pragma unroll
+    for (int b = a; b < 4; b++) {
+      if (M::zlo(a, b)) continue;
+      dg[0][sym(a, b)] = C.geo_c[(GE_DG1 + sym(a, b)) * C.npos + pos];
+      dg[1][sym(a, b)] = C.geo_c[(GE_DG2 + sym(a, b)) * C.npos + pos];
+    }
 }
 
 // The step's Courant reduction spreads its atomics over GRRMHD_DT_SLOTS
@@ -929,6 +946,7 @@ struct MTerms {
 // reduction's slots, which thread 0 also stores in *dt_dev while it resets
 // dtnext (the slots of the following step's reduction) to +inf.
 // cc = 0: no flux or geometric term (F, emf and P are not read).
+template <class Geo>
 DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
                    const unsigned long long* dtmin, unsigned long long* dtnext,
                    const double* __restrict__ P, const double* __restrict__ Un,
@@ -959,14 +977,15 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
   double div[12];
 #pragma unroll
   for (int q = 0; q < 12; q++) div[q] = 0.0;
-  if (cc != 0.0 && C.metric != GRRMHD_MINKOWSKI) {
+  if (cc != 0.0 && Geo::curved(C)) {
     const int pos = i + C.N[0] * j;
-    Metric m;
+    using M = typename Geo::template M<double>;
+    M m;
     load_metric(C.geo_c, C.npos, pos, m);
     double p[12], dg[2][10];
 #pragma unroll
     for (int q = 0; q < 12; q++) p[q] = P[q * C.Ntot + c];
-    load_dg(C, pos, dg);
+    load_dg<M>(C, pos, dg);
     geom_source(m, dg, C.gam, p, S);
   }
   for (int d = 0; d < 3 && cc != 0.0; d++) {
@@ -1021,13 +1040,14 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
   }
 }
 
+template <class Geo>
 __global__ void LB(256) k_update(Ctx C, double ca, double cb, double cc, double* dt_dev,
                                  const unsigned long long* dtmin, unsigned long long* dtnext,
                                  const double* __restrict__ P, const double* __restrict__ Un,
                                  const double* __restrict__ Uprev, const double* __restrict__ F,
                                  const double* __restrict__ emf, MTerms MT,
                                  double* __restrict__ Uexp, const double* __restrict__ Bface) {
-  update_at(C, ca, cb, cc, dt_dev, dtmin, dtnext, P, Un, Uprev, F, emf, MT, Uexp,
+  update_at<Geo>(C, ca, cb, cc, dt_dev, dtmin, dtnext, P, Un, Uprev, F, emf, MT, Uexp,
             (long)blockIdx.x * blockDim.x + threadIdx.x, Bface);
 }
 
@@ -1035,7 +1055,7 @@ __global__ void LB(256) k_update(Ctx C, double ca, double cb, double cc, double*
 // Courant time step: per-cell harmonic combination, block min, one atomic
 // per block on the ordered bit pattern of a positive double
 // ---------------------------------------------------------------------------
-__global__ void k_dt_init(unsigned long long* slot, int n, int stride) {
+static __global__ void k_dt_init(unsigned long long* slot, int n, int stride) {
   for (int i = threadIdx.x; i < n; i += blockDim.x) slot[(long)i * stride] = 0x7FF0000000000000ull;
 }
 
@@ -1072,14 +1092,14 @@ DEV void block_min_atomic(double v, unsigned long long* slot) {
   }
 }
 
-__global__ void LB(256) k_dt_min(Ctx C, const double* __restrict__ vchar,
+static __global__ void LB(256) k_dt_min(Ctx C, const double* __restrict__ vchar,
                                  unsigned long long* slot) {
   block_min_atomic(cell_dt(C, vchar, (long)blockIdx.x * blockDim.x + threadIdx.x), slot);
 }
 
 // The same, and the Courant reduction over interior cells into dtmin (the
 // grid covers both ranges; R.total = 0 when there are no EMFs)
-__global__ void LB(256) k_emf_dt(Ctx C, FaceRange R, const double* __restrict__ F,
+static __global__ void LB(256) k_emf_dt(Ctx C, FaceRange R, const double* __restrict__ F,
                                  double* __restrict__ emf, const double* __restrict__ vchar,
                                  unsigned long long* dtmin) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1087,7 +1107,7 @@ __global__ void LB(256) k_emf_dt(Ctx C, FaceRange R, const double* __restrict__ 
   block_min_atomic(cell_dt(C, vchar, t), dtmin + (blockIdx.x % GRRMHD_DT_SLOTS) * GRRMHD_DT_STRIDE);
 }
 
-__global__ void k_dt_final(const unsigned long long* slot, double courant, double* dt_out) {
+static __global__ void k_dt_final(const unsigned long long* slot, double courant, double* dt_out) {
   *dt_out = courant * __longlong_as_double((long long)*slot);
 }
 
@@ -1188,7 +1208,7 @@ DEV int wave_stats(int trips, unsigned long long* stats) {
 #define GRRMHD_ORDER_BUCKETS 64
 DEV int order_bucket(int key) { return ::min(::max(key, 0), GRRMHD_ORDER_BUCKETS - 1); }
 
-__global__ void __launch_bounds__(1024) k_tile_order(long ntiles, const int* __restrict__ keys,
+static __global__ void __launch_bounds__(1024) k_tile_order(long ntiles, const int* __restrict__ keys,
                                                      int* __restrict__ order) {
   __shared__ int cnt[GRRMHD_ORDER_BUCKETS];
   const long seg = ntiles / 8;
@@ -1211,7 +1231,7 @@ __global__ void __launch_bounds__(1024) k_tile_order(long ntiles, const int* __r
     order[lo + atomicAdd(&cnt[order_bucket(keys[t])], 1)] = (int)t;
 }
 
-__global__ void k_zero_ints(int* p, int k) {
+static __global__ void k_zero_ints(int* p, int k) {
   for (int i = threadIdx.x; i < k; i += blockDim.x) p[i] = 0;
 }
 
@@ -1255,6 +1275,7 @@ DEV bool tile_cell(const Ctx& C, int ti, long wave, int lane, int& i, int& j, in
   return true;
 }
 
+template <class Geo>
 __global__ void LBI k_implicit(Ctx C, int ti, const double* __restrict__ Uexp, const double* Pguess,
                                   double dt_scale, const double* __restrict__ dt_dev,
                                   const double* __restrict__ chi_abs,
@@ -1274,7 +1295,7 @@ __global__ void LBI k_implicit(Ctx C, int ti, const double* __restrict__ Uexp, c
   if (tile_cell(C, ti, tile, threadIdx.x, i, j, k)) {
     t = (i - C.ng[0]) + (long)C.n[0] * ((j - C.ng[1]) + (long)C.n[1] * (k - C.ng[2]));
     const long c = cell_index(C, i, j, k);
-    Metric m;
+    typename Geo::template M<double> m;
     load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -1283,8 +1304,8 @@ __global__ void LBI k_implicit(Ctx C, int ti, const double* __restrict__ Uexp, c
       Pg[q] = Pguess[q * C.Ntot + c];
     }
     CellOut o;
-    if (implicit_fast(m, make_phys(C), make_opts(C), Ui, Pg, dt_scale * (*dt_dev), chi_abs[c],
-                      chi_es[c], o, b, it, extreme, trips))
+    if (implicit_first(m, make_phys(C), make_opts(C), Ui, Pg, dt_scale * (*dt_dev), chi_abs[c],
+                       chi_es[c], o, b, it, extreme, trips))
       store_out(o, c, C.Ntot, P, U, iters, status, err);
     else
       need = true;
@@ -1298,7 +1319,7 @@ __global__ void LBI k_implicit(Ctx C, int ti, const double* __restrict__ Uexp, c
 // the device.
 // FULL: the paper's full cascade (params.cascade = 1), a separate
 // instantiation so the normal cascade keeps its smaller register footprint
-template <bool FULL>
+template <class Geo, bool FULL>
 __global__ void LB(64) k_implicit_list(Ctx C, const double* __restrict__ Uexp,
                                        const double* Pguess, double dt_scale,
                                        const double* __restrict__ dt_dev,
@@ -1317,7 +1338,7 @@ __global__ void LB(64) k_implicit_list(Ctx C, const double* __restrict__ Uexp,
     const int j = C.ng[1] + t2 % C.n[1];
     const int k = C.ng[2] + t2 / C.n[1];
     const long c = cell_index(C, i, j, k);
-    Metric m;
+    typename Geo::template M<double> m;
     load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -1337,6 +1358,7 @@ __global__ void LB(64) k_implicit_list(Ctx C, const double* __restrict__ Uexp,
 }
 
 // Independent flat-space cells: same two-kernel structure.
+template <class Geo>
 __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ Ui_,
                                         const double* __restrict__ Pg_,
                                         const double* __restrict__ dtc,
@@ -1369,6 +1391,7 @@ __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ U
   to_cascade(need, extreme, (int)c, b, it, W);
 }
 
+template <class Geo>
 __global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __restrict__ Ui_,
                                              const double* __restrict__ Pg_,
                                              const double* __restrict__ dtc,
@@ -1415,6 +1438,7 @@ __global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __rest
 // attempt's conditions (listed in K by the cascade kernels): the cold MHD
 // limit, one thread each; the iterations of the cell's energy attempts (in
 // `iters`, when kept) are carried on.
+template <class Geo>
 __global__ void LB(64) k_cold_batch_list(Ctx C, long n, const double* __restrict__ Ui_,
                                          const double* __restrict__ Pg_,
                                          const double* __restrict__ dtc,
@@ -1447,6 +1471,7 @@ __global__ void LB(64) k_cold_batch_list(Ctx C, long n, const double* __restrict
 // The full cascade's rest (params.cascade = 1) for batch cells the PMHD and
 // URAD attempts left unaccepted: K lists their record slots; each resumes
 // after both attempts (one thread per cell).
+template <class Geo>
 __global__ void LB(64) k_rest_batch_list(Ctx C, long n, const double* __restrict__ Ui_,
                                          const double* __restrict__ Pg_,
                                          const double* __restrict__ dtc,
@@ -1481,6 +1506,7 @@ __global__ void LB(64) k_rest_batch_list(Ctx C, long n, const double* __restrict
 // the next entry as soon as their cell ends.  Extreme cells (URAD first, then
 // PMHD from scratch) go to the deferred list D for the per-cell cascade.
 // Results equal those of implicit_cell resuming from the same record.
+template <class Geo>
 __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ Ui_,
                                       const double* __restrict__ Pg_,
                                       const double* __restrict__ dtc,
@@ -1600,6 +1626,7 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
 }
 
 // fail_bits: extra status bits of a cell whose MHD inversion fails
+template <class Geo>
 __global__ void LB(128) k_con2prim(Ctx C, const double* __restrict__ U, const double* Pguess,
                                    double* P, int* __restrict__ status, int fail_bits) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1610,7 +1637,7 @@ __global__ void LB(128) k_con2prim(Ctx C, const double* __restrict__ U, const do
   const int j = C.ng[1] + t2 % C.n[1];
   const int k = C.ng[2] + t2 / C.n[1];
   const long c = cell_index(C, i, j, k);
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   const double igd = 1.0 / m.gdet;
   double u[12], p[12];
@@ -1637,7 +1664,7 @@ __global__ void LB(128) k_con2prim(Ctx C, const double* __restrict__ U, const do
 }
 
 // the 12 fields of src at interior cells into dst (ghost cells untouched)
-__global__ void LB(256) k_copy_interior12(Ctx C, const double* __restrict__ src,
+static __global__ void LB(256) k_copy_interior12(Ctx C, const double* __restrict__ src,
                                           double* __restrict__ dst) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const long nint = (long)C.n[0] * C.n[1] * C.n[2];
@@ -1655,7 +1682,7 @@ __global__ void LB(256) k_copy_interior12(Ctx C, const double* __restrict__ src,
 // M = (U_out - U_expl) / (g dt) in the gas and radiation energy-momentum
 // slots (rows 0-3: U slots 1-4, rows 4-7: slots 8-11; [8][Ntot]), zero where
 // the solve failed.
-__global__ void LB(256) k_stage_m(Ctx C, const double* __restrict__ Ue,
+static __global__ void LB(256) k_stage_m(Ctx C, const double* __restrict__ Ue,
                                   const double* __restrict__ Uo, const int* __restrict__ status,
                                   double g, const double* __restrict__ dt_dev,
                                   double* __restrict__ M) {
@@ -1680,7 +1707,7 @@ __global__ void LB(256) k_stage_m(Ctx C, const double* __restrict__ Ue,
 // dt sum_k m_k M_S^k (MT's arrays: [N] each), and an implicit stage stores
 // M_S = (U_S(P_out) - explicit)/(g dt) from its solution before the fix-ups
 // (zero where the solve failed), as k_stage_m the other sources.
-__global__ void LB(256) k_entropy_mterms(Ctx C, MTerms MT, const double* __restrict__ dt_dev,
+static __global__ void LB(256) k_entropy_mterms(Ctx C, MTerms MT, const double* __restrict__ dt_dev,
                                          double* __restrict__ Sexp) {
   int i, j, k;
   if (!interior_ijk(C, (long)blockIdx.x * blockDim.x + threadIdx.x, i, j, k)) return;
@@ -1690,6 +1717,7 @@ __global__ void LB(256) k_entropy_mterms(Ctx C, MTerms MT, const double* __restr
   Sexp[c] += (*dt_dev) * sm;
 }
 
+template <class Geo>
 __global__ void LB(256) k_stage_ms(Ctx C, const double* __restrict__ Po,
                                    const double* __restrict__ Sexp, const int* __restrict__ status,
                                    double g, const double* __restrict__ dt_dev,
@@ -1701,7 +1729,7 @@ __global__ void LB(256) k_stage_ms(Ctx C, const double* __restrict__ Po,
     MS[c] = 0.0;
     return;
   }
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   double p[5];
 #pragma unroll
@@ -1754,11 +1782,12 @@ DEV void fixup_avg_at(Ctx C, const double* __restrict__ P,
   scr[12 * C.Ntot + c] = 0.0;
 }
 
-__global__ void LB(256) k_fixup_avg(Ctx C, const double* __restrict__ P,
+static __global__ void LB(256) k_fixup_avg(Ctx C, const double* __restrict__ P,
                                     const int* __restrict__ status, double* __restrict__ scr) {
   fixup_avg_at(C, P, status, scr, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
+template <class Geo>
 DEV void fixup_apply_at(Ctx C, double* __restrict__ P, double* __restrict__ U,
                                       int* __restrict__ status, const double* __restrict__ scr,
                                       int* __restrict__ st_acc, const int* __restrict__ it_stage,
@@ -1775,7 +1804,7 @@ DEV void fixup_apply_at(Ctx C, double* __restrict__ P, double* __restrict__ U,
   bool changed = false;
   const bool fail = (st & GRRMHD_ST_FAIL) != 0;
   const bool cold = !fail && (st & GRRMHD_ST_COLD);
-  Metric m;
+  typename Geo::template M<double> m;
   load_metric(C.geo_c, C.npos, i + C.N[0] * j, m);
   if ((fail || cold) && scr[12 * C.Ntot + c] > 0.0) {
     // failed: the neighbours' mean primitives; cold: their mean u_g alone
@@ -1826,11 +1855,13 @@ DEV void fixup_apply_at(Ctx C, double* __restrict__ P, double* __restrict__ U,
   if (it_acc && it_stage) it_acc[c] = accumulate ? it_acc[c] + it_stage[c] : it_stage[c];
 }
 
+template <class Geo>
 __global__ void LB(256) k_fixup_apply(Ctx C, double* __restrict__ P, double* __restrict__ U,
                                       int* __restrict__ status, const double* __restrict__ scr,
                                       int* __restrict__ st_acc, const int* __restrict__ it_stage,
                                       int* __restrict__ it_acc, int accumulate) {
-  fixup_apply_at(C, P, U, status, scr, st_acc, it_stage, it_acc, accumulate, (long)blockIdx.x * blockDim.x + threadIdx.x);
+  fixup_apply_at<Geo>(C, P, U, status, scr, st_acc, it_stage, it_acc, accumulate,
+                      (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1846,12 +1877,9 @@ __global__ void LB(256) k_fixup_apply(Ctx C, double* __restrict__ P, double* __r
 // ---------------------------------------------------------------------------
 #define LBP __launch_bounds__(256, 1)
 
-DEV void setup_cell(const Metric& m, const double Ui[12], double dt, double ca, double ce, Cell& c) {
-  cell_setup(m, Ui, dt, ca, ce, c);
-}
 
-
-DEV void finish_lane(const Cell& c, const Phys& ph, const Opts& o, Lane& L, double U0,
+template <class M>
+DEV void finish_lane(const CellT<M>& c, const Phys& ph, const Opts& o, Lane& L, double U0,
                      const double UB[3], long cidx, long nst, double* P, double* U, int* iters,
                      int* status, double* err) {
   double Uk[12];
@@ -1864,6 +1892,7 @@ DEV void finish_lane(const Cell& c, const Phys& ph, const Opts& o, Lane& L, doub
   store_out(out, cidx, nst, P, U, iters, status, err);
 }
 
+template <class Geo>
 __global__ void LBP k_implicit_persist(Ctx C, long n, const double* __restrict__ Ui_,
                                        const double* __restrict__ Pg_,
                                        const double* __restrict__ dtc,
@@ -2016,6 +2045,7 @@ DEV void lane_load(Lane& L, long c, long n, const double* sd, const int* si) {
 }
 
 // first trip of every cell: guess, first evaluation; active cells to queue
+template <class Geo>
 __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui_,
                                     const double* __restrict__ Pg_, const double* __restrict__ dtc,
                                     const double* __restrict__ chi_abs,
@@ -2059,6 +2089,7 @@ __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui
 }
 
 // one Newton trip for every queued cell
+template <class Geo>
 __global__ void LB(64) k_iter_step(Ctx C, long n, const double* __restrict__ Ui_,
                                    const double* __restrict__ dtc,
                                    const double* __restrict__ chi_abs,
@@ -2086,7 +2117,7 @@ __global__ void LB(64) k_iter_step(Ctx C, long n, const double* __restrict__ Ui_
 #pragma unroll
       for (int q = 0; q < 12; q++) Ui[q] = Ui_[q * n + cidx];
       Cell c;
-      setup_cell(m, Ui, dtc[cidx], chi_abs[cidx], chi_es[cidx], c);
+      cell_setup(m, Ui, dtc[cidx], chi_abs[cidx], chi_es[cidx], c);
       lane_load(L, cidx, n, sd, si);
       double xprev[4] = {L.x[0], L.x[1], L.x[2], L.x[3]};
       bool ended = lane_step(c, o, L);

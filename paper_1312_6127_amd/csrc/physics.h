@@ -16,29 +16,40 @@ struct Vel {
   T usq;   // g_ij u~^i u~^j
 };
 
-template <class T>
-DEV void make_vel(const MetricT<typename RealOf<T>::type>& m, const T ut[3], Vel<T>& v) {
+// g_ab v^b
+template <class T, class M>
+DEV T lower(const M& m, int a, const T v[4]) {
+  if (M::diagonal) return a == 0 ? -v[0] : v[a];
+  if (!M::dense && a == 2) return m.lo(2, 2) * v[2];
+  T s = m.lo(a, 0) * v[0];
+#pragma unroll
+  for (int b = 1; b < 4; b++)
+    if (!M::zlo(a, b)) s = s + m.lo(a, b) * v[b];
+  return s;
+}
+
+template <class T, class M>
+DEV void make_vel(const M& m, const T ut[3], Vel<T>& v) {
   using R = typename RealOf<T>::type;
   T q = T(R(0.0));
 #pragma unroll
   for (int i = 0; i < 3; i++) {
     q = q + m.lo(i + 1, i + 1) * ut[i] * ut[i];
 #pragma unroll
-    for (int j = i + 1; j < 3; j++) q = q + R(2.0) * m.lo(i + 1, j + 1) * ut[i] * ut[j];
+    for (int j = i + 1; j < 3; j++)
+      if (!M::zlo(i + 1, j + 1)) q = q + R(2.0) * m.lo(i + 1, j + 1) * ut[i] * ut[j];
   }
   v.usq = q;
   v.gamma = sqrt(R(1.0) + q);
   const T ga = v.gamma * m.alpha;
   v.ucon[0] = v.gamma / m.alpha;
 #pragma unroll
-  for (int i = 0; i < 3; i++) v.ucon[i + 1] = ut[i] - ga * m.up(0, i + 1);
-#pragma unroll
-  for (int a = 0; a < 4; a++) {
-    T s = m.lo(a, 0) * v.ucon[0];
-#pragma unroll
-    for (int b = 1; b < 4; b++) s = s + m.lo(a, b) * v.ucon[b];
-    v.ucov[a] = s;
+  for (int i = 0; i < 3; i++) {
+    if (M::zup(0, i + 1)) v.ucon[i + 1] = ut[i];
+    else v.ucon[i + 1] = ut[i] - ga * m.up(0, i + 1);
   }
+#pragma unroll
+  for (int a = 0; a < 4; a++) v.ucov[a] = lower(m, a, v.ucon);
 }
 
 // gas state: velocity, fluid-frame field b^mu = B^nu h^mu_nu / u^t (Sec. 2)
@@ -50,8 +61,8 @@ struct Gas {
   T opu;   // 1 + u_t, free of the rest-mass cancellation
 };
 
-template <class T>
-DEV void make_gas(const MetricT<typename RealOf<T>::type>& m, double gam, const T& rho,
+template <class T, class M>
+DEV void make_gas(const M& m, double gam, const T& rho,
                   const T& ug, const T ut[3], const T B[3], Gas<T>& s) {
   using R = typename RealOf<T>::type;
   make_vel(m, ut, s.v);
@@ -64,27 +75,29 @@ DEV void make_gas(const MetricT<typename RealOf<T>::type>& m, double gam, const 
 #pragma unroll
   for (int i = 0; i < 3; i++) s.bcon[i + 1] = (B[i] + bt * s.v.ucon[i + 1]) * iut;
 #pragma unroll
-  for (int a = 0; a < 4; a++) {
-    T q = m.lo(a, 0) * s.bcon[0];
-#pragma unroll
-    for (int b = 1; b < 4; b++) q = q + m.lo(a, b) * s.bcon[b];
-    s.bcov[a] = q;
-  }
+  for (int a = 0; a < 4; a++) s.bcov[a] = lower(m, a, s.bcon);
   s.bsq = s.bcon[0] * s.bcov[0] + s.bcon[1] * s.bcov[1] + s.bcon[2] * s.bcov[2] +
           s.bcon[3] * s.bcov[3];
   // u_t = g_ti u~^i - alpha gamma  =>  1 + u_t = (1 - alpha) - alpha u~^2/(1 + gamma) + g_ti u~^i
-  T gtu = m.lo(0, 1) * ut[0] + m.lo(0, 2) * ut[1] + m.lo(0, 3) * ut[2];
+  T gtu = T(R(0.0));
+  if constexpr (M::dense) gtu = m.lo(0, 1) * ut[0] + m.lo(0, 2) * ut[1] + m.lo(0, 3) * ut[2];
+  else if constexpr (!M::diagonal) gtu = m.lo(0, 1) * ut[0] + m.lo(0, 3) * ut[2];
   s.opu = (R(1.0) - m.alpha) - m.alpha * s.v.usq / (R(1.0) + s.v.gamma) + gtu;
+}
+
+// p_gas + b^2/2, the gas pressure's product fused with the sum
+DEV double ptot_fused(const Gas<double>& s, double gam) {
+  return __builtin_fma(gam - 1.0, s.ug, 0.5 * s.bsq);
 }
 
 // Row mu of the gas conserved/flux vector (Sec. 4 lists of U_q and F_q):
 // out[0] = rho u^mu, out[1] = T^mu_t + rho u^mu, out[2..4] = T^mu_i,
 // out[5..7] = B^i (mu = 0) or b^i u^mu - b^mu u^i, all without sqrt(-g).
 template <class T>
-DEV void gas_row(const Gas<T>& s, const T B[3], int mu, T out[8]) {
+DEV void gas_row(const Gas<T>& s, const T B[3], int mu, T out[8], const T* pt = nullptr) {
   using R = typename RealOf<T>::type;
   const T um = s.v.ucon[mu];
-  const T ptot = s.pg + R(0.5) * s.bsq;
+  const T ptot = pt ? *pt : s.pg + R(0.5) * s.bsq;
   const T enth = s.rho + s.ug + s.pg + s.bsq;
   out[0] = s.rho * um;
   out[1] = s.rho * um * s.opu + (s.ug + s.pg + s.bsq) * um * s.v.ucov[0] - s.bcon[mu] * s.bcov[0];
@@ -136,8 +149,8 @@ DEV void four_force(const Vel<T>& u, const Vel<T>& r, const T& E, const T& kabs,
 // frame of 4-velocity u: the two roots of
 // [(1-c2)(u^t)^2 - c2 g^tt] v^2 - 2[(1-c2) u^t u^d - c2 g^td] v + [(1-c2)(u^d)^2 - c2 g^dd] = 0
 // (the dispersion relation (k.u)^2 = c2 (k.k + (k.u)^2) with k = d(x^d - v t)).
-template <class T>
-DEV void char_speeds(const MetricT<typename RealOf<T>::type>& m, const T u[4], T c2, int dir,
+template <class T, class M>
+DEV void char_speeds(const M& m, const T u[4], T c2, int dir,
                      T& vm, T& vp) {
   using R = typename RealOf<T>::type;
   const T A = (R(1.0) - c2) * u[0] * u[0] - c2 * m.up(0, 0);

@@ -99,7 +99,7 @@ DEV void face_bc_at(const Ctx& C, double* __restrict__ Bf, long t) {
   B[c] = v;
 }
 
-__global__ void LB(256) k_bc_faces(Ctx C, double* __restrict__ Bf) {
+static __global__ void LB(256) k_bc_faces(Ctx C, double* __restrict__ Bf) {
   face_bc_at(C, Bf, (long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
@@ -108,7 +108,7 @@ __global__ void LB(256) k_bc_faces(Ctx C, double* __restrict__ Bf) {
 // on an inactive q), P[5+q] = U[5+q] / sqrt(-g) at the centre; interior
 // cells; P or U may be null
 // ---------------------------------------------------------------------------
-__global__ void LB(256) k_face_center(Ctx C, const double* __restrict__ Bf, double* __restrict__ P,
+static __global__ void LB(256) k_face_center(Ctx C, const double* __restrict__ Bf, double* __restrict__ P,
                                       double* __restrict__ U) {
   int i, j, k;
   if (!interior_ijk(C, (long)blockIdx.x * blockDim.x + threadIdx.x, i, j, k)) return;
@@ -258,7 +258,7 @@ DEV void emf_stag_at(const Ctx& C, const FaceRange& R, const double* __restrict_
   }
 }
 
-__global__ void LB(256) k_emf_stag(Ctx C, FaceRange R, const double* __restrict__ Bf,
+static __global__ void LB(256) k_emf_stag(Ctx C, FaceRange R, const double* __restrict__ Bf,
                                    const double* __restrict__ VF, const double* __restrict__ SP,
                                    double* __restrict__ emf) {
   emf_stag_at(C, R, Bf, VF, SP, emf, (long)blockIdx.x * blockDim.x + threadIdx.x);
@@ -266,7 +266,7 @@ __global__ void LB(256) k_emf_stag(Ctx C, FaceRange R, const double* __restrict_
 
 // the same with the step's Courant reduction over interior cells (the grid
 // covers both ranges)
-__global__ void LB(256) k_emf_stag_dt(Ctx C, FaceRange R, const double* __restrict__ Bf,
+static __global__ void LB(256) k_emf_stag_dt(Ctx C, FaceRange R, const double* __restrict__ Bf,
                                       const double* __restrict__ VF,
                                       const double* __restrict__ SP, double* __restrict__ emf,
                                       const double* __restrict__ vchar,
@@ -283,7 +283,7 @@ __global__ void LB(256) k_emf_stag_dt(Ctx C, FaceRange R, const double* __restri
 // across).  dt: *dt_dev, or courant x the Courant slots' minimum.  cc = 0
 // (an IMEX stage without explicit fluxes): no EMF term and no EMF read.
 // ---------------------------------------------------------------------------
-__global__ void LB(256) k_face_update(Ctx C, FaceRange R, double a, double b, double cc,
+static __global__ void LB(256) k_face_update(Ctx C, FaceRange R, double a, double b, double cc,
                                       const double* __restrict__ dt_dev,
                                       const unsigned long long* __restrict__ dtmin,
                                       const double* Bn, const double* __restrict__ Bprev,
