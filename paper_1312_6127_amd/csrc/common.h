@@ -159,16 +159,19 @@ struct KSMetric {
 
 // What a kernel is compiled for.
 struct KS {
+  static constexpr bool closed = true;
   DEV static constexpr bool curved(const Ctx&) { return true; }
   template <class R>
   using M = KSMetric<R>;
 };
 struct Flat {
+  static constexpr bool closed = true;
   DEV static constexpr bool curved(const Ctx&) { return false; }
   template <class R>
   using M = FlatMetric<R>;
 };
 struct Dense {
+  static constexpr bool closed = false;   // the closed forms of pointwise.h don't apply
   DEV static bool curved(const Ctx& C) { return C.metric == GRRMHD_KERR_SCHILD; }
   template <class R>
   using M = DenseMetric<R>;

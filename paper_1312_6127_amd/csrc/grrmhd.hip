@@ -535,6 +535,16 @@ static int launch_flattener(grrmhd_grid* g, const double* P, const double* ca, c
   return 0;
 }
 
+// launch geometry of the flux kernels
+#define FLUX_BLOCK 64
+static void add_faces(FluxSegs& S, const FaceRange& r, int D) {
+  S.R[S.n] = r;
+  S.D[S.n++] = D;
+  S.pieces = std::max(S.pieces, (int)nblocks((long)r.cnt[0] * r.cnt[1], FLUX_BLOCK));
+  S.nk = std::max(S.nk, r.cnt[2]);
+}
+static dim3 flux_blocks(const FluxSegs& S) { return dim3((unsigned)S.pieces * S.nk * S.n); }
+
 // The faces that set a step's dt keep the dense form: a gradient taken at that
 // dt moves by 1e-6 with its last bit.
 #define STAG_KERNEL(g, ENTF)                                                   \
@@ -554,38 +564,28 @@ static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const doubl
   // faces of every direction, FP64 part and FP32 part (split at mixed_i)
   FluxSegs S64, S32;
   S64.n = S32.n = 0;
-  S64.total = S32.total = 0;
+  S64.pieces = S32.pieces = S64.nk = S32.nk = 0;
   for (int d = 0; d < 3; d++) {
     if (C.n[d] == 1) continue;
     FaceRange r64, r32;
     split_x1(face_range(C, d, Bf ? 2 : 1), C.mixed_i, r64, r32);
-    if (r64.total > 0) {
-      S64.R[S64.n] = r64; S64.D[S64.n] = d + 1; S64.start[S64.n] = S64.total;
-      S64.total += r64.total; S64.n++;
-    }
-    if (r32.total > 0) {
-      S32.R[S32.n] = r32; S32.D[S32.n] = d + 1; S32.start[S32.n] = S32.total;
-      S32.total += r32.total; S32.n++;
-    }
+    if (r64.total > 0) add_faces(S64, r64, d + 1);
+    if (r32.total > 0) add_faces(S32, r32, d + 1);
   }
   if (Bf) {
     const double* flp = (const double*)g->flat;
-    if (S64.total > 0) {
+    if (S64.n > 0) {
       if (Fs)
-        hipLaunchKernelGGL(STAG_KERNEL(g, true), dim3(nblocks(S64.total, 128)), dim3(128),
-                           0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL(STAG_KERNEL(g, true), flux_blocks(S64), dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL(STAG_KERNEL(g, false), dim3(nblocks(S64.total, 128)),
-                           dim3(128), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL(STAG_KERNEL(g, false), flux_blocks(S64), dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
-    if (S32.total > 0) {
+    if (S32.n > 0) {
       if (Fs)
-        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, true>), dim3(nblocks(S32.total, 128)), dim3(128),
-                           0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, true>), flux_blocks(S32), dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, false>), dim3(nblocks(S32.total, 128)),
-                           dim3(128), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, false>), flux_blocks(S32), dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
     // four-state corner EMFs at [ng, ng+n] on each active axis
@@ -607,21 +607,21 @@ static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const doubl
     LAUNCHCHK();
     return 0;
   }
-  if (S64.total > 0) {
+  if (S64.n > 0) {
     if (Fs)
-      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all_s, double), dim3(nblocks(S64.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all_s, double), flux_blocks(S64), dim3(FLUX_BLOCK), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all, double), dim3(nblocks(S64.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all, double), flux_blocks(S64), dim3(FLUX_BLOCK), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }
-  if (S32.total > 0) {
+  if (S32.n > 0) {
     if (Fs)
-      hipLaunchKernelGGL((k_flux_all_s<Dense, float>), dim3(nblocks(S32.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL((k_flux_all_s<Dense, float>), flux_blocks(S32), dim3(FLUX_BLOCK), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL((k_flux_all<Dense, float>), dim3(nblocks(S32.total, 128)), dim3(128), 0,
+      hipLaunchKernelGGL((k_flux_all<Dense, float>), flux_blocks(S32), dim3(FLUX_BLOCK), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }
@@ -663,6 +663,7 @@ static int launch_timestep(grrmhd_grid* g, const double* vch, double* dt_dev) {
   return 0;
 }
 
+#define UPDATE_BLOCK 128
 // dtmin set: dt = courant x *dtmin, stored in *dt_dev; *dtnext reset to +inf
 static int launch_update(grrmhd_grid* g, Form form, double a, double b, double c, const double* dt_dev,
                          const double* P, const double* Un, const double* Up, const double* F,
@@ -672,7 +673,9 @@ static int launch_update(grrmhd_grid* g, Form form, double a, double b, double c
   MTerms MT;
   memset(&MT, 0, sizeof(MT));
   if (mt) MT = *mt;
-  hipLaunchKernelGGL(GEO_KERNEL(g, form, k_update), dim3(nblocks(n_interior(g->C), 256)), dim3(256), 0, g->stream,
+  const int* n = g->C.n;
+  hipLaunchKernelGGL(GEO_KERNEL(g, form, k_update), dim3(nblocks((long)n[0] * n[1], UPDATE_BLOCK) * n[2]),
+                     dim3(UPDATE_BLOCK), 0, g->stream,
                      g->C, a, b, c, const_cast<double*>(dt_dev), dtmin, dtnext, P, Un, Up, F, emf,
                      MT, Ue, Bface);
   LAUNCHCHK();
@@ -888,7 +891,7 @@ static int imex_step(grrmhd_grid* g, double* P, double* U, double* Bf, const dou
                            Bcur);
         LAUNCHCHK();
       }
-      if ((rc = launch_fluxes(g, form, Pcur, chi_abs, chi_es, F, emf, vch, dmin, nflux > 0, Fs, Bcur,
+      if ((rc = launch_fluxes(g, form, Pcur, chi_abs, chi_es, F, emf, dmin ? vch : nullptr, dmin, nflux > 0, Fs, Bcur,
                               VF, SP)))
         return rc;
       nflux++;
@@ -1026,7 +1029,8 @@ static int rk3_step(grrmhd_grid* g, double* P, double* U, double* Bf, const doub
     const bool red = (s == 0 && !dt_fixed);
     unsigned long long* dmin = red ? g->dtstep[g->dtp] : nullptr;
     unsigned long long* dnext = red ? g->dtstep[g->dtp ^ 1] : nullptr;
-    if ((rc = launch_fluxes(g, form, Pin, chi_abs, chi_es, F, emf, vch, dmin, s > 0, Fs, Bin, VF, SP)))
+    if ((rc = launch_fluxes(g, form, Pin, chi_abs, chi_es, F, emf, dmin ? vch : nullptr, dmin, s > 0, Fs,
+                            Bin, VF, SP)))
       return rc;
     if (Bf) {
       // the stage's faces (before the cell update, which averages them)

@@ -5,9 +5,11 @@
 #include "pointwise.h"
 
 #define LB(n) __launch_bounds__(n)
-#ifndef GRRMHD_FLUX_LB
-#define GRRMHD_FLUX_LB __launch_bounds__(128)
-#endif
+// Three wavefronts per SIMD for the closed forms on MC and PPM faces: 28 bytes
+// of the stencil spill, and a 128x64x32 launch takes 57 us (at the two that
+// 174 registers allow: 65; at four, 188 bytes: 101).  The staggered faces,
+// with more to hold, gain nothing from the third (34 and 35 us at 80x50x20).
+#define FLUX_LB __launch_bounds__(64, Geo::closed ? 3 : 1)
 
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup b to XCD b mod 8)
 // and each XCD has its own L2.  This maps b to a work index so that each XCD
@@ -297,6 +299,136 @@ DEV void face_state(const Ctx& C, const M& m, int d, const T* P,
   face_speeds(C, m, d, P, chi_tot, s, r, fs.gm, fs.gp, fs.rm, fs.rp);
 }
 
+// face_state on the closed forms of pointwise.h, FP64 on a sparse metric:
+// the same state, fluxes and speeds, with the terms that depend on the face
+// alone (FaceGeom) formed once for its two states.  face_state's 32 divisions
+// and 14 square roots per face are half its issue cycles; here 10 reciprocals
+// and 8 to 10 roots remain.  With this, the order of column_piece and a third
+// wavefront per SIMD a launch takes 57 us instead of 79 at 128x64x32 and 537
+// instead of 716 at 256x128x64.
+template <class M>
+struct FaceGeom {
+  double ia, beta, ugg;   // 1/alpha; the shift; -(1/alpha)^2 = g^tt
+  double udd, u0d, k;     // g^dd, g^td, (g^td)^2 - g^tt g^dd
+  double hdx;             // sqrt(g_dd) dx^d
+};
+template <int D, class M>
+DEV void face_geom(const Ctx& C, const M& m, FaceGeom<M>& g) {
+  if constexpr (M::diagonal) {
+    g.ia = 1.0;
+    g.beta = 0.0;
+    g.ugg = -1.0;
+    g.udd = 1.0;
+    g.u0d = 0.0;
+    g.k = 1.0;
+    g.hdx = C.dx[D - 1];
+  } else {
+    g.ia = recip(m.alpha);
+    g.beta = m.alpha * m.alpha * m.u01;
+    g.ugg = m.u00;
+    g.udd = m.up(D, D);
+    g.u0d = D == 1 ? m.u01 : 0.0;
+    g.k = g.u0d * g.u0d - m.u00 * g.udd;
+    g.hdx = root0(m.lo(D, D)) * C.dx[D - 1];
+  }
+}
+
+// char_speeds: u0, ud the frame's u^t and u^D
+template <class M>
+DEV void face_char(const FaceGeom<M>& g, double u0, double ud, double c2, double& vm, double& vp) {
+  const double o = 1.0 - c2;
+  const double A = o * u0 * u0 - c2 * g.ugg, B = o * u0 * ud - c2 * g.u0d;
+  const double h = u0 * u0 * g.udd - 2.0 * u0 * ud * g.u0d + ud * ud * g.ugg;
+  const double sq = root0(fmax(c2 * (o * h + c2 * g.k), 0.0)), iA = recip(A);
+  const double v1 = (B + sq) * iA, v2 = (B - sq) * iA;
+  vp = fmax(v1, v2);
+  vm = fmin(v1, v2);
+}
+
+// u^mu and u_mu of u~ (ul: u~_i); returns gamma, i0 = 1/u^t
+template <class M>
+DEV double face_vel(const M& m, const FaceGeom<M>& g, const double ut[3], double ul[3], double& q,
+                    double& u0, double& i0, double uc[3], double& ut_) {
+  low3(m, ut, ul);
+  q = dot3(ut, ul);
+  double ig;
+  const double gam = root(1.0 + q, ig);
+  if constexpr (M::diagonal) {
+    u0 = gam;
+    i0 = ig;
+    ut_ = -gam;
+#pragma unroll
+    for (int i = 0; i < 3; i++) uc[i] = ut[i];
+  } else {
+    u0 = gam * g.ia;
+    i0 = m.alpha * ig;
+    uc[0] = ut[0] - u0 * g.beta;
+    uc[1] = ut[1];
+    uc[2] = ut[2];
+    ut_ = g.beta * ul[0] - m.alpha * gam;
+  }
+  return gam;
+}
+
+template <int D, class M>
+DEV void face_closed(const Ctx& C, const M& m, const FaceGeom<M>& g, const double P[12],
+                     double chi_tot, FaceState<double>& fs) {
+  const double* B = P + 5;
+  const double rho = P[0], ug = P[1], pg = (C.gam - 1.0) * ug, gd = m.gdet;
+  double ul[3], uc[3], q, u0, i0, ut;
+  const double gam = face_vel(m, g, P + 2, ul, q, u0, i0, uc, ut);
+  double opu;
+  if constexpr (M::diagonal) opu = -q * recip(1.0 + gam);
+  else opu = (1.0 - m.alpha) - m.alpha * q * recip(1.0 + gam) + g.beta * ul[0];
+  double Bl[3];
+  low3(m, B, Bl);
+  const double bt = dot3(B, ul);
+  const double bsq = (dot3(B, Bl) + bt * bt) * i0 * i0;
+  double bc[3], bl[3];
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    bc[i] = (B[i] + bt * uc[i]) * i0;
+    bl[i] = (Bl[i] + bt * ul[i]) * i0;
+  }
+  const double b0 = M::diagonal ? bt * ut * i0 : (g.beta * Bl[0] + bt * ut) * i0;
+  const double w = rho + ug + pg, enth = w + bsq, ptot = pg + 0.5 * bsq;
+  const double hm = ug + pg + bsq;
+  const double ud = uc[D - 1], bd = bc[D - 1], r0 = rho * u0, rd = rho * ud;
+  fs.U[0] = gd * r0;
+  fs.F[0] = gd * rd;
+  fs.U[1] = gd * (r0 * opu + hm * u0 * ut - bt * b0 + ptot);
+  fs.F[1] = gd * (rd * opu + hm * ud * ut - bd * b0);
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    const double eu = enth * ul[i];
+    fs.U[2 + i] = gd * (eu * u0 - bt * bl[i]);
+    fs.F[2 + i] = gd * (eu * ud - bd * bl[i] + (i == D - 1 ? ptot : 0.0));
+    fs.U[5 + i] = gd * B[i];
+    fs.F[5 + i] = i == D - 1 ? 0.0 : gd * (bc[i] * ud - bd * uc[i]);
+  }
+  // gas: c_ms^2 = v_A^2 + c_s^2 (1 - v_A^2) = (b^2 + gam p)/(w + b^2)
+  face_char(g, u0, ud, (bsq + C.gam * pg) * recip(enth), fs.gm, fs.gp);
+  double rl[3], rc[3], rq, s0, si, rt;
+  face_vel(m, g, P + 9, rl, rq, s0, si, rc, rt);
+  const double sd = rc[D - 1], E3 = P[8] * (1.0 / 3.0), f0 = 4.0 * E3 * s0 * gd, fd = 4.0 * E3 * sd * gd;
+  fs.U[8] = f0 * rt + gd * E3;
+  fs.F[8] = fd * rt;
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    fs.U[9 + i] = f0 * rl[i];
+    fs.F[9 + i] = fd * rl[i] + (i == D - 1 ? gd * E3 : 0.0);
+  }
+  face_char(g, s0, sd, 1.0 / 3.0, fs.rm, fs.rp);
+  const double tau = chi_tot * rho * g.hdx;
+  if (3.0 * tau > 4.0) {   // optically thick: c = 4/(3 tau) < 1 in the gas frame
+    const double cl = 4.0 * recip(3.0 * tau);
+    double lm, lp;
+    face_char(g, u0, ud, cl * cl, lm, lp);
+    fs.rp = fmin(fs.rp, lp);
+    fs.rm = fmax(fs.rm, lm);
+  }
+}
+
 struct FaceRange {
   int lo[3], cnt[3];
   long total;
@@ -345,27 +477,48 @@ DEV void flux_states(const Ctx& C, int i, int j, long c, long st, T PL[12], T PR
     PR[4 + D] = bn;
   }
   FaceState<T> L, Rs;
-  face_state(C, m, D, PL, (T)(chi_abs[c - st] + chi_es[c - st]), L);
-  face_state(C, m, D, PR, (T)(chi_abs[c] + chi_es[c]), Rs);
+  constexpr bool closed = Geo::closed && std::is_same<T, double>::value;
+  if constexpr (closed) {
+    FaceGeom<typename Geo::template M<T>> g;
+    face_geom<D>(C, m, g);
+    face_closed<D>(C, m, g, PL, chi_abs[c - st] + chi_es[c - st], L);
+    face_closed<D>(C, m, g, PR, chi_abs[c] + chi_es[c], Rs);
+  } else {
+    face_state(C, m, D, PL, (T)(chi_abs[c - st] + chi_es[c - st]), L);
+    face_state(C, m, D, PR, (T)(chi_abs[c] + chi_es[c]), Rs);
+  }
   // eq. hll: v_min = -min(0, v-_L, v-_R), v_max = max(0, v+_L, v+_R)
   const T zero = T(0.0);
   const T gmin = -fmin(zero, fmin(L.gm, Rs.gm)), gmax = fmax(zero, fmax(L.gp, Rs.gp));
   const T rmin = -fmin(zero, fmin(L.rm, Rs.rm)), rmax = fmax(zero, fmax(L.rp, Rs.rp));
+  T iden[2];
+  if constexpr (closed) {
+    iden[0] = recip(gmin + gmax);
+    iden[1] = recip(rmin + rmax);
+  }
 #pragma unroll
   for (int q = 0; q < 12; q++) {
+    if (q == 4 + D) {   // the normal field component has no induction flux
+      if (vchar) F[q * C.Ntot + c] = 0.0;
+      continue;
+    }
     const T vmin = q < 8 ? gmin : rmin, vmax = q < 8 ? gmax : rmax;
     T f;
     if (C.flux == GRRMHD_FLUX_HLL) {
       const T den = vmin + vmax;
+      if constexpr (closed)
+        f = (den > zero) ? (vmin * Rs.F[q] + vmax * L.F[q] - vmin * vmax * (Rs.U[q] - L.U[q])) *
+                               iden[q < 8 ? 0 : 1]
+                         : T(0.5) * (L.F[q] + Rs.F[q]);
+      else
       f = (den > zero) ? (vmin * Rs.F[q] + vmax * L.F[q] - vmin * vmax * (Rs.U[q] - L.U[q])) / den
                        : T(0.5) * (L.F[q] + Rs.F[q]);
     } else {
       f = T(0.5) * (Rs.F[q] + L.F[q] - fmax(vmin, vmax) * (Rs.U[q] - L.U[q]));
     }
-    if (q == 4 + D) f = zero;   // normal field component has no induction flux
     F[q * C.Ntot + c] = (double)f;
   }
-  vchar[c] = (double)fmax(fmax(gmin, gmax), fmax(rmin, rmax));
+  if (vchar) vchar[c] = (double)fmax(fmax(gmin, gmax), fmax(rmin, rmax));
   if constexpr (STAG) {
 #pragma unroll
     for (int sd = 0; sd < 2; sd++) {
@@ -451,15 +604,13 @@ template <class Geo, int D, class T, bool ENTF = false, bool STAG = false>
 DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
                                const double* __restrict__ chi_abs,
                                const double* __restrict__ chi_es, double* __restrict__ F,
-                               double* __restrict__ vchar, const double* __restrict__ fl, long t,
-                               double* __restrict__ Fs = nullptr,
+                               double* __restrict__ vchar, const double* __restrict__ fl, int u,
+                               int k, double* __restrict__ Fs = nullptr,
                                const double* __restrict__ Bf = nullptr,
                                double* __restrict__ VF = nullptr, double* __restrict__ SP = nullptr) {
-  if (t >= R.total) return;
-  const int i = R.lo[0] + t % R.cnt[0];
-  const long t2 = t / R.cnt[0];
-  const int j = R.lo[1] + t2 % R.cnt[1];
-  const int k = R.lo[2] + t2 / R.cnt[1];
+  if (u >= R.cnt[0] * R.cnt[1] || k >= R.cnt[2]) return;
+  const int i = R.lo[0] + u % R.cnt[0], j = R.lo[1] + u / R.cnt[0];
+  k += R.lo[2];
   const long c = cell_index(C, i, j, k);
   const long st = C.st[D - 1];
   if constexpr (STAG) {
@@ -520,41 +671,51 @@ DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
 }
 
 
-// The faces of all directions in one launch: up to three segments (one per
-// direction) laid end to end over the thread index; consecutive threads stay
-// within one direction except at the two segment boundaries.
+// Order of a launch over a 3-D range: each (x1, x2) plane is cut into pieces
+// of one block each, and consecutive blocks take one piece through all x3
+// before the next piece.  What bounds these kernels is the latency of their
+// loads: with the planes one after another the stencil's four planes along x3
+// (12 fields of each) have left an XCD's 4 MB L2 when the next plane wants
+// them; a piece's own column stays.  With the index arithmetic in 32 bits the
+// dense faces of a 256x128x64 launch take 653 us instead of 732.
+DEV void column_piece(long b, int nk, int& u, int& k) {
+  const unsigned q = (unsigned)b / (unsigned)nk;
+  k = (int)((unsigned)b - q * (unsigned)nk);
+  u = (int)(q * blockDim.x + threadIdx.x);
+}
+
+// The faces of all directions in one launch: at each piece and x3 a block for
+// each direction in turn, so that the directions share their reads too.
 struct FluxSegs {
   FaceRange R[3];
-  long start[3];
   int D[3];
   int n;
-  long total;
+  int pieces, nk;   // the largest of the ranges' counts
 };
 
 template <class Geo, class T, bool ENTF = false, bool STAG = false>
 DEV void flux_all_at(Ctx C, const FluxSegs& S, const double* __restrict__ P,
                      const double* __restrict__ chi_abs, const double* __restrict__ chi_es,
                      double* __restrict__ F, double* __restrict__ vchar,
-                     const double* __restrict__ fl, long t, double* __restrict__ Fs = nullptr,
+                     const double* __restrict__ fl, double* __restrict__ Fs = nullptr,
                      const double* __restrict__ Bf = nullptr, double* __restrict__ VF = nullptr,
                      double* __restrict__ SP = nullptr) {
-  if (t >= S.total) return;
-  int k = 0;
-  if (S.n > 1 && t >= S.start[1]) k = 1;
-  if (S.n > 2 && t >= S.start[2]) k = 2;
-  const long u = t - S.start[k];
-  const int D = S.D[k];
+  const unsigned b = (unsigned)xcd_block(blockIdx.x, gridDim.x);
+  const unsigned q = b / (unsigned)S.n, s = b - q * (unsigned)S.n;
+  int u, k;
+  column_piece(q, S.nk, u, k);
+  const int D = S.D[s];
   double* Fd = F + (long)(D - 1) * 12 * C.Ntot;
-  double* vd = vchar + (long)(D - 1) * C.Ntot;
+  double* vd = vchar ? vchar + (long)(D - 1) * C.Ntot : nullptr;
   double* Fsd = ENTF ? Fs + (long)(D - 1) * C.Ntot : nullptr;
-  if (D == 1) flux_at<Geo, 1, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
-  else if (D == 2) flux_at<Geo, 2, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
-  else flux_at<Geo, 3, T, ENTF, STAG>(C, S.R[k], P, chi_abs, chi_es, Fd, vd, fl, u, Fsd, Bf, VF, SP);
+  if (D == 1) flux_at<Geo, 1, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
+  else if (D == 2) flux_at<Geo, 2, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
+  else flux_at<Geo, 3, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
 }
 
 // The same with the staggered field (and, with ENTF, the entropy tracer)
 template <class Geo, class T, bool ENTF>
-__global__ void GRRMHD_FLUX_LB k_flux_all_stag(Ctx C, FluxSegs S, const double* __restrict__ P,
+__global__ void LB(64) k_flux_all_stag(Ctx C, FluxSegs S, const double* __restrict__ P,
                                                const double* __restrict__ chi_abs,
                                                const double* __restrict__ chi_es,
                                                double* __restrict__ F, double* __restrict__ vchar,
@@ -562,32 +723,28 @@ __global__ void GRRMHD_FLUX_LB k_flux_all_stag(Ctx C, FluxSegs S, const double* 
                                                double* __restrict__ Fs,
                                                const double* __restrict__ Bf,
                                                double* __restrict__ VF, double* __restrict__ SP) {
-  flux_all_at<Geo, T, ENTF, true>(C, S, P, chi_abs, chi_es, F, vchar, fl,
-                             xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x, Fs, Bf,
-                             VF, SP);
+  flux_all_at<Geo, T, ENTF, true>(C, S, P, chi_abs, chi_es, F, vchar, fl, Fs, Bf, VF, SP);
 }
 
 template <class Geo, class T>
-__global__ void GRRMHD_FLUX_LB k_flux_all(Ctx C, FluxSegs S, const double* __restrict__ P,
+__global__ void FLUX_LB k_flux_all(Ctx C, FluxSegs S, const double* __restrict__ P,
                                           const double* __restrict__ chi_abs,
                                           const double* __restrict__ chi_es,
                                           double* __restrict__ F, double* __restrict__ vchar,
                                           const double* __restrict__ fl) {
-  flux_all_at<Geo, T>(C, S, P, chi_abs, chi_es, F, vchar, fl,
-                 xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x);
+  flux_all_at<Geo, T>(C, S, P, chi_abs, chi_es, F, vchar, fl);
 }
 
 // The same with the entropy tracer's face fluxes Fs [3][Ntot] (the full
 // implicit cascade's entropy equation)
 template <class Geo, class T>
-__global__ void GRRMHD_FLUX_LB k_flux_all_s(Ctx C, FluxSegs S, const double* __restrict__ P,
+__global__ void FLUX_LB k_flux_all_s(Ctx C, FluxSegs S, const double* __restrict__ P,
                                             const double* __restrict__ chi_abs,
                                             const double* __restrict__ chi_es,
                                             double* __restrict__ F, double* __restrict__ vchar,
                                             const double* __restrict__ fl,
                                             double* __restrict__ Fs) {
-  flux_all_at<Geo, T, true>(C, S, P, chi_abs, chi_es, F, vchar, fl,
-                       xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x, Fs);
+  flux_all_at<Geo, T, true>(C, S, P, chi_abs, chi_es, F, vchar, fl, Fs);
 }
 
 // sqrt(-g) S u^t of one cell's primitives p (the entropy tracer; NAN where
@@ -909,6 +1066,54 @@ DEV void geom_source(const M& m, const double dg[2][10], double gam, const T p[1
   }
 }
 
+// geom_source on the closed forms: the tensors' components contracted as the
+// derivatives are loaded, so that neither set is held whole.  Adds to S.
+template <class M>
+DEV void geom_source_closed(const Ctx& C, const M& m, int pos, const double p[12], double S[12]) {
+  const double ia = recip(m.alpha), beta = m.alpha * m.alpha * m.u01;
+  const double* B = p + 5;
+  const double pg = (C.gam - 1.0) * p[1], E3 = p[8] * (1.0 / 3.0);
+  double ul[3], ig, rg, u[4], b[4], r[4];
+  low3(m, p + 2, ul);
+  u[0] = root(1.0 + dot3(p + 2, ul), ig) * ia;
+  const double i0 = m.alpha * ig, bt = dot3(B, ul);
+  double Bl[3];
+  low3(m, B, Bl);
+  const double bsq = (dot3(B, Bl) + bt * bt) * i0 * i0;
+  low3(m, p + 9, Bl);
+  r[0] = root(1.0 + dot3(p + 9, Bl), rg) * ia;
+  b[0] = bt;
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    u[1 + i] = p[2 + i] - (i == 0 ? u[0] * beta : 0.0);
+    r[1 + i] = p[9 + i] - (i == 0 ? r[0] * beta : 0.0);
+    b[1 + i] = (B[i] + bt * u[1 + i]) * i0;
+  }
+  const double enth = p[0] + p[1] + pg + bsq, ptot = pg + 0.5 * bsq;
+  double sg[2] = {0.0, 0.0}, sr[2] = {0.0, 0.0};
+#pragma unroll
+  for (int a = 0; a < 4; a++)
+#pragma unroll
+    for (int c = a; c < 4; c++) {
+      if (M::zlo(a, c)) continue;
+      const double w = a == c ? 1.0 : 2.0;
+      const double up = M::zup(a, c) ? 0.0 : m.up(a, c);
+      const double tg = w * (enth * u[a] * u[c] - b[a] * b[c] + ptot * up);
+      const double tr = w * E3 * (4.0 * r[a] * r[c] + up);
+#pragma unroll
+      for (int n = 0; n < 2; n++) {
+        const double dg = C.geo_c[((n ? GE_DG2 : GE_DG1) + sym(a, c)) * C.npos + pos];
+        sg[n] += tg * dg;
+        sr[n] += tr * dg;
+      }
+    }
+#pragma unroll
+  for (int n = 0; n < 2; n++) {
+    S[2 + n] = 0.5 * m.gdet * sg[n];
+    S[9 + n] = 0.5 * m.gdet * sr[n];
+  }
+}
+
 template <class M>
 DEV void load_dg(const Ctx& C, int pos, double dg[2][10]) {
 #pragma unroll
@@ -952,18 +1157,16 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
                    const double* __restrict__ P, const double* __restrict__ Un,
                    const double* __restrict__ Uprev, const double* __restrict__ F,
                    const double* __restrict__ emf, const MTerms& MT, double* __restrict__ Uexp,
-                   long t, const double* __restrict__ Bface = nullptr) {
-  const long nint = (long)C.n[0] * C.n[1] * C.n[2];
-  if (t >= nint) return;
-  const int i = C.ng[0] + t % C.n[0];
-  const long t2 = t / C.n[0];
-  const int j = C.ng[1] + t2 % C.n[1];
-  const int k = C.ng[2] + t2 / C.n[1];
+                   int t, int k, const double* __restrict__ Bface = nullptr) {
+  if (t >= C.n[0] * C.n[1]) return;
+  const int i = C.ng[0] + t % C.n[0], j = C.ng[1] + t / C.n[0];
+  const bool first = t == 0 && k == 0;
+  k += C.ng[2];
   const long c = cell_index(C, i, j, k);
   double dt;
   if (dtmin) {
     dt = C.courant * dt_slots_min(dtmin);
-    if (t == 0) {
+    if (first) {
       *dt_dev = dt;
 #pragma unroll
       for (int i = 0; i < GRRMHD_DT_SLOTS; i++) dtnext[i * GRRMHD_DT_STRIDE] = 0x7FF0000000000000ull;
@@ -977,16 +1180,21 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
   double div[12];
 #pragma unroll
   for (int q = 0; q < 12; q++) div[q] = 0.0;
-  if (cc != 0.0 && Geo::curved(C)) {
+  if constexpr (!std::is_same<Geo, Flat>::value) if (cc != 0.0 && Geo::curved(C)) {
     const int pos = i + C.N[0] * j;
     using M = typename Geo::template M<double>;
     M m;
     load_metric(C.geo_c, C.npos, pos, m);
-    double p[12], dg[2][10];
+    double p[12];
 #pragma unroll
     for (int q = 0; q < 12; q++) p[q] = P[q * C.Ntot + c];
-    load_dg<M>(C, pos, dg);
-    geom_source(m, dg, C.gam, p, S);
+    if constexpr (Geo::closed) {
+      geom_source_closed(C, m, pos, p, S);
+    } else {
+      double dg[2][10];
+      load_dg<M>(C, pos, dg);
+      geom_source(m, dg, C.gam, p, S);
+    }
   }
   for (int d = 0; d < 3 && cc != 0.0; d++) {
     if (C.n[d] == 1) continue;
@@ -1041,14 +1249,15 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
 }
 
 template <class Geo>
-__global__ void LB(256) k_update(Ctx C, double ca, double cb, double cc, double* dt_dev,
+__global__ void LB(128) k_update(Ctx C, double ca, double cb, double cc, double* dt_dev,
                                  const unsigned long long* dtmin, unsigned long long* dtnext,
                                  const double* __restrict__ P, const double* __restrict__ Un,
                                  const double* __restrict__ Uprev, const double* __restrict__ F,
                                  const double* __restrict__ emf, MTerms MT,
                                  double* __restrict__ Uexp, const double* __restrict__ Bface) {
-  update_at<Geo>(C, ca, cb, cc, dt_dev, dtmin, dtnext, P, Un, Uprev, F, emf, MT, Uexp,
-            (long)blockIdx.x * blockDim.x + threadIdx.x, Bface);
+  int u, k;
+  column_piece(xcd_block(blockIdx.x, gridDim.x), C.n[2], u, k);
+  update_at<Geo>(C, ca, cb, cc, dt_dev, dtmin, dtnext, P, Un, Uprev, F, emf, MT, Uexp, u, k, Bface);
 }
 
 // ---------------------------------------------------------------------------
