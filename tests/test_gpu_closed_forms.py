@@ -129,3 +129,22 @@ def test_implicit(G, orc, n, kind):
     assert field_err(Pg, Pr, good).max() < tol[0], (field_err(Pg, Pr, good), tol)
     assert field_err(Ug, Ur, good).max() < tol[1], (field_err(Ug, Ur, good), tol)
     g.close()
+
+
+@pytest.mark.parametrize("n", [(7, 4, 1), (97, 13, 6)], ids=_name)
+def test_lane_statistics(G, orc, n):
+    """Launches of fewer and of more tiles than the statistics have slots: the
+    totals are the cells' own trip counts."""
+    say("case", n, "lane statistics")
+    pd, P, ca, ce = I.accretion_disk(n=n, seed=3)
+    P = orc.bc(pd, P)
+    g = G.Grid(pd)
+    U = g.prim_to_cons(dev(P))
+    for launches in (1, 2):
+        _, _, it, st, _ = g.implicit(U, dev(P), 1.0, dev(np.array([1e-3])), dev(ca), dev(ce))
+        trips, slots, rest = g.implicit_stats()
+        m = interior_mask(pd)
+        assert rest == 0 and np.all(host(st)[m] == G.ST_PMHD)
+        assert trips == launches * (host(it)[m] + 1).sum()
+        assert trips <= slots <= launches * 64 * (host(it)[m] + 1).sum() and slots % 64 == 0
+    g.close()
