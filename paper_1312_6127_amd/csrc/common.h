@@ -159,19 +159,22 @@ struct KSMetric {
 
 // What a kernel is compiled for.
 struct KS {
-  static constexpr bool closed = true;
+  static constexpr bool closed = true, closed_faces = true;
   DEV static constexpr bool curved(const Ctx&) { return true; }
   template <class R>
   using M = KSMetric<R>;
 };
 struct Flat {
-  static constexpr bool closed = true;
+  // Faces keep face_state's order of operations: 200 steps of a shock tube
+  // amplify a face's last bit to 1e-10 of a field, and its 9 us launches are
+  // latency, not arithmetic
+  static constexpr bool closed = true, closed_faces = false;
   DEV static constexpr bool curved(const Ctx&) { return false; }
   template <class R>
   using M = FlatMetric<R>;
 };
 struct Dense {
-  static constexpr bool closed = false;   // the closed forms of pointwise.h don't apply
+  static constexpr bool closed = false, closed_faces = false;   // no closed forms
   DEV static bool curved(const Ctx& C) { return C.metric == GRRMHD_KERR_SCHILD; }
   template <class R>
   using M = DenseMetric<R>;

@@ -9,7 +9,7 @@
 // of the stencil spill, and a 128x64x32 launch takes 57 us (at the two that
 // 174 registers allow: 65; at four, 188 bytes: 101).  The staggered faces,
 // with more to hold, gain nothing from the third (34 and 35 us at 80x50x20).
-#define FLUX_LB __launch_bounds__(64, Geo::closed ? 3 : 1)
+#define FLUX_LB __launch_bounds__(64, Geo::closed_faces ? 3 : 1)
 
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup b to XCD b mod 8)
 // and each XCD has its own L2.  This maps b to a work index so that each XCD
@@ -299,7 +299,7 @@ DEV void face_state(const Ctx& C, const M& m, int d, const T* P,
   face_speeds(C, m, d, P, chi_tot, s, r, fs.gm, fs.gp, fs.rm, fs.rp);
 }
 
-// face_state on the closed forms of pointwise.h, FP64 on a sparse metric:
+// face_state on the closed forms of pointwise.h, FP64 on Kerr-Schild:
 // the same state, fluxes and speeds, with the terms that depend on the face
 // alone (FaceGeom) formed once for its two states.  face_state's 32 divisions
 // and 14 square roots per face are half its issue cycles; here 10 reciprocals
@@ -314,23 +314,13 @@ struct FaceGeom {
 };
 template <int D, class M>
 DEV void face_geom(const Ctx& C, const M& m, FaceGeom<M>& g) {
-  if constexpr (M::diagonal) {
-    g.ia = 1.0;
-    g.beta = 0.0;
-    g.ugg = -1.0;
-    g.udd = 1.0;
-    g.u0d = 0.0;
-    g.k = 1.0;
-    g.hdx = C.dx[D - 1];
-  } else {
-    g.ia = recip(m.alpha);
-    g.beta = m.alpha * m.alpha * m.u01;
-    g.ugg = m.u00;
-    g.udd = m.up(D, D);
-    g.u0d = D == 1 ? m.u01 : 0.0;
-    g.k = g.u0d * g.u0d - m.u00 * g.udd;
-    g.hdx = root0(m.lo(D, D)) * C.dx[D - 1];
-  }
+  g.ia = recip(m.alpha);
+  g.beta = m.alpha * m.alpha * m.u01;
+  g.ugg = m.u00;
+  g.udd = m.up(D, D);
+  g.u0d = D == 1 ? m.u01 : 0.0;
+  g.k = g.u0d * g.u0d - m.u00 * g.udd;
+  g.hdx = root0(m.lo(D, D)) * C.dx[D - 1];
 }
 
 // char_speeds: u0, ud the frame's u^t and u^D
@@ -353,20 +343,12 @@ DEV double face_vel(const M& m, const FaceGeom<M>& g, const double ut[3], double
   q = dot3(ut, ul);
   double ig;
   const double gam = root(1.0 + q, ig);
-  if constexpr (M::diagonal) {
-    u0 = gam;
-    i0 = ig;
-    ut_ = -gam;
-#pragma unroll
-    for (int i = 0; i < 3; i++) uc[i] = ut[i];
-  } else {
-    u0 = gam * g.ia;
-    i0 = m.alpha * ig;
-    uc[0] = ut[0] - u0 * g.beta;
-    uc[1] = ut[1];
-    uc[2] = ut[2];
-    ut_ = g.beta * ul[0] - m.alpha * gam;
-  }
+  u0 = gam * g.ia;
+  i0 = m.alpha * ig;
+  uc[0] = ut[0] - u0 * g.beta;
+  uc[1] = ut[1];
+  uc[2] = ut[2];
+  ut_ = g.beta * ul[0] - m.alpha * gam;
   return gam;
 }
 
@@ -377,9 +359,7 @@ DEV void face_closed(const Ctx& C, const M& m, const FaceGeom<M>& g, const doubl
   const double rho = P[0], ug = P[1], pg = (C.gam - 1.0) * ug, gd = m.gdet;
   double ul[3], uc[3], q, u0, i0, ut;
   const double gam = face_vel(m, g, P + 2, ul, q, u0, i0, uc, ut);
-  double opu;
-  if constexpr (M::diagonal) opu = -q * recip(1.0 + gam);
-  else opu = (1.0 - m.alpha) - m.alpha * q * recip(1.0 + gam) + g.beta * ul[0];
+  const double opu = (1.0 - m.alpha) - m.alpha * q * recip(1.0 + gam) + g.beta * ul[0];
   double Bl[3];
   low3(m, B, Bl);
   const double bt = dot3(B, ul);
@@ -390,7 +370,7 @@ DEV void face_closed(const Ctx& C, const M& m, const FaceGeom<M>& g, const doubl
     bc[i] = (B[i] + bt * uc[i]) * i0;
     bl[i] = (Bl[i] + bt * ul[i]) * i0;
   }
-  const double b0 = M::diagonal ? bt * ut * i0 : (g.beta * Bl[0] + bt * ut) * i0;
+  const double b0 = (g.beta * Bl[0] + bt * ut) * i0;
   const double w = rho + ug + pg, enth = w + bsq, ptot = pg + 0.5 * bsq;
   const double hm = ug + pg + bsq;
   const double ud = uc[D - 1], bd = bc[D - 1], r0 = rho * u0, rd = rho * ud;
@@ -477,7 +457,7 @@ DEV void flux_states(const Ctx& C, int i, int j, long c, long st, T PL[12], T PR
     PR[4 + D] = bn;
   }
   FaceState<T> L, Rs;
-  constexpr bool closed = Geo::closed && std::is_same<T, double>::value;
+  constexpr bool closed = Geo::closed_faces && std::is_same<T, double>::value;
   if constexpr (closed) {
     FaceGeom<typename Geo::template M<T>> g;
     face_geom<D>(C, m, g);
