@@ -57,6 +57,7 @@ static void cascade_layout(char* base, size_t cap, Work& W) {
   W.rec.d = (double*)(base + round256(sizeof(int) * cap));
   W.rec.i = (int*)(base + round256(sizeof(int) * cap) + round256(sizeof(double) * 13 * cap));
   W.rec.cap = (long)cap;
+  W.rec.x = nullptr;
 }
 
 static thread_local std::string g_err;
@@ -2015,7 +2016,7 @@ extern "C" int grrmhd_step_adjoint_saved(grrmhd_grid* g, const double* chi_abs,
 // workspace of the per-cell batched form: counters and statistics, cascade
 // list with first-attempt records, deferred-cell and cold-cell lists
 static constexpr size_t batch_ws_bytes(size_t n) {
-  return 256 + cascade_bytes(n) + 2 * round256(sizeof(int) * n);
+  return 256 + cascade_bytes(n) + round256(sizeof(double) * 4 * n) + 2 * round256(sizeof(int) * n);
 }
 
 extern "C" size_t grrmhd_implicit_source_workspace_bytes_ex(long n, int mode) {
@@ -2066,10 +2067,11 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   int* cursor = W.counter + 4;        // cascade queue cursor
   W.stats = (unsigned long long*)(base + 64);
   cascade_layout(base + 256, (size_t)n, W);
-  // deferred (extreme) cells of the cascade
+  W.rec.x = (double*)(base + 256 + cascade_bytes((size_t)n));
+  // extreme cells of the cascade
   Work D = W;
   D.counter = W.counter + 5;
-  D.list = (int*)(base + 256 + cascade_bytes((size_t)n));
+  D.list = (int*)((char*)W.rec.x + round256(sizeof(double) * 4 * (size_t)n));
   // cells the cascade leaves without an energy solution, for the cold limit
   Work K = W;
   K.counter = W.counter + 6;
@@ -2087,13 +2089,13 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
   if (mode == GRRMHD_IMPLICIT_PER_CELL) {
     hipLaunchKernelGGL(k_implicit_batch<Dense>, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
-                       dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W);
+                       dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, D);
     LAUNCHCHK();
   } else if (mode == GRRMHD_IMPLICIT_PERSISTENT) {
     const long waves = (long)ncu * waves_per_cu;
     const long blocks = std::max<long>(1, std::min<long>(waves * 64 / block, nblocks(n, block)));
     hipLaunchKernelGGL(k_implicit_persist<Dense>, dim3((unsigned)blocks), dim3(block), 0, s, C, n, U_expl,
-                       P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, next, W);
+                       P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, next, W, D);
     LAUNCHCHK();
   } else {
     const size_t qb = round256(sizeof(int) * (size_t)n);
@@ -2102,7 +2104,7 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
     double* sd = (double*)(extra + 2 * qb);
     int* si = (int*)(extra + 2 * qb + round256(sizeof(double) * LS_ND * (size_t)n));
     hipLaunchKernelGGL(k_iter_start<Dense>, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
-                       dt_cell, chi_abs, chi_es, sd, si, qc, q0, W);
+                       dt_cell, chi_abs, chi_es, sd, si, qc, q0, W, D);
     LAUNCHCHK();
     // every attempt ends within max_iter trips (+3 round-off trips are inside it)
     for (int t = 0; t <= C.max_iter; t++) {
@@ -2118,16 +2120,21 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
       LAUNCHCHK();
     }
   }
-  // the rest of the cascade: URAD attempts in a compacting persistent grid
-  // (one wavefront per SIMD: the kernel holds ~470 registers per lane), then
-  // the deferred extreme cells one thread each
-  const long cwaves = std::max<long>(1, std::min<long>(4L * ncu, nblocks(n, 64)));
+  // the rest of the cascade: the extreme cells and the URAD attempts in a
+  // compacting persistent grid (one wavefront per SIMD: the kernel holds ~470
+  // registers per lane), then the outputs
+  const long cwaves = std::max<long>(1, std::min<long>(4L * ncu, n));
   hipLaunchKernelGGL(k_cascade_urad<Dense>, dim3((unsigned)cwaves), dim3(64), 0, s, C, n, U_expl, P_guess,
                      dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, cursor, D, K);
   LAUNCHCHK();
-  hipLaunchKernelGGL(k_implicit_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
-                     P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, D, K);
+  hipLaunchKernelGGL(k_cascade_finish<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
+                     P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, K);
   LAUNCHCHK();
+  if (C.cascade) {
+    hipLaunchKernelGGL(k_implicit_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
+                       P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, D);
+    LAUNCHCHK();
+  }
   // the full cascade's rest for the cells the PMHD and URAD attempts left
   // unaccepted (K holds their record slots), the cold limit inline
   if (C.cascade) {
@@ -2136,7 +2143,7 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
     LAUNCHCHK();
   } else if (C.cold && C.u_floor > 0.0) {
     // cells with no energy solution: the cold MHD limit, one thread each
-    hipLaunchKernelGGL(k_cold_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
+    hipLaunchKernelGGL(k_cold_batch_list<Dense>, dim3((unsigned)cwaves), dim3(64), 0, s, C, n, U_expl,
                        P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, K);
     LAUNCHCHK();
   }

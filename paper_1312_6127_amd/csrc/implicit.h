@@ -318,9 +318,10 @@ DEV void eval_urad(const CellT<M>& c, const Phys& ph, const double x[4], const d
 // URAD residual and its exact Jacobian dE_rad/dx in one dual-number pass:
 // the same steps as eval_urad, the gas inversion differentiated by the
 // implicit-function theorem (mhd_invert_dual).  Values equal eval_urad's.
+// root: of the gas inversion, if it is known.
 template <bool ENT = false, class M>
 DEV void eval_urad_jac(const CellT<M>& c, const Phys& ph, const double x[4], const double Pgas[5],
-                       Eval& e, double J[4][4]) {
+                       Eval& e, double J[4][4], const double* root = nullptr) {
   using D = Dual<4>;
   e.ok = 1;
   D xd[4];
@@ -333,7 +334,7 @@ DEV void eval_urad_jac(const CellT<M>& c, const Phys& ph, const double x[4], con
                    c.Tgi[3] - (xd[3] - c.Ri[3])};
   const D Eg = c.Tgi[0] - (xd[0] - c.Ri[0]);
   D rho, ug, ut[3];
-  if (mhd_invert_dual<4>(c.m, ph.gam, c.rhout, Eg, Tt, c.B, Pgas[1], Pgas + 2, rho, ug, ut)) {
+  if (mhd_invert_dual<4>(c.m, ph.gam, c.rhout, Eg, Tt, c.B, Pgas[1], Pgas + 2, rho, ug, ut, root)) {
     e.ok = 0;
     e.eT = INFINITY;
     return;
@@ -1007,18 +1008,23 @@ DEV void cold_fallback(const M& m, const Phys& ph, const Opts& o, const double U
 
 // Result of a cell's first PMHD attempt, kept per cascade-list slot so that
 // the cascade resumes where the first attempt ended: field-major [f][cap],
-// d = P[12], e_T; i = radiation flags, ok, iterations.
+// d = P[12], e_T; i = radiation flags (and the cell's status bits from
+// REC_STATUS up), ok (REC_EXTREME: no attempt was made), iterations.  A batch
+// keeps its URAD attempts' results there too (ok: 1 | method << 1), with their
+// iterates in x.
 struct RecBuf {
   double* d;
   int* i;
   long cap;
+  double* x;   // [4][cap], batches alone
 };
+enum { REC_STATUS = 8, REC_EXTREME = -1 };
 
-DEV void rec_store(const RecBuf& R, long slot, const Best& b, int iters) {
+DEV void rec_store(const RecBuf& R, long slot, const Best& b, int iters, int status = 0) {
 #pragma unroll
   for (int q = 0; q < 12; q++) R.d[q * R.cap + slot] = b.P[q];
   R.d[12 * R.cap + slot] = b.eT;
-  R.i[slot] = b.radflags;
+  R.i[slot] = b.radflags | status << REC_STATUS;
   R.i[R.cap + slot] = b.ok;
   R.i[2 * R.cap + slot] = iters;
 }
@@ -1029,7 +1035,7 @@ DEV void rec_load(const RecBuf& R, long slot, Best& b, int& iters) {
 #pragma unroll
   for (int q = 0; q < 12; q++) b.P[q] = R.d[q * R.cap + slot];
   b.eT = R.d[12 * R.cap + slot];
-  b.radflags = R.i[slot];
+  b.radflags = R.i[slot] & ((1 << REC_STATUS) - 1);
   b.ok = R.i[R.cap + slot];
   iters = R.i[2 * R.cap + slot];
 }
@@ -1049,6 +1055,7 @@ DEV bool implicit_fast(const M& m, const Phys& ph, const Opts& o, const double U
   iters = 0;
   trips = 0;
   extreme = pr.extreme;
+  out.status = pr.status;
   if (pr.extreme) return false;
   const double x0[4] = {pr.Pthin[1], pr.Pthin[2], pr.Pthin[3], pr.Pthin[4]};
   newton<M_PMHD>(c, ph, o, x0, pr.Pthin, b, iters);
@@ -1543,6 +1550,9 @@ DEV void lane_start(const Eval& ev, Lane& L) {
 // are those of newton<M_URAD>.
 // ---------------------------------------------------------------------------
 enum { UM_START = 0, UM_STEP = 1, UM_BACK = 2 };
+// a lane's place within an evaluation: none under way; the gas inversion's
+// Newton iteration; waiting for its bisection; its root known; without one
+enum { UE_NONE = 0, UE_NEWTON, UE_BISECT, UE_ROOT, UE_FAILED };
 
 struct UradLane {
   double x[4], p[4];     // iterate; point of this trip's evaluation
@@ -1594,6 +1604,21 @@ DEV void urad_take(const Eval& ev, const double Jn[4][4], UradLane& L) {
 #pragma unroll
   for (int q = 0; q < 5; q++) L.Pn[q] = ev.P[q];
   L.eT = ev.eT;
+}
+
+// The gas inversion of eval_urad_jac at x, by itself
+template <class M>
+DEV MhdC urad_gas(const CellT<M>& c, const Phys& ph, const double x[4]) {
+  using D = Dual<4>;
+  D xd[4];
+#pragma unroll
+  for (int k = 0; k < 4; k++) xd[k] = D::var(x[k], k);
+  const D Tt[3] = {c.Tgi[1] - (xd[1] - c.Ri[1]), c.Tgi[2] - (xd[2] - c.Ri[2]),
+                   c.Tgi[3] - (xd[3] - c.Ri[3])};
+  const D Eg = c.Tgi[0] - (xd[0] - c.Ri[0]);
+  MhdCT<D> cd;
+  mhd_consts(c.m, ph.gam, c.rhout, Eg, Tt, c.B, cd);
+  return mhd_values(cd);
 }
 
 // After the evaluation at L.p (true: the attempt ends here).

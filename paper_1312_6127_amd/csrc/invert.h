@@ -227,51 +227,81 @@ DEV void mhd_consts(const M& m, double gam, double rhout, const C& Eg, const C T
 
 // The root W' of eq. EMHD: Newton from the guess primitives (W' = D u~^2/(1+gamma)
 // + chi gamma^2), bracketed bisection when Newton leaves the admissible
-// region or stalls.  0 on success (with chi > 0 at the root), 1 otherwise.
+// region or stalls.  The Newton iteration's state, so that a caller may take
+// it a few steps at a time:
+struct MhdIter {
+  double Wp, dprev;
+  int it, conv;
+  bool ok;   // false: to be bisected
+};
+
+// false: no root
 template <class M>
-DEV int mhd_solve(const M& m, const MhdC& c, double ug_g, const double ut_g[3], double& Wp) {
-  if (!(c.D > 0.0) || !(c.Ep > 0.0) || !isfinite(c.Ep) || !isfinite(c.Qt2)) return 1;
-  {
-    double q = 0.0;
+DEV bool mhd_start(const M& m, const MhdC& c, double ug_g, const double ut_g[3], MhdIter& s) {
+  if (!(c.D > 0.0) || !(c.Ep > 0.0) || !isfinite(c.Ep) || !isfinite(c.Qt2)) return false;
+  double q = 0.0;
 #pragma unroll
-    for (int i = 0; i < 3; i++)
+  for (int i = 0; i < 3; i++)
 #pragma unroll
-      for (int j = 0; j < 3; j++)
-        if (!M::zlo(i + 1, j + 1)) q += m.lo(i + 1, j + 1) * ut_g[i] * ut_g[j];
-    const double g = ::sqrt(1.0 + q);
-    Wp = c.D * q / (1.0 + g) + c.gam * ug_g * (1.0 + q);
-  }
-  bool ok = isfinite(Wp) && Wp > 0.0;
-  int conv = 0;
-  double dprev = INFINITY;
-  if (ok) {
-    for (int it = 0; it < 60; it++) {
+    for (int j = 0; j < 3; j++)
+      if (!M::zlo(i + 1, j + 1)) q += m.lo(i + 1, j + 1) * ut_g[i] * ut_g[j];
+  const double g = ::sqrt(1.0 + q);
+  s.Wp = c.D * q / (1.0 + g) + c.gam * ug_g * (1.0 + q);
+  s.ok = isfinite(s.Wp) && s.Wp > 0.0;
+  s.conv = 0;
+  s.dprev = INFINITY;
+  s.it = 0;
+  return true;
+}
+
+// Up to `steps` Newton steps (WHOLE: all); true when the iteration has ended,
+// with s.ok and chi > 0 or for bisection.
+template <bool WHOLE>
+DEV bool mhd_iterate(const MhdC& c, MhdIter& s, int steps = 0) {
+  if (s.ok) {
+    bool ended = false;
+    for (; (WHOLE || steps-- > 0) && s.it < 60; s.it++) {
       Dual<1> chi, gm;
-      const Dual<1> f = mhd_f<Dual<1>>(c, Dual<1>::var(Wp, 0), chi, gm);
-      if (!(f.d[0] > 0.0) || !isfinite(f.v)) { ok = false; break; }
-      double Wn = Wp - f.v / f.d[0];
+      const Dual<1> f = mhd_f<Dual<1>>(c, Dual<1>::var(s.Wp, 0), chi, gm);
+      if (!(f.d[0] > 0.0) || !isfinite(f.v)) { s.ok = false; break; }
+      double Wn = s.Wp - f.v / f.d[0];
       if (!(Wn > 0.0) || mhd_vsq(c, Wn + c.D) >= 1.0) {
-        Wn = 0.5 * Wp;                                     // stay admissible
-        if (mhd_vsq(c, Wn + c.D) >= 1.0) { ok = false; break; }
+        Wn = 0.5 * s.Wp;                                     // stay admissible
+        if (mhd_vsq(c, Wn + c.D) >= 1.0) { s.ok = false; break; }
       }
-      const double dW = ::fabs(Wn - Wp);
-      Wp = Wn;
-      if (dW <= 2.0 * DBL_EPSILON * Wp) { conv++; if (conv >= 2) break; }
-      else conv = 0;
+      const double dW = ::fabs(Wn - s.Wp);
+      s.Wp = Wn;
+      if (dW <= 2.0 * DBL_EPSILON * s.Wp) {
+        s.conv++;
+        if (s.conv >= 2) { ended = true; break; }
+      } else {
+        s.conv = 0;
+      }
       // at the rounding floor of f: a step already below 1e-12 W' that no
       // longer shrinks is noise of the residual, not progress (a few cells
       // otherwise circle the root for all 60 steps and then bisect)
-      if (conv == 0 && dW <= 1e-12 * Wp && dW >= dprev) break;
-      dprev = dW;
-      if (it == 59) ok = false;
+      if (s.conv == 0 && dW <= 1e-12 * s.Wp && dW >= s.dprev) { ended = true; break; }
+      s.dprev = dW;
+      if (s.it == 59) s.ok = false;
     }
+    if (!WHOLE && s.ok && !ended) return false;
   }
-  if (ok) {
+  if (s.ok) {
     double chi, gm;
-    mhd_f<double>(c, Wp, chi, gm);
-    if (!(chi > 0.0)) ok = false;
+    mhd_f<double>(c, s.Wp, chi, gm);
+    if (!(chi > 0.0)) s.ok = false;
   }
-  if (!ok && mhd_bisect(c, Wp)) return 1;
+  return true;
+}
+
+// 0 on success (with chi > 0 at the root), 1 otherwise
+template <class M>
+DEV int mhd_solve(const M& m, const MhdC& c, double ug_g, const double ut_g[3], double& Wp) {
+  MhdIter s;
+  if (!mhd_start(m, c, ug_g, ut_g, s)) return 1;
+  mhd_iterate<true>(c, s);
+  Wp = s.Wp;
+  if (!s.ok && mhd_bisect(c, Wp)) return 1;
   return 0;
 }
 
@@ -305,14 +335,9 @@ DEV int mhd_invert(const M& m, double gam, double rhout, double Eg, const double
 // The same inversion as a function of upstream unknowns carried by dual
 // numbers: the root W' in double precision, then its derivative from the
 // implicit-function theorem on eq. EMHD, dW' = -(df/dc . dc) / (df/dW'),
-// and the primitives' derivatives through eq. tveq.
-template <int N, class M>
-DEV int mhd_invert_dual(const M& m, double gam, double rhout, const Dual<N>& Eg,
-                        const Dual<N> Tt[3], const double B[3], double ug_g, const double ut_g[3],
-                        Dual<N>& rho, Dual<N>& ug, Dual<N> ut[3]) {
-  using D = Dual<N>;
-  MhdCT<D> cd;
-  mhd_consts(m, gam, rhout, Eg, Tt, B, cd);
+// and the primitives' derivatives through eq. tveq.  root: W' if it is known.
+template <int N>
+DEV MhdC mhd_values(const MhdCT<Dual<N>>& cd) {
   MhdC cv;
   cv.D = cd.D;
   cv.Bsq = cd.Bsq;
@@ -325,8 +350,19 @@ DEV int mhd_invert_dual(const M& m, double gam, double rhout, const Dual<N>& Eg,
     cv.Qt[i] = cd.Qt[i].v;
     cv.Bz[i] = cd.Bz[i];
   }
+  return cv;
+}
+template <int N, class M>
+DEV int mhd_invert_dual(const M& m, double gam, double rhout, const Dual<N>& Eg,
+                        const Dual<N> Tt[3], const double B[3], double ug_g, const double ut_g[3],
+                        Dual<N>& rho, Dual<N>& ug, Dual<N> ut[3], const double* root = nullptr) {
+  using D = Dual<N>;
+  MhdCT<D> cd;
+  mhd_consts(m, gam, rhout, Eg, Tt, B, cd);
+  const MhdC cv = mhd_values(cd);
   double Wp;
-  if (mhd_solve(m, cv, ug_g, ut_g, Wp)) return 1;
+  if (root) Wp = *root;
+  else if (mhd_solve(m, cv, ug_g, ut_g, Wp)) return 1;
   D chi, gm;
   const D f = mhd_f<D>(cd, D(Wp), chi, gm);            // df/dc . dc at fixed W'
   Dual<1> chi1, gm1;

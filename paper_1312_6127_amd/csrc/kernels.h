@@ -1446,9 +1446,22 @@ DEV void store_out(const CellOut& o, long c, long Nst, double* P, double* U, int
 
 // A cell the fast path did not accept: to the work list, with its first
 // attempt (extreme cells have none).
-DEV void to_cascade(bool need, bool extreme, int item, const Best& b, int iters, const Work& W) {
+DEV void to_cascade(bool need, bool extreme, int item, const Best& b, int iters, const Work& W,
+                    int status = 0) {
   const long slot = wave_append(need, item, W.counter, W.list);
-  if (slot >= 0 && !extreme) rec_store(W.rec, slot, b, iters);
+  if (slot >= 0 && !extreme) rec_store(W.rec, slot, b, iters, status);
+}
+
+// The same in a batch: extreme cells to the list D as well, their slots of W
+// marked.
+DEV void to_batch_cascade(bool need, bool extreme, int item, const Best& b, int iters, int status,
+                          const Work& W, const Work& D) {
+  const long slot = wave_append(need, item, W.counter, W.list);
+  if (slot >= 0) {
+    if (extreme) W.rec.i[W.rec.cap + slot] = REC_EXTREME;
+    else rec_store(W.rec, slot, b, iters, status);
+  }
+  wave_append(need && extreme, item, D.counter, D.list);
 }
 
 // Common path of the implicit solve at interior cells; cells that need the
@@ -1564,11 +1577,11 @@ __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ U
                                         const double* __restrict__ chi_es,
                                         double* __restrict__ Po, double* __restrict__ Uo,
                                         int* __restrict__ iters, int* __restrict__ status,
-                                        double* __restrict__ err, Work W) {
+                                        double* __restrict__ err, Work W, Work D) {
   const long c = (long)blockIdx.x * blockDim.x + threadIdx.x;
   bool need = false, extreme = false;
   Best b;
-  int it = 0, trips = 0;
+  int it = 0, trips = 0, st0 = 0;
   if (c < n) {
     Metric m;
     flat_metric(m);
@@ -1584,24 +1597,37 @@ __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ U
       store_out(o, c, n, Po, Uo, iters, status, err);
     else
       need = true;
+    st0 = o.status;
   }
   wave_stats(trips, W.stats);
-  to_cascade(need, extreme, (int)c, b, it, W);
+  to_batch_cascade(need, extreme, (int)c, b, it, st0, W, D);
 }
 
-template <class Geo>
-__global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __restrict__ Ui_,
-                                             const double* __restrict__ Pg_,
-                                             const double* __restrict__ dtc,
-                                             const double* __restrict__ chi_abs,
-                                             const double* __restrict__ chi_es,
-                                             double* __restrict__ Po, double* __restrict__ Uo,
-                                             int* __restrict__ iters, int* __restrict__ status,
-                                             double* __restrict__ err, Work W, Work K) {
-  const int cnt = *W.counter;
-  for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < cnt;
-       w += (long)gridDim.x * blockDim.x) {
-    const long c = W.list[w];
+// A batch's list entries over a grid of wavefronts: a list shorter than the
+// grid in wavefronts of one lane each, which then run that cell's branches
+// alone; a longer one in full wavefronts.  (41 cold cells of a batch of 4099
+// in one wavefront 73 us, in 41 58; 10198 of one of 2^20 in 160 wavefronts
+// 123 us, in 1020 of ten lanes 148, each wavefront fetching the code anew.)
+// This lane's first entry (cnt: none) and the distance to its next.
+DEV long list_first(int cnt, long& step) {
+  const int width = cnt <= (int)gridDim.x ? 1 : 64;
+  step = (long)gridDim.x * width;
+  return (int)threadIdx.x < width ? (long)blockIdx.x * width + threadIdx.x : (long)cnt;
+}
+
+// Extreme cells of a batch (radiation far below the gas: URAD first, then PMHD
+// from scratch), listed in D, one thread each; those left without an energy
+// solution go on to the cold limit's list K.
+DEV void extreme_cells(const Ctx& C, long n, const double* __restrict__ Ui_,
+                       const double* __restrict__ Pg_, const double* __restrict__ dtc,
+                       const double* __restrict__ chi_abs, const double* __restrict__ chi_es,
+                       double* __restrict__ Po, double* __restrict__ Uo, int* __restrict__ iters,
+                       int* __restrict__ status, double* __restrict__ err, const Work& D,
+                       const Work& K) {
+  const int cnt = *D.counter;
+  long step;
+  for (long w = list_first(cnt, step); w < cnt; w += step) {
+    const long c = D.list[w];
     Metric m;
     flat_metric(m);
     double Ui[12], Pg[12];
@@ -1612,15 +1638,7 @@ __global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __rest
     }
     CellOut o;
     const Opts op = make_opts(C);
-    if (C.cascade) {
-      // the full cascade from scratch, the cold limit inline; a cell without
-      // a grid takes the entropy of its prior primitives
-      implicit_cell_full(m, make_phys(C), op, Ui, entropy_cons(C.gam, m, Pg), Pg, dtc[c],
-                         chi_abs[c], chi_es[c], o);
-      store_out(o, c, n, Po, Uo, iters, status, err);
-      continue;
-    }
-    implicit_cell(m, make_phys(C), op, Ui, Pg, dtc[c], chi_abs[c], chi_es[c], o, &W.rec, w, false);
+    implicit_cell(m, make_phys(C), op, Ui, Pg, dtc[c], chi_abs[c], chi_es[c], o, nullptr, 0, false);
     store_out(o, c, n, Po, Uo, iters, status, err);
     bool cold = false;
     if ((o.status & GRRMHD_ST_FAIL) && op.cold) {
@@ -1629,6 +1647,36 @@ __global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __rest
       cold = cold_allowed(cl, Pg);
     }
     wave_append(cold, (int)c, K.counter, K.list);
+  }
+}
+
+// The same with the full cascade (params.cascade = 1), the cold limit inline;
+// a cell without a grid takes the entropy of its prior primitives.
+template <class Geo>
+__global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __restrict__ Ui_,
+                                             const double* __restrict__ Pg_,
+                                             const double* __restrict__ dtc,
+                                             const double* __restrict__ chi_abs,
+                                             const double* __restrict__ chi_es,
+                                             double* __restrict__ Po, double* __restrict__ Uo,
+                                             int* __restrict__ iters, int* __restrict__ status,
+                                             double* __restrict__ err, Work D) {
+  const int cnt = *D.counter;
+  for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < cnt;
+       w += (long)gridDim.x * blockDim.x) {
+    const long c = D.list[w];
+    Metric m;
+    flat_metric(m);
+    double Ui[12], Pg[12];
+#pragma unroll
+    for (int q = 0; q < 12; q++) {
+      Ui[q] = Ui_[q * n + c];
+      Pg[q] = Pg_[q * n + c];
+    }
+    CellOut o;
+    implicit_cell_full(m, make_phys(C), make_opts(C), Ui, entropy_cons(C.gam, m, Pg), Pg, dtc[c],
+                       chi_abs[c], chi_es[c], o);
+    store_out(o, c, n, Po, Uo, iters, status, err);
   }
 }
 
@@ -1646,8 +1694,8 @@ __global__ void LB(64) k_cold_batch_list(Ctx C, long n, const double* __restrict
                                          int* __restrict__ iters, int* __restrict__ status,
                                          double* __restrict__ err, Work K) {
   const int cnt = *K.counter;
-  for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < cnt;
-       w += (long)gridDim.x * blockDim.x) {
+  long step;
+  for (long w = list_first(cnt, step); w < cnt; w += step) {
     const long c = K.list[w];
     Metric m;
     flat_metric(m);
@@ -1701,9 +1749,28 @@ __global__ void LB(64) k_rest_batch_list(Ctx C, long n, const double* __restrict
 // The cascade of a batch, compacting: a fixed grid of wavefronts whose lanes
 // take list entries from a cursor (one atomic per wavefront) and run the URAD
 // attempt as a lane state machine, one residual evaluation per trip, taking
-// the next entry as soon as their cell ends.  Extreme cells (URAD first, then
-// PMHD from scratch) go to the deferred list D for the per-cell cascade.
+// the next entry as soon as their cell ends.  With some five trips to a cell
+// a few lanes begin and end in every trip, and what they do then costs the
+// wavefront as much as if all did it: so a lane only loads its cell and the
+// first attempt's record, and at the end leaves the better attempt there for
+// k_cascade_finish.  (With the cells' set-up, its MHD inversion included, and
+// the outputs in this loop a batch of 2^20 cells took 3085 us here; without
+// them 2482, and 126 in k_cascade_finish.)  Extreme cells come first, one
+// thread each: they take a few wavefronts of this grid while the others are
+// at the list (a launch of their own took 141 us at 4099 cells, 212 at 2^20).
 // Results equal those of implicit_cell resuming from the same record.
+// An evaluation's gas inversion takes a lane 5 Newton steps or, near the edge
+// of the admissible states, up to 60 and a bisection of as many evaluations
+// again, and its wavefront with it.  While there is more of the list than the
+// grid's lanes can hold, a lane has GRRMHD_URAD_STEPS of them in a trip and
+// goes on in the next while the others evaluate, and bisections wait until
+// GRRMHD_URAD_BISECT lanes want one or no lane can do without: 1861 us at 2^20
+// cells (each evaluation in one trip: 2482; 8 steps or 12: 1921, 1908; 8
+// bisections: 2133; 32: 1927).  A shorter list is spread over all wavefronts,
+// a few lanes each, and nothing waits: 306 us at 4099 cells (in full
+// wavefronts 323, waiting 452).
+#define GRRMHD_URAD_STEPS 4
+#define GRRMHD_URAD_BISECT 16
 template <class Geo>
 __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ Ui_,
                                       const double* __restrict__ Pg_,
@@ -1714,6 +1781,8 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
                                       int* __restrict__ iters, int* __restrict__ status,
                                       double* __restrict__ err, Work W, int* cursor, Work D,
                                       Work K) {
+  if (!C.cascade)
+    extreme_cells(C, n, Ui_, Pg_, dtc, chi_abs, chi_es, Po, Uo, iters, status, err, D, K);
   const Phys ph = make_phys(C);
   const Opts o = make_opts(C);
   Metric m;
@@ -1721,105 +1790,167 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
   const int cnt = *W.counter;
   UradLane L;
   Cell c;
-  long item = 0, slot = 0;
-  int pst = 0;
-  bool active = false, exhausted = false;
+  MhdIter in;
+  long slot = 0;
+  int stage = UE_NONE;
+  // wavefronts that had an extreme cell come late
+  const int busy = C.cascade ? 0 : ::min(*D.counter, (int)gridDim.x / 2);
+  const int width = ::min((cnt + (int)gridDim.x - busy - 1) / ((int)gridDim.x - busy), 64);
+  const bool apart = width < 64;
+  const int steps = apart ? 60 : GRRMHD_URAD_STEPS;
+  bool active = false, exhausted = (int)threadIdx.x >= width;
   unsigned long long useful = 0, slots = 0;
   for (;;) {
     const bool need = !active && !exhausted;
     const long got = wave_fetch(need, cursor);
-    bool defer = false;
     if (need) {
-      if (got < cnt) {
-        slot = got;
-        item = W.list[slot];
-        double Ui[12], Pg[12];
-#pragma unroll
-        for (int q = 0; q < 12; q++) {
-          Ui[q] = Ui_[q * n + item];
-          Pg[q] = Pg_[q * n + item];
-        }
-        Prep pr;
-        prepare(m, ph, Ui, Pg, dtc[item], chi_abs[item], chi_es[item], c, pr);
-        pst = pr.status;
-        if (pr.extreme) {
-          defer = true;
-        } else {
-          // URAD from the first attempt's solution when it got below 1e-4, else from the guess
-          Best b0;
-          int it0;
-          rec_load(W.rec, slot, b0, it0);
-          const bool prev = b0.ok && b0.eT < 1e-4;
-          const double* src = prev ? b0.P : Pg;
-          rad_cons4(m, src, L.p);
-#pragma unroll
-          for (int q = 0; q < 5; q++) L.Pn[q] = src[q];
-          L.iters = it0;
-          L.mode = UM_START;
-          active = true;
-        }
-      } else {
+      if (got >= cnt) {
         exhausted = true;
+      } else if (W.rec.i[W.rec.cap + got] != REC_EXTREME) {
+        slot = got;
+        const long item = W.list[slot];
+        double Ui[12];
+#pragma unroll
+        for (int q = 0; q < 12; q++) Ui[q] = Ui_[q * n + item];
+        cell_setup(m, Ui, dtc[item], chi_abs[item], chi_es[item], c);
+        // URAD from the first attempt's solution when it got below 1e-4, else from the guess
+        Best b0;
+        int it0;
+        rec_load(W.rec, slot, b0, it0);
+        const bool prev = b0.ok && b0.eT < 1e-4;
+        if (!prev) {
+#pragma unroll
+          for (int q = 0; q < 12; q++) b0.P[q] = Pg_[q * n + item];
+        }
+        rad_cons4(m, b0.P, L.p);
+#pragma unroll
+        for (int q = 0; q < 5; q++) L.Pn[q] = b0.P[q];
+        L.iters = it0;
+        L.mode = UM_START;
+        active = true;
       }
     }
-    wave_append(defer, (int)item, D.counter, D.list);
-    bool ended = false, doeval = false;
-    if (active) {
+    bool ended = false;
+    if (active && stage == UE_NONE) {
       ended = urad_before(c, o, L);
-      doeval = !ended;
+      if (!ended) {
+        const MhdC gc = urad_gas(c, ph, L.p);
+        stage = mhd_start(m, gc, L.Pn[1], L.Pn + 2, in) ? UE_NEWTON : UE_FAILED;
+      }
     }
+    if (stage == UE_NEWTON) {
+      const MhdC gc = urad_gas(c, ph, L.p);
+      if (mhd_iterate<false>(gc, in, steps)) stage = in.ok ? UE_ROOT : UE_BISECT;
+    }
+    if (__popcll(__ballot(stage == UE_BISECT)) >= GRRMHD_URAD_BISECT || apart ||
+        !__any(stage == UE_NEWTON || stage == UE_ROOT || stage == UE_FAILED)) {
+      if (stage == UE_BISECT) {
+        const MhdC gc = urad_gas(c, ph, L.p);
+        stage = mhd_bisect(gc, in.Wp) ? UE_FAILED : UE_ROOT;
+      }
+    }
+    const bool doeval = stage == UE_ROOT || stage == UE_FAILED;
     if (doeval) {
       Eval ev;
       double Jn[4][4];
-      eval_urad_jac(c, ph, L.p, L.Pn, ev, Jn);
+      if (stage == UE_ROOT) {
+        eval_urad_jac(c, ph, L.p, L.Pn, ev, Jn, &in.Wp);
+      } else {
+        ev.ok = 0;
+        ev.eT = INFINITY;
+      }
       ended = urad_after(ev, Jn, L);
+      stage = UE_NONE;
     }
     const unsigned long long ev_mask = __ballot(doeval);
     useful += __popcll(ev_mask);
     slots += ev_mask ? 64ull : 0ull;
-    bool failed = false;
     if (ended) {
-      Best best;
-      int it0;
-      rec_load(W.rec, slot, best, it0);
-      int bm = -1;
-      if (best.ok) bm = M_PMHD;
-      else best.eT = INFINITY;
-      if (L.best.ok && L.best.eT < best.eT) {
-        best = L.best;
-        bm = M_URAD;
-      }
-      double Ui[12], Pg[12];
+      // the record: the better attempt, its method and all iterations
+      int* const i0 = W.rec.i + slot;
+      int& ok = i0[W.rec.cap];
+      const double e0 = ok ? W.rec.d[12 * W.rec.cap + slot] : INFINITY;
+      if (L.best.ok && L.best.eT < e0) {
+        const int st = i0[0] >> REC_STATUS;
+        L.best.ok = 1 | M_URAD << 1;
+        rec_store(W.rec, slot, L.best, L.iters, st);
 #pragma unroll
-      for (int q = 0; q < 12; q++) {
-        Ui[q] = Ui_[q * n + item];
-        Pg[q] = Pg_[q * n + item];
-      }
-      CellOut out;
-      if (bm < 0) failed_out(Ui, Pg, pst, L.iters, out);
-      else finalize(c, ph, o, best, bm, pst, L.iters, Ui, out);
-      store_out(out, item, n, Po, Uo, iters, status, err);
-      if (C.cascade) {
-        // not accepted: the rest of the full cascade resumes from the better of
-        // the PMHD and URAD attempts, kept in the cell's record (method in ok)
-        failed = !(bm >= 0 && best.eT < accept_threshold(o));
-        if (failed) {
-          Best kb = best;
-          kb.ok = (bm >= 0 ? 1 : 0) | ((bm >= 0 ? bm : 0) << 1);
-          rec_store(W.rec, slot, kb, L.iters);
-        }
+        for (int k = 0; k < 4; k++) W.rec.x[k * W.rec.cap + slot] = L.best.x[k];
       } else {
-        failed = (out.status & GRRMHD_ST_FAIL) && o.cold && cold_allowed(c, Pg);
+        ok = ok ? 1 | M_PMHD << 1 : 0;
+        i0[2 * W.rec.cap] = L.iters;
       }
       active = false;
     }
-    // to the cold limit; with the full cascade, the record slot to its rest
-    wave_append(failed, C.cascade ? (int)slot : (int)item, K.counter, K.list);
     if (!__any(active) && __all(exhausted)) break;
   }
   if ((threadIdx.x & 63) == 0 && useful) {
     atomicAdd(&W.stats[2], useful);
     atomicAdd(&W.stats[3], slots);
+  }
+}
+
+// Outputs of the cells of k_cascade_urad from their records, one thread each;
+// cells without an acceptable solution go on to the cold limit's list or, with
+// the full cascade, their slots to its rest (K).
+template <class Geo>
+__global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict__ Ui_,
+                                        const double* __restrict__ Pg_,
+                                        const double* __restrict__ dtc,
+                                        const double* __restrict__ chi_abs,
+                                        const double* __restrict__ chi_es,
+                                        double* __restrict__ Po, double* __restrict__ Uo,
+                                        int* __restrict__ iters, int* __restrict__ status,
+                                        double* __restrict__ err, Work W, Work K) {
+  const Phys ph = make_phys(C);
+  const Opts o = make_opts(C);
+  Metric m;
+  flat_metric(m);
+  const int cnt = *W.counter;
+  for (long slot = (long)blockIdx.x * blockDim.x + threadIdx.x; slot < cnt;
+       slot += (long)gridDim.x * blockDim.x) {
+    Best best;
+    int its;
+    if (W.rec.i[W.rec.cap + slot] == REC_EXTREME) continue;
+    rec_load(W.rec, slot, best, its);
+    const int st = W.rec.i[slot] >> REC_STATUS;
+    const int bm = best.ok ? best.ok >> 1 : -1;
+    const long item = W.list[slot];
+    double Ui[12], Pg[12];
+#pragma unroll
+    for (int q = 0; q < 12; q++) Ui[q] = Ui_[q * n + item];
+    Cell c;
+    cell_setup(m, Ui, dtc[item], chi_abs[item], chi_es[item], c);
+    CellOut out;
+    const bool done = bm >= 0 && best.eT < accept_threshold(o);
+    if (!done) {
+#pragma unroll
+      for (int q = 0; q < 12; q++) Pg[q] = Pg_[q * n + item];
+    }
+    if (bm < 0) {
+      failed_out(Ui, Pg, st, its, out);
+    } else {
+      if (bm == M_URAD) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) best.x[k] = W.rec.x[k * W.rec.cap + slot];
+      }
+      finalize(c, ph, o, best, bm, st, its, Ui, out);
+    }
+    store_out(out, item, n, Po, Uo, iters, status, err);
+    bool failed;
+    if (C.cascade) {
+      failed = !done;
+    } else {
+      failed = (out.status & GRRMHD_ST_FAIL) && o.cold;
+      if (failed) {
+        if (done) {   // solved, with u_g <= 0
+#pragma unroll
+          for (int q = 0; q < 12; q++) Pg[q] = Pg_[q * n + item];
+        }
+        failed = cold_allowed(c, Pg);
+      }
+    }
+    wave_append(failed, C.cascade ? (int)slot : (int)item, K.counter, K.list);
   }
 }
 
@@ -2098,7 +2229,7 @@ __global__ void LBP k_implicit_persist(Ctx C, long n, const double* __restrict__
                                        const double* __restrict__ chi_es,
                                        double* __restrict__ Po, double* __restrict__ Uo,
                                        int* __restrict__ iters, int* __restrict__ status,
-                                       double* __restrict__ err, int* next, Work W) {
+                                       double* __restrict__ err, int* next, Work W, Work D) {
   const Phys ph = make_phys(C);
   const Opts o = make_opts(C);
   const double thr = accept_threshold(o);
@@ -2170,7 +2301,7 @@ __global__ void LBP k_implicit_persist(Ctx C, long n, const double* __restrict__
         tolist = true;
       active = false;
     }
-    to_cascade(tolist, extreme, (int)item, L.best, L.iters, W);
+    to_batch_cascade(tolist, extreme, (int)item, L.best, L.iters, L.status, W, D);
     if (!__any(active) && __all(exhausted)) break;
   }
   if ((threadIdx.x & 63) == 0 && useful) {
@@ -2248,7 +2379,7 @@ __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui
                                     const double* __restrict__ Pg_, const double* __restrict__ dtc,
                                     const double* __restrict__ chi_abs,
                                     const double* __restrict__ chi_es, double* sd, int* si,
-                                    int* qcount, int* queue, Work W) {
+                                    int* qcount, int* queue, Work W, Work D) {
   const long cidx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   bool act = false, tolist = false, extreme = false;
   int trips = 0;
@@ -2283,7 +2414,7 @@ __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui
   }
   wave_stats(trips, W.stats);
   wave_append(act, (int)cidx, qcount, queue);
-  to_cascade(tolist, extreme, (int)cidx, L.best, L.iters, W);
+  to_batch_cascade(tolist, extreme, (int)cidx, L.best, L.iters, L.status, W, D);
 }
 
 // one Newton trip for every queued cell
@@ -2340,6 +2471,6 @@ __global__ void LB(64) k_iter_step(Ctx C, long n, const double* __restrict__ Ui_
     }
     wave_stats(trips, W.stats);
     wave_append(keepgoing, (int)cidx, qout_count, qout);
-    to_cascade(tolist, false, (int)cidx, L.best, L.iters, W);
+    to_cascade(tolist, false, (int)cidx, L.best, L.iters, W, L.status);
   }
 }

@@ -15,7 +15,7 @@ import pytest
 
 from paper_1312_6127_amd import inputs as I
 from test_oracle_pins import _periodic_box
-from test_gpu_parity import dev, field_err, host, interior_mask, say
+from test_gpu_parity import _batch_cons, dev, field_err, host, interior_mask, say
 
 pytestmark = pytest.mark.gpu
 
@@ -148,3 +148,34 @@ def test_lane_statistics(G, orc, n):
         assert trips == launches * (host(it)[m] + 1).sum()
         assert trips <= slots <= launches * 64 * (host(it)[m] + 1).sum() and slots % 64 == 0
     g.close()
+
+
+def test_batch_cascade_in_parts(G, orc):
+    """A batch whose cascade list is longer than the lanes of the grid (lanes
+    take their inversions in parts, bisections wait for company), against the
+    same cells in batches down to a single cell, whose lists are spread over
+    the wavefronts: the same bits, cell by cell."""
+    k, reps = 5000, 30
+    n = k * reps + 1
+    say("case batch cascade", n)
+    pd, P, dt, ca, ce = I.implicit_batch(k, seed=11)
+    U = _batch_cons(orc, pd, P)
+    tile = np.arange(n) % k
+    dt = dt[tile] * (1.0 + 0.02 * (np.arange(n) // k))
+    args = [dev(x) for x in (U[:, tile], P[:, tile], dt, ca[tile], ce[tile])]
+    ws = G.batch_workspace(n)
+    whole = G.implicit_source_ex(pd, *args, G.PER_CELL, ws=ws)
+    assert G.batch_stats(ws)[2] > 64 * 1024
+    evals = G.batch_cascade_stats(ws)[0]
+    at = parts = 0
+    for size in (1, 63, 64, 65, 1023, 4099, 20000, n):
+        end = min(at + size, n)
+        sub = [x[..., at:end].contiguous() for x in args]
+        ws = G.batch_workspace(end - at)
+        part = G.implicit_source_ex(pd, *sub, G.PER_CELL, ws=ws)
+        parts += G.batch_cascade_stats(ws)[0]
+        for a, b in zip(whole, part):
+            a, b = host(a[..., at:end].contiguous()), host(b)
+            assert np.array_equal(a.view(np.uint8), b.view(np.uint8)), (at, end)
+        at = end
+    assert at == n and parts == evals
