@@ -554,15 +554,8 @@ static __global__ void LB(256) k_adj_stage(Ctx C, double a, double b, const doub
 // the stage cotangent lamUe (zero outside the interior) through the face
 // induction fluxes the update builds from the EMFs.
 // ---------------------------------------------------------------------------
-DEV void adj_emf_at(Ctx C, int a, FaceRange R, double scale,
-                                  const double* __restrict__ dt_dev,
-                                  const double* __restrict__ lamUe, double* __restrict__ lamE, long t) {
-  if (t >= R.total) return;
-  const int i = R.lo[0] + t % R.cnt[0];
-  const long t2 = t / R.cnt[0];
-  const int j = R.lo[1] + t2 % R.cnt[1];
-  const int k = R.lo[2] + t2 / R.cnt[1];
-  const long e = cell_index(C, i, j, k);
+DEV double adj_emf_at(const Ctx& C, int a, int j, long e, double scale,
+                      const double* __restrict__ dt_dev, const double* __restrict__ lamUe) {
   const int b = (a + 1) % 3, cd = (a + 2) % 3;
   double acc = 0.0;
   bool zero = false;
@@ -583,13 +576,27 @@ DEV void adj_emf_at(Ctx C, int a, FaceRange R, double scale,
       acc += coef * ((L[e - sd] + L[e - sd - sb]) - (L[e] + L[e - sb]));
     }
   }
-  lamE[(long)a * C.Ntot + e] = acc;
+  return acc;
 }
 
-static __global__ void LB(256) k_adj_emf(Ctx C, int a, FaceRange R, double scale,
-                                  const double* __restrict__ dt_dev,
-                                  const double* __restrict__ lamUe, double* __restrict__ lamE) {
-  adj_emf_at(C, a, R, scale, dt_dev, lamUe, lamE, (long)blockIdx.x * blockDim.x + threadIdx.x);
+// Every orientation at every allocated position, zero off the edges (a launch
+// for each, behind one that cleared lamE, took 20 us of a stage where this
+// takes 6: grids of this size are launches and their gaps).
+static __global__ void LB(256) k_adj_emf(Ctx C, double scale, const double* __restrict__ dt_dev,
+                                         const double* __restrict__ lamUe,
+                                         double* __restrict__ lamE) {
+  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= C.Ntot) return;
+  const int k = (int)(e / C.npos), pos = (int)(e - (long)k * C.npos);
+  const int idx[3] = {pos % C.N[0], pos / C.N[0], k};
+#pragma unroll
+  for (int a = 0; a < 3; a++) {
+    bool edge = C.n[(a + 1) % 3] > 1 && C.n[(a + 2) % 3] > 1;
+#pragma unroll
+    for (int d = 0; d < 3; d++)
+      edge = edge && idx[d] >= C.ng[d] && idx[d] < C.ng[d] + C.n[d] + (d == a ? 0 : 1);
+    lamE[(long)a * C.Ntot + e] = edge ? adj_emf_at(C, a, idx[1], e, scale, dt_dev, lamUe) : 0.0;
+  }
 }
 
 // A face state reduced to what the flux cotangent needs: the sums
@@ -884,20 +891,40 @@ DEV void adj_flux_at(Ctx C, FaceRange R, double scale,
   }
 }
 
-template <class Geo, int D, bool PPM>
-__global__ void __launch_bounds__(64) k_adj_flux(Ctx C, FaceRange R, double scale,
+// The faces of all active directions in one launch, one direction after the
+// other: first[d] is the first block of the d-th, in G + d gs.  A wavefront
+// holds a SIMD by itself, and a launch takes as many rounds of 62 us as it has
+// 1024ths of wavefronts, so three launches waste three last rounds: at
+// 49x25x12 a stage's three launches took 186 us, this one 69; at 96x48x24 376
+// and 364.
+struct AdjFaces {
+  FaceRange R[3];
+  unsigned first[4];
+};
+template <class Geo, bool PPM>
+__global__ void __launch_bounds__(64) k_adj_flux(Ctx C, AdjFaces S, double scale,
                                                  const double* __restrict__ dt_dev,
                                                  const double* __restrict__ P,
                                                  const double* __restrict__ chi_abs,
                                                  const double* __restrict__ chi_es,
                                                  const double* __restrict__ lamUe,
                                                  const double* __restrict__ lamE,
-                                                 double* __restrict__ G, double* __restrict__ Gx,
+                                                 double* __restrict__ G, long gs,
+                                                 double* __restrict__ Gx,
                                                  const double* __restrict__ fl,
                                                  double* __restrict__ GF,
                                                  const double* __restrict__ lamS) {
-  adj_flux_at<Geo, D, PPM>(C, R, scale, dt_dev, P, chi_abs, chi_es, lamUe, lamE, G, Gx, fl, GF, lamS,
-                      (long)blockIdx.x * blockDim.x + threadIdx.x);
+  const int d = blockIdx.x < S.first[1] ? 0 : blockIdx.x < S.first[2] ? 1 : 2;
+  const long t = (long)(blockIdx.x - S.first[d]) * blockDim.x + threadIdx.x;
+  double* Gd = G + d * gs;
+  double* Gxd = Gx ? Gx + 2 * d * C.Ntot : nullptr;
+  double* GFd = PPM ? GF + 4 * d * C.Ntot : nullptr;
+  if (d == 0)
+    adj_flux_at<Geo, 1, PPM>(C, S.R[0], scale, dt_dev, P, chi_abs, chi_es, lamUe, lamE, Gd, Gxd, fl, GFd, lamS, t);
+  else if (d == 1)
+    adj_flux_at<Geo, 2, PPM>(C, S.R[1], scale, dt_dev, P, chi_abs, chi_es, lamUe, lamE, Gd, Gxd, fl, GFd, lamS, t);
+  else
+    adj_flux_at<Geo, 3, PPM>(C, S.R[2], scale, dt_dev, P, chi_abs, chi_es, lamUe, lamE, Gd, Gxd, fl, GFd, lamS, t);
 }
 
 // ---------------------------------------------------------------------------

@@ -30,6 +30,7 @@ struct grrmhd_grid {
   int tile_i = 0;
   int* tkeys = nullptr;
   int* torder = nullptr;
+  int ncu = 0;             // compute units of the device
   int cp = 0;
   Work W;               // implicit cascade list (interior indices), records, stats;
                         // W.counter is the list length of the last launch
@@ -241,9 +242,12 @@ extern "C" int grrmhd_init_grid(const grrmhd_params* p, int device, void* hip_st
   HIPCHK(hipGetDeviceCount(&ndev));
   if (device < 0 || device >= ndev) return fail(GRRMHD_EINVAL, "device ordinal out of range");
   HIPCHK(hipSetDevice(device));
+  int ncu = 0;
+  HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device));
   grrmhd_grid* g = new grrmhd_grid;
   g->p = *p;
   g->device = device;
+  g->ncu = ncu;
   g->stream = (hipStream_t)hip_stream;
   fill_ctx(p, g->C);
   const size_t tab = (size_t)g->C.npos;
@@ -488,17 +492,6 @@ static FaceRange face_range(const Ctx& C, int d, int ext = 1) {
   return R;
 }
 
-static FaceRange edge_range(const Ctx& C, int a) {
-  FaceRange R;
-  R.total = 1;
-  for (int e = 0; e < 3; e++) {
-    if (e == a) { R.lo[e] = C.ng[e]; R.cnt[e] = C.n[e]; }
-    else { R.lo[e] = C.ng[e]; R.cnt[e] = C.n[e] + 1; }
-    R.total *= R.cnt[e];
-  }
-  return R;
-}
-
 // Split a range at x1 index i0: [lo, i0) and [i0, hi) (either may be empty).
 static void split_x1(const FaceRange& R, int i0, FaceRange& a, FaceRange& b) {
   a = b = R;
@@ -701,14 +694,19 @@ static int launch_implicit(grrmhd_grid* g, Form form, const double* Ue, const do
   W.counter = g->cnt[g->cp];
   W.counter_next = g->cnt[g->cp ^ 1];
   const bool timed = g->timing && g->nt < grrmhd_grid::TCAP;
-  // tiles costliest first by the previous launch's trip counts
-  hipLaunchKernelGGL(k_tile_order, dim3(9), dim3(1024), 0, g->stream, g->ntiles,
-                     (const int*)g->tkeys, g->torder);
-  LAUNCHCHK();
+  // tiles costliest first by the previous launch's trip counts; where every
+  // tile starts at once (a SIMD each) there is nothing to order, and the sort
+  // would be 3 to 5 us of a stage of 60
+  const bool sort = g->ntiles > 4L * g->ncu;
+  if (sort) {
+    hipLaunchKernelGGL(k_tile_order, dim3(9), dim3(1024), 0, g->stream, g->ntiles,
+                       (const int*)g->tkeys, g->torder);
+    LAUNCHCHK();
+  }
   if (timed) HIPCHK(hipEventRecord(g->ev[2 * g->nt], g->stream));
   hipLaunchKernelGGL(GEO_KERNEL(g, form, k_implicit), dim3((unsigned)g->ntiles), dim3(64), 0, g->stream, g->C,
                      g->tile_i, Ue, Pg, scale, dt_dev, ca, ce, P, U, it, st, err, W,
-                     (const int*)g->torder, g->tkeys);
+                     (const int*)(sort ? g->torder : nullptr), sort ? g->tkeys : (int*)nullptr);
   LAUNCHCHK();
   if (timed) {
     HIPCHK(hipEventRecord(g->ev[2 * g->nt + 1], g->stream));
@@ -1286,35 +1284,22 @@ static int adj_explicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
   const double* fl = ppm ? FLT->fl : nullptr;
   double* GF = ppm ? FLT->GF : nullptr;
   int rc;
-  if ((rc = fill_d(g, lamE, 3 * N, 0.0))) return rc;
-  for (int a = 0; a < 3; a++) {
-    if (C.n[(a + 1) % 3] == 1 || C.n[(a + 2) % 3] == 1) continue;
-    const FaceRange R = edge_range(C, a);
-    hipLaunchKernelGGL(k_adj_emf, dim3(nblocks(R.total, 256)), dim3(256), 0, s, C, a, R, scale,
-                       dt_dev, lamUe, lamE);
-    LAUNCHCHK();
-  }
+  hipLaunchKernelGGL(k_adj_emf, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, scale, dt_dev,
+                     lamUe, lamE);
+  LAUNCHCHK();
   FaceRanges FR;
-  for (int d = 0; d < 3; d++) FR.r[d] = face_range(C, d);
+  AdjFaces AF;
+  AF.first[0] = 0;
   for (int d = 0; d < 3; d++) {
-    if (C.n[d] == 1) continue;
-    const FaceRange& R = FR.r[d];
-    double* Gd = G + (size_t)d * gs;
-    double* Gxd = Gx ? Gx + (size_t)d * 2 * N : nullptr;
-    double* GFd = ppm ? GF + (size_t)d * 4 * N : nullptr;
-    const dim3 gr(nblocks(R.total, 64)), bl(64);
-#define ADJ_FLUX(D, PPM)                                                                      \
-  hipLaunchKernelGGL((k_adj_flux<Dense, D, PPM>), gr, bl, 0, s, C, R, scale, dt_dev, Pb, ca, ce, lamUe, \
-                     (const double*)lamE, Gd, Gxd, fl, GFd, lamS)
-    if (ppm) {
-      if (d == 0) ADJ_FLUX(1, true);
-      if (d == 1) ADJ_FLUX(2, true);
-      if (d == 2) ADJ_FLUX(3, true);
-    } else {
-      if (d == 0) ADJ_FLUX(1, false);
-      if (d == 1) ADJ_FLUX(2, false);
-      if (d == 2) ADJ_FLUX(3, false);
-    }
+    FR.r[d] = AF.R[d] = face_range(C, d);
+    AF.first[d + 1] = AF.first[d] + (C.n[d] > 1 ? nblocks(FR.r[d].total, 64) : 0);
+  }
+  if (AF.first[3] > 0) {
+#define ADJ_FLUX(PPM)                                                                         \
+  hipLaunchKernelGGL((k_adj_flux<Dense, PPM>), dim3(AF.first[3]), dim3(64), 0, s, C, AF, scale, \
+                     dt_dev, Pb, ca, ce, lamUe, (const double*)lamE, G, (long)gs, Gx, fl, GF, lamS)
+    if (ppm) ADJ_FLUX(true);
+    else ADJ_FLUX(false);
 #undef ADJ_FLUX
     LAUNCHCHK();
   }

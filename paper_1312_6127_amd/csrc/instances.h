@@ -75,23 +75,11 @@
       Work, Work);
 
 #define INST_ADJ_FLUX(X, Geo)                                                                     \
-  X template __global__ void k_adj_flux<Geo, 1, false>(Ctx, FaceRange, double, const              \
-      double*, const double*, const double*, const double*, const double*, const double*,         \
-      double*, double*, const double*, double*, const double*);                                   \
-  X template __global__ void k_adj_flux<Geo, 2, false>(Ctx, FaceRange, double, const              \
-      double*, const double*, const double*, const double*, const double*, const double*,         \
-      double*, double*, const double*, double*, const double*);                                   \
-  X template __global__ void k_adj_flux<Geo, 3, false>(Ctx, FaceRange, double, const              \
-      double*, const double*, const double*, const double*, const double*, const double*,         \
-      double*, double*, const double*, double*, const double*);                                   \
-  X template __global__ void k_adj_flux<Geo, 1, true>(Ctx, FaceRange, double, const double*,      \
-      const double*, const double*, const double*, const double*, const double*, double*,         \
+  X template __global__ void k_adj_flux<Geo, false>(Ctx, AdjFaces, double, const double*, const   \
+      double*, const double*, const double*, const double*, const double*, double*, long,         \
       double*, const double*, double*, const double*);                                            \
-  X template __global__ void k_adj_flux<Geo, 2, true>(Ctx, FaceRange, double, const double*,      \
-      const double*, const double*, const double*, const double*, const double*, double*,         \
-      double*, const double*, double*, const double*);                                            \
-  X template __global__ void k_adj_flux<Geo, 3, true>(Ctx, FaceRange, double, const double*,      \
-      const double*, const double*, const double*, const double*, const double*, double*,         \
+  X template __global__ void k_adj_flux<Geo, true>(Ctx, AdjFaces, double, const double*, const    \
+      double*, const double*, const double*, const double*, const double*, double*, long,         \
       double*, const double*, double*, const double*);
 
 #define INST_ADJ_IMPLICIT(X, Geo)                                                                 \
