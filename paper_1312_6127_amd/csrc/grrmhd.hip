@@ -1304,11 +1304,11 @@ static int adj_explicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
     LAUNCHCHK();
   }
   if (ppm)
-    hipLaunchKernelGGL(k_adj_gather<6>, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, FR,
+    hipLaunchKernelGGL(k_adj_gather<6>, dim3(nblocks(C.Ntot, 256), 12), dim3(256), 0, s, C, FR,
                        (const double*)G, (const double*)(G + gs), (const double*)(G + 2 * gs),
                        lamPb);
   else
-    hipLaunchKernelGGL(k_adj_gather<4>, dim3(nblocks(C.Ntot, 256)), dim3(256), 0, s, C, FR,
+    hipLaunchKernelGGL(k_adj_gather<4>, dim3(nblocks(C.Ntot, 256), 12), dim3(256), 0, s, C, FR,
                        (const double*)G, (const double*)(G + gs), (const double*)(G + 2 * gs),
                        lamPb);
   LAUNCHCHK();
