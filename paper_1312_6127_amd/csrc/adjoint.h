@@ -979,11 +979,14 @@ __global__ void LB(256) k_adj_gather(Ctx C, FaceRanges FR, const double* __restr
 }
 
 // Interior cell t (curved metric): lamPb += c dt (dS/dP)^T lamUe, the
-// geometric source's Jacobian by Dual<4> passes over the 12 primitives.
+// geometric source's Jacobian by Dual<4> passes over the 12 primitives, all in
+// one thread (one row of blocks) or a thread for each (three rows): the latter
+// where the chip holds all of their wavefronts, one a SIMD (49x25x12: 15 us in
+// one thread, 8 in three; 96x48x24, three times over that: 31 and 35).
 template <class Geo>
 DEV void adj_geom_at(Ctx C, double scale, const double* __restrict__ dt_dev,
                      const double* __restrict__ P, const double* __restrict__ lamUe,
-                     double* __restrict__ lamPb, long t) {
+                     double* __restrict__ lamPb, long t, int from, int to) {
   if (t >= (long)C.n[0] * C.n[1] * C.n[2]) return;
   int i, j, k;
   interior_cell(C, t, i, j, k);
@@ -1001,7 +1004,7 @@ DEV void adj_geom_at(Ctx C, double scale, const double* __restrict__ dt_dev,
   const double cdt = scale * (*dt_dev);
   // values kept opaque per pass (empty asm), as in the face passes
 #pragma unroll 1
-  for (int pass = 0; pass < 3; pass++) {
+  for (int pass = from; pass < to; pass++) {
     D4 pd[12], S[12];
     double pv[12];
 #pragma unroll
@@ -1025,7 +1028,9 @@ template <class Geo>
 __global__ void LB(64) k_adj_geom(Ctx C, double scale, const double* __restrict__ dt_dev,
                                   const double* __restrict__ P, const double* __restrict__ lamUe,
                                   double* __restrict__ lamPb) {
-  adj_geom_at<Geo>(C, scale, dt_dev, P, lamUe, lamPb, (long)blockIdx.x * blockDim.x + threadIdx.x);
+  const int n = 3 / gridDim.y;
+  adj_geom_at<Geo>(C, scale, dt_dev, P, lamUe, lamPb, (long)blockIdx.x * blockDim.x + threadIdx.x,
+                   n * blockIdx.y, n * (blockIdx.y + 1));
 }
 
 // Opacity cotangents through the fluxes: per allocated cell, the faces that

@@ -31,6 +31,10 @@ struct grrmhd_grid {
   int* tkeys = nullptr;
   int* torder = nullptr;
   int ncu = 0;             // compute units of the device
+  bool sorted = false;     // torder is up to date with tkeys
+  // where every tile starts at once (a SIMD each) there is nothing to order,
+  // and the sort would be 3 to 5 us of a stage of 60
+  bool sorts() const { return ntiles > 4L * ncu; }
   int cp = 0;
   Work W;               // implicit cascade list (interior indices), records, stats;
                         // W.counter is the list length of the last launch
@@ -672,10 +676,18 @@ static int launch_update(grrmhd_grid* g, Form form, double a, double b, double c
   memset(&MT, 0, sizeof(MT));
   if (mt) MT = *mt;
   const int* n = g->C.n;
-  hipLaunchKernelGGL(GEO_KERNEL(g, form, k_update), dim3(nblocks((long)n[0] * n[1], UPDATE_BLOCK) * n[2]),
+  // the next implicit launch's tiles are sorted here: a launch for it takes 5
+  // us at 128x64x32 (9 blocks), beside an update nothing
+  TileSort TS = {g->ntiles, g->tkeys, nullptr};
+  if (g->sorts() && !g->sorted) {
+    TS.order = g->torder;
+    g->sorted = true;
+  }
+  const unsigned blocks = nblocks((long)n[0] * n[1], UPDATE_BLOCK) * n[2];
+  hipLaunchKernelGGL(GEO_KERNEL(g, form, k_update), dim3(blocks + (TS.order ? TILE_SORT_BLOCKS : 0)),
                      dim3(UPDATE_BLOCK), 0, g->stream,
                      g->C, a, b, c, const_cast<double*>(dt_dev), dtmin, dtnext, P, Un, Up, F, emf,
-                     MT, Ue, Bface);
+                     MT, Ue, Bface, TS);
   LAUNCHCHK();
   return 0;
 }
@@ -694,15 +706,15 @@ static int launch_implicit(grrmhd_grid* g, Form form, const double* Ue, const do
   W.counter = g->cnt[g->cp];
   W.counter_next = g->cnt[g->cp ^ 1];
   const bool timed = g->timing && g->nt < grrmhd_grid::TCAP;
-  // tiles costliest first by the previous launch's trip counts; where every
-  // tile starts at once (a SIMD each) there is nothing to order, and the sort
-  // would be 3 to 5 us of a stage of 60
-  const bool sort = g->ntiles > 4L * g->ncu;
-  if (sort) {
-    hipLaunchKernelGGL(k_tile_order, dim3(9), dim3(1024), 0, g->stream, g->ntiles,
+  // tiles costliest first by the previous launch's trip counts: sorted beside
+  // the update that came before, or here
+  const bool sort = g->sorts();
+  if (sort && !g->sorted) {
+    hipLaunchKernelGGL(k_tile_order, dim3(GRRMHD_ORDER_BLOCKS), dim3(1024), 0, g->stream, g->ntiles,
                        (const int*)g->tkeys, g->torder);
     LAUNCHCHK();
   }
+  g->sorted = false;
   if (timed) HIPCHK(hipEventRecord(g->ev[2 * g->nt], g->stream));
   hipLaunchKernelGGL(GEO_KERNEL(g, form, k_implicit), dim3((unsigned)g->ntiles), dim3(64), 0, g->stream, g->C,
                      g->tile_i, Ue, Pg, scale, dt_dev, ca, ce, P, U, it, st, err, W,
@@ -1314,7 +1326,8 @@ static int adj_explicit(grrmhd_grid* g, double scale, const double* dt_dev, cons
   LAUNCHCHK();
   if (C.metric != GRRMHD_MINKOWSKI) {
     const long ncell = (long)C.n[0] * C.n[1] * C.n[2];
-    hipLaunchKernelGGL(k_adj_geom<Dense>, dim3(nblocks(ncell, 64)), dim3(64), 0, s, C, scale, dt_dev, Pb,
+    const unsigned rows = 3L * nblocks(ncell, 64) <= 4L * g->ncu ? 3 : 1;
+    hipLaunchKernelGGL(k_adj_geom<Dense>, dim3(nblocks(ncell, 64), rows), dim3(64), 0, s, C, scale, dt_dev, Pb,
                        lamUe, lamPb);
     LAUNCHCHK();
   }

@@ -1228,15 +1228,72 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
   }
 }
 
+// Dispatch order of the implicit kernel's tiles: costliest first, by the
+// largest Newton-trip count of each tile's first attempts in the previous
+// launch (keys), one bucket per count up to GRRMHD_ORDER_BUCKETS - 1.  A
+// wavefront costs what its slowest lane costs, and with a few waves per
+// SIMD the launch ends on whichever tiles start last: dispatching the long
+// ones first leaves the short ones to fill the end.  The sort keeps the
+// XCD-aware split (xcd_block: XCD x works through the x-th eighth of the
+// tiles, whose neighbours share its L2): each eighth is sorted apart, one
+// block each (a ninth takes the remainder tiles), by counting sort (ties in
+// any order; every tile's result is independent of it).  order[] maps each
+// eighth onto itself.
+#define GRRMHD_ORDER_BUCKETS 64
+DEV int order_bucket(int key) { return ::min(::max(key, 0), GRRMHD_ORDER_BUCKETS - 1); }
+
+#define GRRMHD_ORDER_BLOCKS 9
+DEV void tile_order(long ntiles, const int* __restrict__ keys, int* __restrict__ order) {
+  __shared__ int cnt[GRRMHD_ORDER_BUCKETS];
+  const long seg = ntiles / 8;
+  const long lo = (blockIdx.x < 8) ? (long)blockIdx.x * seg : 8 * seg;
+  const long hi = (blockIdx.x < 8) ? lo + seg : ntiles;
+  for (int b = threadIdx.x; b < GRRMHD_ORDER_BUCKETS; b += blockDim.x) cnt[b] = 0;
+  __syncthreads();
+  for (long t = lo + threadIdx.x; t < hi; t += blockDim.x) atomicAdd(&cnt[order_bucket(keys[t])], 1);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int sum = 0;   // exclusive prefix, largest bucket first
+    for (int b = GRRMHD_ORDER_BUCKETS - 1; b >= 0; b--) {
+      const int c = cnt[b];
+      cnt[b] = sum;
+      sum += c;
+    }
+  }
+  __syncthreads();
+  for (long t = lo + threadIdx.x; t < hi; t += blockDim.x)
+    order[lo + atomicAdd(&cnt[order_bucket(keys[t])], 1)] = (int)t;
+}
+
+static __global__ void __launch_bounds__(1024) k_tile_order(long ntiles, const int* __restrict__ keys,
+                                                     int* __restrict__ order) {
+  tile_order(ntiles, keys, order);
+}
+
+// The same beside another kernel's work: the launch's first TILE_SORT_BLOCKS
+// blocks (a multiple of the XCDs, so that the others keep theirs).
+struct TileSort {
+  long ntiles;
+  const int* keys;
+  int* order;   // null: no sort, no blocks for it
+};
+#define TILE_SORT_BLOCKS 16
+
 template <class Geo>
 __global__ void LB(128) k_update(Ctx C, double ca, double cb, double cc, double* dt_dev,
                                  const unsigned long long* dtmin, unsigned long long* dtnext,
                                  const double* __restrict__ P, const double* __restrict__ Un,
                                  const double* __restrict__ Uprev, const double* __restrict__ F,
                                  const double* __restrict__ emf, MTerms MT,
-                                 double* __restrict__ Uexp, const double* __restrict__ Bface) {
+                                 double* __restrict__ Uexp, const double* __restrict__ Bface,
+                                 TileSort TS) {
+  const unsigned skip = TS.order ? TILE_SORT_BLOCKS : 0;
+  if (blockIdx.x < skip) {
+    if (blockIdx.x < GRRMHD_ORDER_BLOCKS) tile_order(TS.ntiles, TS.keys, TS.order);
+    return;
+  }
   int u, k;
-  column_piece(xcd_block(blockIdx.x, gridDim.x), C.n[2], u, k);
+  column_piece(xcd_block(blockIdx.x - skip, gridDim.x - skip), C.n[2], u, k);
   update_at<Geo>(C, ca, cb, cc, dt_dev, dtmin, dtnext, P, Un, Uprev, F, emf, MT, Uexp, u, k, Bface);
 }
 
@@ -1389,43 +1446,6 @@ DEV int wave_stats(int trips, unsigned long long* stats) {
     atomicAdd(&stats[1], 64ull * (unsigned long long)mx);
   }
   return mx;
-}
-
-// Dispatch order of the implicit kernel's tiles: costliest first, by the
-// largest Newton-trip count of each tile's first attempts in the previous
-// launch (keys), one bucket per count up to GRRMHD_ORDER_BUCKETS - 1.  A
-// wavefront costs what its slowest lane costs, and with a few waves per
-// SIMD the launch ends on whichever tiles start last: dispatching the long
-// ones first leaves the short ones to fill the end.  The sort keeps the
-// XCD-aware split (xcd_block: XCD x works through the x-th eighth of the
-// tiles, whose neighbours share its L2): each eighth is sorted apart, one
-// block each (a ninth takes the remainder tiles), by counting sort (ties in
-// any order; every tile's result is independent of it).  order[] maps each
-// eighth onto itself.
-#define GRRMHD_ORDER_BUCKETS 64
-DEV int order_bucket(int key) { return ::min(::max(key, 0), GRRMHD_ORDER_BUCKETS - 1); }
-
-static __global__ void __launch_bounds__(1024) k_tile_order(long ntiles, const int* __restrict__ keys,
-                                                     int* __restrict__ order) {
-  __shared__ int cnt[GRRMHD_ORDER_BUCKETS];
-  const long seg = ntiles / 8;
-  const long lo = (blockIdx.x < 8) ? (long)blockIdx.x * seg : 8 * seg;
-  const long hi = (blockIdx.x < 8) ? lo + seg : ntiles;
-  for (int b = threadIdx.x; b < GRRMHD_ORDER_BUCKETS; b += blockDim.x) cnt[b] = 0;
-  __syncthreads();
-  for (long t = lo + threadIdx.x; t < hi; t += blockDim.x) atomicAdd(&cnt[order_bucket(keys[t])], 1);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int sum = 0;   // exclusive prefix, largest bucket first
-    for (int b = GRRMHD_ORDER_BUCKETS - 1; b >= 0; b--) {
-      const int c = cnt[b];
-      cnt[b] = sum;
-      sum += c;
-    }
-  }
-  __syncthreads();
-  for (long t = lo + threadIdx.x; t < hi; t += blockDim.x)
-    order[lo + atomicAdd(&cnt[order_bucket(keys[t])], 1)] = (int)t;
 }
 
 static __global__ void k_zero_ints(int* p, int k) {
