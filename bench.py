@@ -81,7 +81,7 @@ def parse():
 def kernel_digest():
     """sha256 over the HIP sources of the implicit kernel: the headers it
     includes and the part of kernels.h from the implicit-solve section
-    (make_phys, make_opts, Work, the tile order, k_implicit) up to the
+    (make_phys, make_opts, Work, k_implicit) up to the
     listed-cell kernel, plus xcd_block."""
     import hashlib
 

@@ -314,6 +314,9 @@ extern "C" int grrmhd_init_grid(const grrmhd_params* p, int device, void* hip_st
   hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)g->W.stats, STAT_INTS);
   // no costs known yet: the first launch takes the tiles in any order
   hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, g->tkeys, (int)g->ntiles);
+  // from here on torder holds a permutation of the tiles whatever runs next
+  hipLaunchKernelGGL(k_tile_order, dim3(GRRMHD_ORDER_BLOCKS), dim3(1024), 0, g->stream, g->ntiles,
+                     (const int*)g->tkeys, g->torder);
   hipLaunchKernelGGL(k_dt_init, dim3(1), dim3(64), 0, g->stream, g->dtslot, 1, 1);
   hipLaunchKernelGGL(k_dt_init, dim3(1), dim3(64), 0, g->stream, g->dtstep[0],
                      2 * GRRMHD_DT_SLOTS, GRRMHD_DT_STRIDE);

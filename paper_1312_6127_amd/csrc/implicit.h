@@ -57,8 +57,8 @@ struct Phys {
 struct Opts {
   double tol_pmhd, tol_urad, tol_accept, tol_fail;
   int max_iter, roundoff;
-  int cold;         // try the cold MHD limit where no energy solution is found
-  double u_floor;   // u_g of the cold limit
+  int cold = 0;           // try the cold MHD limit where no energy solution is found
+  double u_floor = 0.0;   // u_g of the cold limit
 };
 
 template <class M>
