@@ -46,9 +46,9 @@ STEP_BYTES_PER_ZONE = 1344
 # (FETCH_SIZE x 2 + WRITE_SIZE x 1, the scales from a copy of known size).
 # They hold for the kernel sources whose digest is KERNEL_DIGEST; otherwise
 # traffic is reported as null and the flop figure as stale.
-FLOPS_PER_TRIP = 1732.0
-HBM_BYTES_PER_LAUNCH = 161.4e6
-KERNEL_DIGEST = "a496eb5245363797"
+FLOPS_PER_TRIP = 933.0
+HBM_BYTES_PER_LAUNCH = 143.6e6
+KERNEL_DIGEST = "f1a16800e7e22f90"
 
 
 def parse():
