@@ -1016,7 +1016,7 @@ struct RecBuf {
   double* d;
   int* i;
   long cap;
-  double* x;   // [4][cap], batches alone
+  double* x;   // [4][cap], batches alone (a grid's records hold PMHD attempts)
 };
 enum { REC_STATUS = 8, REC_EXTREME = -1 };
 
@@ -1029,15 +1029,33 @@ DEV void rec_store(const RecBuf& R, long slot, const Best& b, int iters, int sta
   R.i[2 * R.cap + slot] = iters;
 }
 
-DEV void rec_load(const RecBuf& R, long slot, Best& b, int& iters) {
+// A batch cell's URAD attempt b beside the first attempt in its record: the
+// better one stays there, with its method and all iterations.
+DEV void rec_urad(const RecBuf& R, long slot, Best& b, int iters) {
+  int& ok = R.i[R.cap + slot];
+  const double e0 = ok ? R.d[12 * R.cap + slot] : INFINITY;
+  if (b.ok && b.eT < e0) {
+    b.ok = 1 | M_URAD << 1;
+    rec_store(R, slot, b, iters, R.i[slot] >> REC_STATUS);
 #pragma unroll
-  for (int k = 0; k < 4; k++) b.x[k] = 0.0;
+    for (int k = 0; k < 4; k++) R.x[k * R.cap + slot] = b.x[k];
+  } else {
+    ok = ok ? 1 | M_PMHD << 1 : 0;
+    R.i[2 * R.cap + slot] = iters;
+  }
+}
+
+// With a URAD attempt's iterate, which its conserved radiation is.
+DEV void rec_load(const RecBuf& R, long slot, Best& b, int& iters) {
 #pragma unroll
   for (int q = 0; q < 12; q++) b.P[q] = R.d[q * R.cap + slot];
   b.eT = R.d[12 * R.cap + slot];
   b.radflags = R.i[slot] & ((1 << REC_STATUS) - 1);
   b.ok = R.i[R.cap + slot];
   iters = R.i[2 * R.cap + slot];
+  const bool urad = b.ok >> 1 == M_URAD;
+#pragma unroll
+  for (int k = 0; k < 4; k++) b.x[k] = urad ? R.x[k * R.cap + slot] : 0.0;
 }
 
 // Common case: not extreme, first PMHD attempt accepted.  Returns false when

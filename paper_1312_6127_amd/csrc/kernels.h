@@ -1886,20 +1886,7 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
     useful += __popcll(ev_mask);
     slots += ev_mask ? 64ull : 0ull;
     if (ended) {
-      // the record: the better attempt, its method and all iterations
-      int* const i0 = W.rec.i + slot;
-      int& ok = i0[W.rec.cap];
-      const double e0 = ok ? W.rec.d[12 * W.rec.cap + slot] : INFINITY;
-      if (L.best.ok && L.best.eT < e0) {
-        const int st = i0[0] >> REC_STATUS;
-        L.best.ok = 1 | M_URAD << 1;
-        rec_store(W.rec, slot, L.best, L.iters, st);
-#pragma unroll
-        for (int k = 0; k < 4; k++) W.rec.x[k * W.rec.cap + slot] = L.best.x[k];
-      } else {
-        ok = ok ? 1 | M_PMHD << 1 : 0;
-        i0[2 * W.rec.cap] = L.iters;
-      }
+      rec_urad(W.rec, slot, L.best, L.iters);
       active = false;
     }
     if (!__any(active) && __all(exhausted)) break;
@@ -1950,10 +1937,6 @@ __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict_
     if (bm < 0) {
       failed_out(Ui, Pg, st, its, out);
     } else {
-      if (bm == M_URAD) {
-#pragma unroll
-        for (int k = 0; k < 4; k++) best.x[k] = W.rec.x[k * W.rec.cap + slot];
-      }
       finalize(c, ph, o, best, bm, st, its, Ui, out);
     }
     store_out(out, item, n, Po, Uo, iters, status, err);

@@ -209,3 +209,32 @@ def test_adjoint_guards_of_the_full_cascade(G):
     with pytest.raises(RuntimeError, match="cascade"):
         gr.implicit_vjp(Pt, Pt, st, 1.0, dtt, dev(ca), dev(ce), Pt, Pt)
     gr.close()
+
+
+def test_batch_full_cascade_unaccepted_urad(G, orc):
+    """Cells whose URAD attempt stays the best without being accepted: their
+    conserved radiation, from the attempt's record, is that of their
+    primitives, and energy and momentum are conserved.  Both differ by
+    rounding alone: 100 operations, their errors raised up to gamma^2 = 8100
+    by the inversion, are 100 * 8100 * 2^-53 = 9e-11 of the cell's scale."""
+    say("case batch full cascade, URAD unaccepted")
+    n = 3001
+    pd, P, dt, ca, ce, Ui = _batch(orc, n, 4)
+    pd = dict(pd, roundoff=0, tol_accept=1e-14)
+    args = [dev(Ui), dev(P), dev(dt), dev(ca), dev(ce)]
+    Pg, Ug, it, st, err = (host(x) for x in G.implicit_source(pd, *args))
+    limited = ((st & G.ST_TYPE2_NEG) != 0) | \
+        (np.sqrt(1.0 + (Pg[9:12] ** 2).sum(0)) > 0.9 * pd["gamma_max"])
+    kept = ((st & G.ST_URAD) != 0) & ~limited & \
+        ((st & (G.ST_FAIL | G.ST_ENTROPY | G.ST_STAGED)) == 0)
+    late = kept & (err >= pd["tol_accept"])
+    say(f"  URAD solutions {kept.sum()}, unaccepted {late.sum()}")
+    assert late.sum() > 20
+    g0 = orc.geom(pd, 0.0, 0.0)
+    Uc = np.stack([orc.p2u(pd, g0, Pg[:, c]) for c in range(n)], axis=1)
+    em = [1, 2, 3, 4, 8, 9, 10, 11]
+    scale = np.abs(Ui[em]).sum(0) + np.abs(Uc[em]).sum(0)
+    d = np.abs(Ug - Uc)[8:12].max(0) / scale
+    t = np.abs(Ug[1:5] + Ug[8:12] - Ui[1:5] - Ui[8:12]).max(0) / scale
+    say(f"  radiation {d[late].max():.2e}, conservation {t[late].max():.2e}")
+    assert d[kept].max() < 9e-11 and t[kept].max() < 9e-11
