@@ -784,26 +784,29 @@ DEV void cell_setup(const M& m, const double Ui[12], double dt, double chi_abs,
   c.Si = NAN;
 }
 
+// known: the regime decided before (0, 1), -1 to decide it here.  A cell within
+// rounding of the threshold is decided once: another kernel's form of the same
+// expression may fall on the other side.
 template <class M>
 DEV void prepare(const M& m, const Phys& ph, const double Ui[12], const double Pg[12], double dt,
-                 double chi_abs, double chi_es, CellT<M>& c, Prep& pr) {
+                 double chi_abs, double chi_es, CellT<M>& c, Prep& pr, int known = -1) {
   cell_setup(m, Ui, dt, chi_abs, chi_es, c);
   pr.status = 0;
   // extreme radiation sub-dominance: R^t_t against the gas energy, or the
   // gas-frame radiation energy of the guess against u_g, below 10 eps
-  double Ehat;
-  {
+  pr.extreme = known > 0;
+  if (known < 0) {
     Vel<double> u, r;
     make_vel(m, Pg + 2, u);
     make_vel(m, Pg + 9, r);
     double w = 0.0;
 #pragma unroll
     for (int a = 0; a < 4; a++) w += r.ucon[a] * u.ucov[a];
-    Ehat = (4.0 / 3.0) * Pg[8] * w * w - Pg[8] * (1.0 / 3.0);
+    const double Ehat = (4.0 / 3.0) * Pg[8] * w * w - Pg[8] * (1.0 / 3.0);
+    const double tenEps = 10.0 * DBL_EPSILON;
+    pr.extreme = (::fabs(c.Ri[0]) <= tenEps * (::fabs(c.Tgi[0]) + ::fabs(c.Ri[0]))) ||
+                 (::fabs(Ehat) <= tenEps * (::fabs(Pg[1]) + ::fabs(Ehat)));
   }
-  const double tenEps = 10.0 * DBL_EPSILON;
-  pr.extreme = (::fabs(c.Ri[0]) <= tenEps * (::fabs(c.Tgi[0]) + ::fabs(c.Ri[0]))) ||
-               (::fabs(Ehat) <= tenEps * (::fabs(Pg[1]) + ::fabs(Ehat)));
   if (pr.extreme) pr.status |= GRRMHD_ST_EXTREME;
   // PMHD guess: prior primitives, or the MHD inversion of U(i) when the
   // temporal optical depth dt kappa_tot(P_n) < 2/3
@@ -976,12 +979,12 @@ DEV bool cold_allowed(const CellT<M>& c, const double Pg[12]) {
 template <class M>
 DEV bool cold_cell(const M& m, const Phys& ph, const Opts& o, const double Ui[12],
                    const double Pg[12], double dt, double chi_abs, double chi_es, int& iters,
-                   CellOut& out) {
+                   CellOut& out, int known = -1) {
   CellT<M> c;
   cell_setup(m, Ui, dt, chi_abs, chi_es, c);
   if (!cold_allowed(c, Pg)) return false;
   Prep pr;   // the set-up's status bits (EXTREME, C2P_FAIL) for the output
-  prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr);
+  prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr, known);
   c.cold = 1;
   const double x0[4] = {o.u_floor, Pg[2], Pg[3], Pg[4]};
   Best b;
@@ -1002,7 +1005,9 @@ DEV void cold_fallback(const M& m, const Phys& ph, const Opts& o, const double U
   if (!(out.status & GRRMHD_ST_FAIL) || !o.cold || !(o.u_floor > 0.0)) return;
   int iters = out.iters;
   CellOut oc;
-  if (cold_cell(m, ph, o, Ui, Pg, dt, chi_abs, chi_es, iters, oc)) out = oc;
+  if (cold_cell(m, ph, o, Ui, Pg, dt, chi_abs, chi_es, iters, oc,
+                (out.status & GRRMHD_ST_EXTREME) != 0))
+    out = oc;
   out.iters = iters;
 }
 
@@ -1028,6 +1033,15 @@ DEV void rec_store(const RecBuf& R, long slot, const Best& b, int iters, int sta
   R.i[R.cap + slot] = b.ok;
   R.i[2 * R.cap + slot] = iters;
 }
+
+// What the first kernel leaves of a listed cell: its first attempt, or, where
+// it is extreme, that it has none.
+DEV void rec_first(const RecBuf& R, long slot, bool extreme, const Best& b, int iters,
+                   int status = 0) {
+  if (extreme) R.i[R.cap + slot] = REC_EXTREME;
+  else rec_store(R, slot, b, iters, status);
+}
+DEV bool rec_extreme(const RecBuf& R, long slot) { return R.i[R.cap + slot] == REC_EXTREME; }
 
 // A batch cell's URAD attempt b beside the first attempt in its record: the
 // better one stays there, with its method and all iterations.
@@ -1083,10 +1097,10 @@ DEV bool implicit_fast(const M& m, const Phys& ph, const Opts& o, const double U
   return true;
 }
 
-// Full cascade for one cell (Sec. 4.10-4.11).  With R, a non-extreme cell
-// resumes after its first PMHD attempt, stored at list slot `slot` by the
-// kernel that ran it (that attempt was not accepted, else the cell would not
-// be in the cascade).
+// Full cascade for one cell (Sec. 4.10-4.11).  With R, a cell that the record
+// at list slot `slot` does not call extreme resumes after its first PMHD
+// attempt, stored there by the kernel that ran it (that attempt was not
+// accepted, else the cell would not be in the cascade).
 template <class M>
 DEV void implicit_cell(const M& m, const Phys& ph, const Opts& o, const double Ui[12],
                        const double Pg[12], double dt, double chi_abs, double chi_es,
@@ -1094,7 +1108,7 @@ DEV void implicit_cell(const M& m, const Phys& ph, const Opts& o, const double U
                        bool try_cold = true) {
   CellT<M> c;
   Prep pr;
-  prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr);
+  prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr, R ? rec_extreme(*R, slot) : -1);
   Best best;
   best.eT = INFINITY;
   best.ok = 0;
@@ -1399,7 +1413,7 @@ DEV void implicit_cell_full(const M& m, const Phys& ph, const Opts& o, const dou
                             long slot = 0, int resume = 0) {
   CellT<M> c;
   Prep pr;
-  prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr);
+  prepare(m, ph, Ui, Pg, dt, chi_abs, chi_es, c, pr, R ? rec_extreme(*R, slot) : -1);
   c.Si = Si / m.gdet;
   const double acc = accept_threshold(o);
   double Pradthin[12];

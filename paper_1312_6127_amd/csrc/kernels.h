@@ -1464,23 +1464,19 @@ DEV void store_out(const CellOut& o, long c, long Nst, double* P, double* U, int
   if (err) err[c] = o.err;
 }
 
-// A cell the fast path did not accept: to the work list, with its first
-// attempt (extreme cells have none).
+// A cell the fast path did not accept: to the work list, with what the rest of
+// the cascade starts from.
 DEV void to_cascade(bool need, bool extreme, int item, const Best& b, int iters, const Work& W,
                     int status = 0) {
   const long slot = wave_append(need, item, W.counter, W.list);
-  if (slot >= 0 && !extreme) rec_store(W.rec, slot, b, iters, status);
+  if (slot >= 0) rec_first(W.rec, slot, extreme, b, iters, status);
 }
 
-// The same in a batch: extreme cells to the list D as well, their slots of W
-// marked.
+// The same in a batch: extreme cells to the list D as well.
 DEV void to_batch_cascade(bool need, bool extreme, int item, const Best& b, int iters, int status,
                           const Work& W, const Work& D) {
   const long slot = wave_append(need, item, W.counter, W.list);
-  if (slot >= 0) {
-    if (extreme) W.rec.i[W.rec.cap + slot] = REC_EXTREME;
-    else rec_store(W.rec, slot, b, iters, status);
-  }
+  if (slot >= 0) rec_first(W.rec, slot, extreme, b, iters, status);
   wave_append(need && extreme, item, D.counter, D.list);
 }
 
@@ -1826,7 +1822,7 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
     if (need) {
       if (got >= cnt) {
         exhausted = true;
-      } else if (W.rec.i[W.rec.cap + got] != REC_EXTREME) {
+      } else if (!rec_extreme(W.rec, got)) {
         slot = got;
         const long item = W.list[slot];
         double Ui[12];
@@ -1918,7 +1914,7 @@ __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict_
        slot += (long)gridDim.x * blockDim.x) {
     Best best;
     int its;
-    if (W.rec.i[W.rec.cap + slot] == REC_EXTREME) continue;
+    if (rec_extreme(W.rec, slot)) continue;
     rec_load(W.rec, slot, best, its);
     const int st = W.rec.i[slot] >> REC_STATUS;
     const int bm = best.ok ? best.ok >> 1 : -1;

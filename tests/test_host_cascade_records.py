@@ -49,3 +49,47 @@ def test_full_cascade_resumes_from_the_record(orc, tmp_path, accept):
     vals = _run(tmp_path, "cascade_records_check.cpp", str(tmp_path / "batch.bin"))
     assert vals["resumed"] > 300 and vals["urad"] > 50, vals
     assert vals["differing"] == 0, vals
+
+
+def test_regime_is_decided_once(orc, tmp_path):
+    """Fast gas on a Kerr-Schild grid, its radiation a few ulp about 10 eps of
+    the gas energy; attempts of one step, so that the cells on the other side
+    are listed too."""
+    n = 4000
+    pd, *_ = I.accretion_disk(n=(16, 8, 1))
+    r = np.random.default_rng(3)
+    sym = [(a, b) for a in range(4) for b in range(a, 4)]
+    rows = []
+    for c in range(n):
+        g = orc.geom(pd, r.uniform(0.3, 3.0), r.uniform(0.4, 1.2))
+        lo, up, gdet, alpha = orc.geom_arrays(g)
+        P = np.zeros(12)
+        P[0], P[1] = 1.0, 10.0 ** r.uniform(-4, 0)
+        s = 1.0 / np.sqrt(np.diag(lo)[1:])
+        P[2:5] = 10.0 ** r.uniform(0, 1.5) * r.standard_normal(3) * s
+        P[9:12] = P[2:5] + r.standard_normal(3) * s
+
+        def vel(ut):
+            gm = np.sqrt(1.0 + ut @ lo[1:, 1:] @ ut)
+            u = np.concatenate([[0.0], ut]) - gm * alpha * up[0]
+            u[0] = gm / alpha
+            return u
+
+        w = vel(P[2:5]) @ lo @ vel(P[9:12])
+        k = (4.0 * w * w - 1.0) / 3.0
+        eps = 10.0 * np.finfo(float).eps
+        P[8] = eps * P[1] / (1.0 - eps) / k * (1.0 + r.integers(-8, 9) * 2.0 ** -52)
+        U = orc.p2u(pd, g, P)
+        U[8:] *= 1e16   # the explicit state's radiation is not negligible
+        rows.append(np.concatenate([[lo[a, b] for a, b in sym], [up[a, b] for a, b in sym],
+                                    [gdet, alpha], U, P, [1e-3]]))
+    with open(tmp_path / "cells.bin", "wb") as f:
+        np.array([n], dtype=np.int64).tofile(f)
+        np.array([pd["gam"], pd["arad"], pd["gamma_max"], pd["tol_pmhd"], pd["tol_urad"],
+                  pd["tol_accept"], pd["tol_fail"], 1, pd["roundoff"]],
+                 dtype=np.float64).tofile(f)
+        np.array(rows).tofile(f)
+    vals = _run(tmp_path, "cascade_extreme_check.cpp", str(tmp_path / "cells.bin"))
+    assert vals["extreme"] > 500 and vals["cells"] - vals["extreme"] > 100, vals
+    assert vals["split"] > 100, vals
+    assert vals["differing"] == 0, vals
