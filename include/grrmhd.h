@@ -452,9 +452,9 @@ int grrmhd_implicit_source(const grrmhd_params *p, long n, const double *U_expl,
  * allocation, for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
  * per-cell form's scratch memory (counters, lane statistics, cascade list
- * with first-attempt records, deferred-cell and cold-cell lists, 160 bytes
+ * with first-attempt records, deferred-cell and cold-cell lists, 128 bytes
  * per cell) lives in a static device array sized for GRRMHD_NOALLOC_MAX_CELLS
- * cells (40 MiB); each device the library runs on holds its own copy until
+ * cells (32 MiB); each device the library runs on holds its own copy until
  * the process ends.  Its address is looked up on the first call on each
  * device (the current HIP device, which must own hip_stream); no call
  * allocates, frees or calls an allocating library routine.  Arguments,

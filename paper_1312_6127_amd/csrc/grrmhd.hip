@@ -54,7 +54,7 @@ static constexpr size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
 // from `base` (256-byte aligned); returns the bytes used.
 static constexpr size_t cascade_bytes(size_t cap) {
   return round256(sizeof(int) * cap) + round256(sizeof(double) * 13 * cap) +
-         round256(sizeof(int) * 3 * cap);
+         round256(sizeof(int) * 2 * cap);
 }
 
 static void cascade_layout(char* base, size_t cap, Work& W) {
@@ -62,7 +62,7 @@ static void cascade_layout(char* base, size_t cap, Work& W) {
   W.rec.d = (double*)(base + round256(sizeof(int) * cap));
   W.rec.i = (int*)(base + round256(sizeof(int) * cap) + round256(sizeof(double) * 13 * cap));
   W.rec.cap = (long)cap;
-  W.rec.x = nullptr;
+  W.extreme = nullptr;
 }
 
 static thread_local std::string g_err;
@@ -2010,15 +2010,12 @@ extern "C" int grrmhd_step_adjoint_saved(grrmhd_grid* g, const double* chi_abs,
 }
 
 // Workspace of the batched solve: [0, 256) counters (list length @0, queue
-// cursor @4, two queue lengths @8, cascade cursor @16, deferred and cold
-// list lengths @20 and @24, stats @64), then the cascade list and records,
-// the deferred (extreme) and cold lists, and for the per-iteration form two
-// queues and the lane state.
-// workspace of the per-cell batched form: counters and statistics, cascade
-// list with first-attempt records, deferred-cell and cold-cell lists
-static constexpr size_t batch_ws_bytes(size_t n) {
-  return 256 + cascade_bytes(n) + round256(sizeof(double) * 4 * n) + 2 * round256(sizeof(int) * n);
-}
+// cursor @4, two queue lengths @8, cascade cursor @16, lengths of the extreme
+// and cold lists @20 and @24, stats @64), then per cell a record (14 doubles, 2
+// ints), the cascade list (the extreme cells from its end) and the cold list,
+// and for the per-iteration form two queues and the lane state.
+static constexpr size_t BATCH_CELL_BYTES = 14 * sizeof(double) + 4 * sizeof(int);
+static constexpr size_t batch_ws_bytes(size_t n) { return 256 + round256(BATCH_CELL_BYTES * n); }
 
 extern "C" size_t grrmhd_implicit_source_workspace_bytes_ex(long n, int mode) {
   if (n <= 0) return 0;
@@ -2067,17 +2064,16 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   int* qc = W.counter + 2;            // per-iteration queue lengths (2)
   int* cursor = W.counter + 4;        // cascade queue cursor
   W.stats = (unsigned long long*)(base + 64);
-  cascade_layout(base + 256, (size_t)n, W);
-  W.rec.x = (double*)(base + 256 + cascade_bytes((size_t)n));
-  // extreme cells of the cascade
-  Work D = W;
-  D.counter = W.counter + 5;
-  D.list = (int*)((char*)W.rec.x + round256(sizeof(double) * 4 * (size_t)n));
+  W.rec.d = (double*)(base + 256);
+  W.rec.i = (int*)(W.rec.d + 14 * (size_t)n);
+  W.rec.cap = n;
+  W.list = W.rec.i + 2 * (size_t)n;
+  W.extreme = W.counter + 5;
   // cells the cascade leaves without an energy solution, for the cold limit
   Work K = W;
   K.counter = W.counter + 6;
-  K.list = (int*)((char*)D.list + round256(sizeof(int) * (size_t)n));
-  char* extra = (char*)K.list + round256(sizeof(int) * (size_t)n);
+  K.list = W.list + n;
+  char* extra = base + batch_ws_bytes((size_t)n);
   if (mode == GRRMHD_IMPLICIT_PERSISTENT) {
     if (block != 64 && block != 128 && block != 256) return fail(GRRMHD_EINVAL, "block must be 64, 128 or 256");
     if (waves_per_cu < 1 || waves_per_cu > 64) return fail(GRRMHD_EINVAL, "waves_per_cu out of [1, 64]");
@@ -2090,13 +2086,13 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
   if (mode == GRRMHD_IMPLICIT_PER_CELL) {
     hipLaunchKernelGGL(k_implicit_batch<Dense>, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
-                       dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, D);
+                       dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W);
     LAUNCHCHK();
   } else if (mode == GRRMHD_IMPLICIT_PERSISTENT) {
     const long waves = (long)ncu * waves_per_cu;
     const long blocks = std::max<long>(1, std::min<long>(waves * 64 / block, nblocks(n, block)));
     hipLaunchKernelGGL(k_implicit_persist<Dense>, dim3((unsigned)blocks), dim3(block), 0, s, C, n, U_expl,
-                       P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, next, W, D);
+                       P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, next, W);
     LAUNCHCHK();
   } else {
     const size_t qb = round256(sizeof(int) * (size_t)n);
@@ -2105,7 +2101,7 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
     double* sd = (double*)(extra + 2 * qb);
     int* si = (int*)(extra + 2 * qb + round256(sizeof(double) * LS_ND * (size_t)n));
     hipLaunchKernelGGL(k_iter_start<Dense>, dim3(nblocks(n, 64)), dim3(64), 0, s, C, n, U_expl, P_guess,
-                       dt_cell, chi_abs, chi_es, sd, si, qc, q0, W, D);
+                       dt_cell, chi_abs, chi_es, sd, si, qc, q0, W);
     LAUNCHCHK();
     // every attempt ends within max_iter trips (+3 round-off trips are inside it)
     for (int t = 0; t <= C.max_iter; t++) {
@@ -2126,14 +2122,14 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   // registers per lane), then the outputs
   const long cwaves = std::max<long>(1, std::min<long>(4L * ncu, n));
   hipLaunchKernelGGL(k_cascade_urad<Dense>, dim3((unsigned)cwaves), dim3(64), 0, s, C, n, U_expl, P_guess,
-                     dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, cursor, D, K);
+                     dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, cursor, K);
   LAUNCHCHK();
   hipLaunchKernelGGL(k_cascade_finish<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
                      P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, K);
   LAUNCHCHK();
   if (C.cascade) {
     hipLaunchKernelGGL(k_implicit_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
-                       P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, D);
+                       P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W);
     LAUNCHCHK();
   }
   // the full cascade's rest for the cells the PMHD and URAD attempts left
@@ -2152,19 +2148,20 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
 }
 
 // stats[0..1] at `src`, summed over `slots` of them, and the list length at
-// `cnt` into out[0..2]
-static int read_stats(const unsigned long long* src, int slots, const int* cnt,
+// `cnt` (with that of a batch's extreme cells) into out[0..2]
+static int read_stats(const unsigned long long* src, int slots, const int* cnt, const int* extreme,
                       unsigned long long out[3], hipStream_t s) {
   unsigned long long st[GRRMHD_STAT_SLOTS * GRRMHD_STAT_STRIDE];
-  int c = 0;
+  int c = 0, e = 0;
   const size_t used = 2 + (size_t)(slots - 1) * GRRMHD_STAT_STRIDE;
   HIPCHK(hipMemcpyAsync(st, src, 8 * used, hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(&c, cnt, sizeof(int), hipMemcpyDeviceToHost, s));
+  if (extreme) HIPCHK(hipMemcpyAsync(&e, extreme, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   out[0] = out[1] = 0;
   for (int i = 0; i < slots; i++)
     for (int q = 0; q < 2; q++) out[q] += st[i * GRRMHD_STAT_STRIDE + q];
-  out[2] = (unsigned long long)c;
+  out[2] = (unsigned long long)c + (unsigned long long)e;
   return 0;
 }
 
@@ -2202,7 +2199,7 @@ extern "C" int grrmhd_implicit_time(grrmhd_grid* g, double* total_ms, int* launc
 extern "C" int grrmhd_implicit_stats(grrmhd_grid* g, unsigned long long out[3]) {
   if (!g || !out) return fail(GRRMHD_EINVAL, "NULL argument");
   HIPCHK(hipSetDevice(g->device));
-  return read_stats(g->W.stats, GRRMHD_STAT_SLOTS, g->W.counter, out, g->stream);
+  return read_stats(g->W.stats, GRRMHD_STAT_SLOTS, g->W.counter, nullptr, out, g->stream);
 }
 
 extern "C" int grrmhd_implicit_source_stats(const void* workspace, unsigned long long out[3],
@@ -2210,8 +2207,8 @@ extern "C" int grrmhd_implicit_source_stats(const void* workspace, unsigned long
   if (!workspace || !out) return fail(GRRMHD_EINVAL, "NULL argument");
   if (((uintptr_t)workspace) & 255) return fail(GRRMHD_EINVAL, "workspace must be 256-byte aligned");
   const char* base = (const char*)workspace;
-  return read_stats((const unsigned long long*)(base + 64), 1, (const int*)base, out,
-                    (hipStream_t)hip_stream);
+  return read_stats((const unsigned long long*)(base + 64), 1, (const int*)base,
+                    (const int*)base + 5, out, (hipStream_t)hip_stream);
 }
 
 extern "C" int grrmhd_implicit_source_cascade_stats(const void* workspace,

@@ -1013,63 +1013,71 @@ DEV void cold_fallback(const M& m, const Phys& ph, const Opts& o, const double U
 
 // Result of a cell's first PMHD attempt, kept per cascade-list slot so that
 // the cascade resumes where the first attempt ended: field-major [f][cap],
-// d = P[12], e_T; i = radiation flags (and the cell's status bits from
-// REC_STATUS up), ok (REC_EXTREME: no attempt was made), iterations.  A batch
-// keeps its URAD attempts' results there too (ok: 1 | method << 1), with their
-// iterates in x.
+// d = P[12], e_T; i = flags (the limiters', the attempt's ok and method from
+// REC_OK up, REC_EXTREME where the cell is extreme and no attempt was made, its
+// status bits from REC_STATUS up), iterations.  A batch keeps its URAD
+// attempts' results there too, their iterates in place of P's field (the
+// explicit state's, which every reader has) and in a 14th row of d: at 120
+// bytes with the two words of its lists a cell of a batch takes 128.
 struct RecBuf {
   double* d;
   int* i;
   long cap;
-  double* x;   // [4][cap], batches alone (a grid's records hold PMHD attempts)
 };
-enum { REC_STATUS = 8, REC_EXTREME = -1 };
+enum { REC_OK = 2, REC_EXTREME = 1 << 5, REC_STATUS = 8 };
 
 DEV void rec_store(const RecBuf& R, long slot, const Best& b, int iters, int status = 0) {
 #pragma unroll
   for (int q = 0; q < 12; q++) R.d[q * R.cap + slot] = b.P[q];
   R.d[12 * R.cap + slot] = b.eT;
-  R.i[slot] = b.radflags | status << REC_STATUS;
-  R.i[R.cap + slot] = b.ok;
-  R.i[2 * R.cap + slot] = iters;
+  R.i[slot] = (b.radflags & 3) | b.ok << REC_OK | status << REC_STATUS;
+  R.i[R.cap + slot] = iters;
 }
 
-// What the first kernel leaves of a listed cell: its first attempt, or, where
-// it is extreme, that it has none.
-DEV void rec_first(const RecBuf& R, long slot, bool extreme, const Best& b, int iters,
-                   int status = 0) {
-  if (extreme) R.i[R.cap + slot] = REC_EXTREME;
-  else rec_store(R, slot, b, iters, status);
+// What the first kernel leaves of a grid's listed cell: its first attempt, or,
+// where it is extreme, that it has none.
+DEV void rec_first(const RecBuf& R, long slot, bool extreme, const Best& b, int iters) {
+  if (extreme) R.i[slot] = REC_EXTREME;
+  else rec_store(R, slot, b, iters);
 }
-DEV bool rec_extreme(const RecBuf& R, long slot) { return R.i[R.cap + slot] == REC_EXTREME; }
+DEV bool rec_extreme(const RecBuf& R, long slot) { return (R.i[slot] & REC_EXTREME) != 0; }
 
 // A batch cell's URAD attempt b beside the first attempt in its record: the
 // better one stays there, with its method and all iterations.
 DEV void rec_urad(const RecBuf& R, long slot, Best& b, int iters) {
-  int& ok = R.i[R.cap + slot];
-  const double e0 = ok ? R.d[12 * R.cap + slot] : INFINITY;
+  const int f = R.i[slot];
+  const double e0 = (f >> REC_OK & 1) ? R.d[12 * R.cap + slot] : INFINITY;
   if (b.ok && b.eT < e0) {
     b.ok = 1 | M_URAD << 1;
-    rec_store(R, slot, b, iters, R.i[slot] >> REC_STATUS);
 #pragma unroll
-    for (int k = 0; k < 4; k++) R.x[k * R.cap + slot] = b.x[k];
+    for (int k = 0; k < 3; k++) b.P[5 + k] = b.x[k];
+    R.d[13 * R.cap + slot] = b.x[3];
+    rec_store(R, slot, b, iters, f >> REC_STATUS);
   } else {
-    ok = ok ? 1 | M_PMHD << 1 : 0;
-    R.i[2 * R.cap + slot] = iters;
+    R.i[R.cap + slot] = iters;
   }
 }
 
-// With a URAD attempt's iterate, which its conserved radiation is.
-DEV void rec_load(const RecBuf& R, long slot, Best& b, int& iters) {
+// B: the cell's explicit field, given where the record may be a URAD attempt's
+// (b.ok: 1 | method << 1); x, its iterate, is the conserved radiation.
+DEV void rec_load(const RecBuf& R, long slot, Best& b, int& iters, const double* B = nullptr) {
 #pragma unroll
   for (int q = 0; q < 12; q++) b.P[q] = R.d[q * R.cap + slot];
   b.eT = R.d[12 * R.cap + slot];
-  b.radflags = R.i[slot] & ((1 << REC_STATUS) - 1);
-  b.ok = R.i[R.cap + slot];
-  iters = R.i[2 * R.cap + slot];
-  const bool urad = b.ok >> 1 == M_URAD;
+  const int f = R.i[slot];
+  b.radflags = f & ((1 << REC_OK) - 1);
+  b.ok = f >> REC_OK & 7;
+  iters = R.i[R.cap + slot];
 #pragma unroll
-  for (int k = 0; k < 4; k++) b.x[k] = urad ? R.x[k * R.cap + slot] : 0.0;
+  for (int k = 0; k < 4; k++) b.x[k] = 0.0;
+  if (B && b.ok >> 1 == M_URAD) {
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+      b.x[k] = b.P[5 + k];
+      b.P[5 + k] = B[k];
+    }
+    b.x[3] = R.d[13 * R.cap + slot];
+  }
 }
 
 // Common case: not extreme, first PMHD attempt accepted.  Returns false when
@@ -1432,7 +1440,7 @@ DEV void implicit_cell_full(const M& m, const Phys& ph, const Opts& o, const dou
   int mE = -1, sE = 0, iters = 0, skip = 0;
   if (R && resume && !pr.extreme) {
     Best b;
-    rec_load(*R, slot, b, iters);
+    rec_load(*R, slot, b, iters, c.B);
     const int meth = b.ok >> 1;
     b.ok &= 1;
     if (b.ok) {

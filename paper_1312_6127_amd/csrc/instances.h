@@ -47,21 +47,21 @@
 #define INST_BATCH(X, Geo)                                                                        \
   X template __global__ void k_implicit_batch<Geo>(Ctx, long, const double*, const double*,       \
       const double*, const double*, const double*, double*, double*, int*, int*, double*,         \
-      Work, Work);                                                                                \
+      Work);                                                                                      \
   X template __global__ void k_cold_batch_list<Geo>(Ctx, long, const double*, const double*,      \
       const double*, const double*, const double*, double*, double*, int*, int*, double*,         \
       Work);                                                                                      \
   X template __global__ void k_cascade_urad<Geo>(Ctx, long, const double*, const double*,         \
       const double*, const double*, const double*, double*, double*, int*, int*, double*,         \
-      Work, int*, Work, Work);                                                                    \
+      Work, int*, Work);                                                                          \
   X template __global__ void k_cascade_finish<Geo>(Ctx, long, const double*, const double*,       \
       const double*, const double*, const double*, double*, double*, int*, int*, double*,         \
       Work, Work);                                                                                \
   X template __global__ void k_implicit_persist<Geo>(Ctx, long, const double*, const              \
       double*, const double*, const double*, const double*, double*, double*, int*, int*,         \
-      double*, int*, Work, Work);                                                                 \
+      double*, int*, Work);                                                                       \
   X template __global__ void k_iter_start<Geo>(Ctx, long, const double*, const double*,           \
-      const double*, const double*, const double*, double*, int*, int*, int*, Work, Work);        \
+      const double*, const double*, const double*, double*, int*, int*, int*, Work);              \
   X template __global__ void k_iter_step<Geo>(Ctx, long, const double*, const double*, const      \
       double*, const double*, double*, int*, const int*, const int*, int*, int*, double*,         \
       double*, int*, int*, double*, Work);

@@ -1422,6 +1422,7 @@ struct Work {
   int* list;
   unsigned long long* stats;
   RecBuf rec;
+  int* extreme;        // batches: number of extreme cells, listed from list's end
 };
 
 // A grid's launches spread their lane statistics over GRRMHD_STAT_SLOTS pairs,
@@ -1466,19 +1467,21 @@ DEV void store_out(const CellOut& o, long c, long Nst, double* P, double* U, int
 
 // A cell the fast path did not accept: to the work list, with what the rest of
 // the cascade starts from.
-DEV void to_cascade(bool need, bool extreme, int item, const Best& b, int iters, const Work& W,
-                    int status = 0) {
+DEV void to_cascade(bool need, bool extreme, int item, const Best& b, int iters, const Work& W) {
   const long slot = wave_append(need, item, W.counter, W.list);
-  if (slot >= 0) rec_first(W.rec, slot, extreme, b, iters, status);
+  if (slot >= 0) rec_first(W.rec, slot, extreme, b, iters);
 }
 
-// The same in a batch: extreme cells to the list D as well.
+// The same in a batch: extreme cells, which have no record, from the list's
+// end down.
 DEV void to_batch_cascade(bool need, bool extreme, int item, const Best& b, int iters, int status,
-                          const Work& W, const Work& D) {
-  const long slot = wave_append(need, item, W.counter, W.list);
-  if (slot >= 0) rec_first(W.rec, slot, extreme, b, iters, status);
-  wave_append(need && extreme, item, D.counter, D.list);
+                          const Work& W) {
+  const long slot = wave_append(need && !extreme, item, W.counter, W.list);
+  if (slot >= 0) rec_store(W.rec, slot, b, iters, status);
+  const long e = wave_fetch(need && extreme, W.extreme);
+  if (e >= 0) W.list[W.rec.cap - 1 - e] = item;
 }
+DEV long extreme_cell(const Work& W, long e) { return W.list[W.rec.cap - 1 - e]; }
 
 // Common path of the implicit solve at interior cells; cells that need the
 // full cascade go to the work list (index into the interior enumeration).
@@ -1593,7 +1596,7 @@ __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ U
                                         const double* __restrict__ chi_es,
                                         double* __restrict__ Po, double* __restrict__ Uo,
                                         int* __restrict__ iters, int* __restrict__ status,
-                                        double* __restrict__ err, Work W, Work D) {
+                                        double* __restrict__ err, Work W) {
   const long c = (long)blockIdx.x * blockDim.x + threadIdx.x;
   bool need = false, extreme = false;
   Best b;
@@ -1616,7 +1619,7 @@ __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ U
     st0 = o.status;
   }
   wave_stats(trips, W.stats);
-  to_batch_cascade(need, extreme, (int)c, b, it, st0, W, D);
+  to_batch_cascade(need, extreme, (int)c, b, it, st0, W);
 }
 
 // A batch's list entries over a grid of wavefronts: a list shorter than the
@@ -1632,18 +1635,18 @@ DEV long list_first(int cnt, long& step) {
 }
 
 // Extreme cells of a batch (radiation far below the gas: URAD first, then PMHD
-// from scratch), listed in D, one thread each; those left without an energy
+// from scratch), one thread each; those left without an energy
 // solution go on to the cold limit's list K.
 DEV void extreme_cells(const Ctx& C, long n, const double* __restrict__ Ui_,
                        const double* __restrict__ Pg_, const double* __restrict__ dtc,
                        const double* __restrict__ chi_abs, const double* __restrict__ chi_es,
                        double* __restrict__ Po, double* __restrict__ Uo, int* __restrict__ iters,
-                       int* __restrict__ status, double* __restrict__ err, const Work& D,
+                       int* __restrict__ status, double* __restrict__ err, const Work& W,
                        const Work& K) {
-  const int cnt = *D.counter;
+  const int cnt = *W.extreme;
   long step;
   for (long w = list_first(cnt, step); w < cnt; w += step) {
-    const long c = D.list[w];
+    const long c = extreme_cell(W, w);
     Metric m;
     flat_metric(m);
     double Ui[12], Pg[12];
@@ -1676,11 +1679,11 @@ __global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __rest
                                              const double* __restrict__ chi_es,
                                              double* __restrict__ Po, double* __restrict__ Uo,
                                              int* __restrict__ iters, int* __restrict__ status,
-                                             double* __restrict__ err, Work D) {
-  const int cnt = *D.counter;
+                                             double* __restrict__ err, Work W) {
+  const int cnt = *W.extreme;
   for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < cnt;
        w += (long)gridDim.x * blockDim.x) {
-    const long c = D.list[w];
+    const long c = extreme_cell(W, w);
     Metric m;
     flat_metric(m);
     double Ui[12], Pg[12];
@@ -1795,10 +1798,9 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
                                       const double* __restrict__ chi_es,
                                       double* __restrict__ Po, double* __restrict__ Uo,
                                       int* __restrict__ iters, int* __restrict__ status,
-                                      double* __restrict__ err, Work W, int* cursor, Work D,
-                                      Work K) {
+                                      double* __restrict__ err, Work W, int* cursor, Work K) {
   if (!C.cascade)
-    extreme_cells(C, n, Ui_, Pg_, dtc, chi_abs, chi_es, Po, Uo, iters, status, err, D, K);
+    extreme_cells(C, n, Ui_, Pg_, dtc, chi_abs, chi_es, Po, Uo, iters, status, err, W, K);
   const Phys ph = make_phys(C);
   const Opts o = make_opts(C);
   Metric m;
@@ -1810,7 +1812,7 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
   long slot = 0;
   int stage = UE_NONE;
   // wavefronts that had an extreme cell come late
-  const int busy = C.cascade ? 0 : ::min(*D.counter, (int)gridDim.x / 2);
+  const int busy = C.cascade ? 0 : ::min(*W.extreme, (int)gridDim.x / 2);
   const int width = ::min((cnt + (int)gridDim.x - busy - 1) / ((int)gridDim.x - busy), 64);
   const bool apart = width < 64;
   const int steps = apart ? 60 : GRRMHD_URAD_STEPS;
@@ -1822,7 +1824,7 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
     if (need) {
       if (got >= cnt) {
         exhausted = true;
-      } else if (!rec_extreme(W.rec, got)) {
+      } else {
         slot = got;
         const long item = W.list[slot];
         double Ui[12];
@@ -1912,18 +1914,17 @@ __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict_
   const int cnt = *W.counter;
   for (long slot = (long)blockIdx.x * blockDim.x + threadIdx.x; slot < cnt;
        slot += (long)gridDim.x * blockDim.x) {
-    Best best;
-    int its;
-    if (rec_extreme(W.rec, slot)) continue;
-    rec_load(W.rec, slot, best, its);
-    const int st = W.rec.i[slot] >> REC_STATUS;
-    const int bm = best.ok ? best.ok >> 1 : -1;
     const long item = W.list[slot];
     double Ui[12], Pg[12];
 #pragma unroll
     for (int q = 0; q < 12; q++) Ui[q] = Ui_[q * n + item];
     Cell c;
     cell_setup(m, Ui, dtc[item], chi_abs[item], chi_es[item], c);
+    Best best;
+    int its;
+    rec_load(W.rec, slot, best, its, c.B);
+    const int st = W.rec.i[slot] >> REC_STATUS;
+    const int bm = best.ok ? best.ok >> 1 : -1;
     CellOut out;
     const bool done = bm >= 0 && best.eT < accept_threshold(o);
     if (!done) {
@@ -2228,7 +2229,7 @@ __global__ void LBP k_implicit_persist(Ctx C, long n, const double* __restrict__
                                        const double* __restrict__ chi_es,
                                        double* __restrict__ Po, double* __restrict__ Uo,
                                        int* __restrict__ iters, int* __restrict__ status,
-                                       double* __restrict__ err, int* next, Work W, Work D) {
+                                       double* __restrict__ err, int* next, Work W) {
   const Phys ph = make_phys(C);
   const Opts o = make_opts(C);
   const double thr = accept_threshold(o);
@@ -2300,7 +2301,7 @@ __global__ void LBP k_implicit_persist(Ctx C, long n, const double* __restrict__
         tolist = true;
       active = false;
     }
-    to_batch_cascade(tolist, extreme, (int)item, L.best, L.iters, L.status, W, D);
+    to_batch_cascade(tolist, extreme, (int)item, L.best, L.iters, L.status, W);
     if (!__any(active) && __all(exhausted)) break;
   }
   if ((threadIdx.x & 63) == 0 && useful) {
@@ -2378,7 +2379,7 @@ __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui
                                     const double* __restrict__ Pg_, const double* __restrict__ dtc,
                                     const double* __restrict__ chi_abs,
                                     const double* __restrict__ chi_es, double* sd, int* si,
-                                    int* qcount, int* queue, Work W, Work D) {
+                                    int* qcount, int* queue, Work W) {
   const long cidx = (long)blockIdx.x * blockDim.x + threadIdx.x;
   bool act = false, tolist = false, extreme = false;
   int trips = 0;
@@ -2413,7 +2414,7 @@ __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui
   }
   wave_stats(trips, W.stats);
   wave_append(act, (int)cidx, qcount, queue);
-  to_batch_cascade(tolist, extreme, (int)cidx, L.best, L.iters, L.status, W, D);
+  to_batch_cascade(tolist, extreme, (int)cidx, L.best, L.iters, L.status, W);
 }
 
 // one Newton trip for every queued cell
@@ -2470,6 +2471,6 @@ __global__ void LB(64) k_iter_step(Ctx C, long n, const double* __restrict__ Ui_
     }
     wave_stats(trips, W.stats);
     wave_append(keepgoing, (int)cidx, qout_count, qout);
-    to_cascade(tolist, false, (int)cidx, L.best, L.iters, W, L.status);
+    to_batch_cascade(tolist, false, (int)cidx, L.best, L.iters, L.status, W);
   }
 }

@@ -70,11 +70,10 @@ int main(int argc, char** argv) {
         old.radflags = 0;
         old.ok = 1;
         double rd[13];
-        int ri[3];
+        int ri[2];
         RecBuf R;
         R.d = rd;
         R.i = ri;
-        R.x = nullptr;
         R.cap = 1;
         rec_store(R, 0, old, 7);
         rec_first(R, 0, ext, b, it);

@@ -56,12 +56,11 @@ int main(int argc, char** argv) {
     int it = 0, tr = 0;
     bool ext = false;
     if (implicit_fast(m, ph, o, u, p, dt[cc], ca[cc], ce[cc], out, b, it, ext, tr) || ext) continue;
-    double rd[13], rx[4];
-    int ri[3];
+    double rd[14];
+    int ri[2];
     RecBuf R;
     R.d = rd;
     R.i = ri;
-    R.x = rx;
     R.cap = 1;
     rec_store(R, 0, b, it, out.status);
     // the URAD attempt

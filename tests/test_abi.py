@@ -97,3 +97,19 @@ def test_batch_workspace_sizes(L):
         assert a >= 256 + 4 * n + 13 * 8 * n + 3 * 4 * n + 2 * 4 * n and a % 256 == 0
         # two queues, 47 doubles and 8 ints of lane state per cell
         assert c >= a + 8 * n + 47 * 8 * n + 8 * 4 * n
+
+
+def test_batch_workspace_of_128_bytes_a_cell(L):
+    """A caller that keeps a workspace of 128 bytes a cell, each of its seven
+    parts rounded up to 256 bytes, can go on doing so."""
+    from paper_1312_6127_amd import grrmhd as G
+
+    def up(b):
+        return -(-b // 256) * 256
+
+    f = L.grrmhd_implicit_source_workspace_bytes_ex
+    for n in (1, 2, 17, 63, 64, 65, 1000, 4099, 1 << 20, (1 << 24) + 1):
+        old = 256 + 3 * up(4 * n) + up(13 * 8 * n) + up(3 * 4 * n)
+        lanes = 2 * up(4 * n) + up(47 * 8 * n) + up(13 * 4 * n)
+        assert f(n, G.PER_CELL) <= old and f(n, G.PERSISTENT) <= old
+        assert f(n, G.PER_ITERATION) <= old + lanes
