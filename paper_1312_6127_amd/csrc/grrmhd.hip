@@ -545,10 +545,20 @@ static int launch_flattener(grrmhd_grid* g, const double* P, const double* ca, c
 static void add_faces(FluxSegs& S, const FaceRange& r, int D) {
   S.R[S.n] = r;
   S.D[S.n++] = D;
-  S.pieces = std::max(S.pieces, (int)nblocks((long)r.cnt[0] * r.cnt[1], FLUX_BLOCK));
-  S.nk = std::max(S.nk, r.cnt[2]);
 }
-static dim3 flux_blocks(const FluxSegs& S) { return dim3((unsigned)S.pieces * S.nk * S.n); }
+// sets the order of the launch in S too
+static dim3 flux_blocks(FluxSegs& S) {
+  long plane = 0, nk = 0, total = 0;
+  for (int s = 0; s < S.n; s++) {
+    plane = std::max(plane, (long)S.R[s].cnt[0] * S.R[s].cnt[1]);
+    nk = std::max(nk, (long)S.R[s].cnt[2]);
+    total = std::max(total, S.R[s].total);
+  }
+  S.flat = thin_planes(plane, nk, FLUX_BLOCK);
+  S.pieces = (int)nblocks(S.flat ? total : plane, FLUX_BLOCK);
+  S.nk = S.flat ? 1 : (int)nk;
+  return dim3((unsigned)S.pieces * S.nk * S.n);
+}
 
 // The faces that set a step's dt keep the dense form: a gradient taken at that
 // dt moves by 1e-6 with its last bit.
@@ -569,7 +579,6 @@ static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const doubl
   // faces of every direction, FP64 part and FP32 part (split at mixed_i)
   FluxSegs S64, S32;
   S64.n = S32.n = 0;
-  S64.pieces = S32.pieces = S64.nk = S32.nk = 0;
   for (int d = 0; d < 3; d++) {
     if (C.n[d] == 1) continue;
     FaceRange r64, r32;
@@ -577,20 +586,21 @@ static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const doubl
     if (r64.total > 0) add_faces(S64, r64, d + 1);
     if (r32.total > 0) add_faces(S32, r32, d + 1);
   }
+  const dim3 b64 = flux_blocks(S64), b32 = flux_blocks(S32);
   if (Bf) {
     const double* flp = (const double*)g->flat;
     if (S64.n > 0) {
       if (Fs)
-        hipLaunchKernelGGL(STAG_KERNEL(g, true), flux_blocks(S64), dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL(STAG_KERNEL(g, true), b64, dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL(STAG_KERNEL(g, false), flux_blocks(S64), dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL(STAG_KERNEL(g, false), b64, dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
     if (S32.n > 0) {
       if (Fs)
-        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, true>), flux_blocks(S32), dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, true>), b32, dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, false>), flux_blocks(S32), dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, false>), b32, dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
     // four-state corner EMFs at [ng, ng+n] on each active axis
@@ -614,19 +624,19 @@ static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const doubl
   }
   if (S64.n > 0) {
     if (Fs)
-      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all_s, double), flux_blocks(S64), dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all_s, double), b64, dim3(FLUX_BLOCK), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all, double), flux_blocks(S64), dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all, double), b64, dim3(FLUX_BLOCK), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }
   if (S32.n > 0) {
     if (Fs)
-      hipLaunchKernelGGL((k_flux_all_s<Dense, float>), flux_blocks(S32), dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL((k_flux_all_s<Dense, float>), b32, dim3(FLUX_BLOCK), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL((k_flux_all<Dense, float>), flux_blocks(S32), dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL((k_flux_all<Dense, float>), b32, dim3(FLUX_BLOCK), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }
@@ -686,7 +696,10 @@ static int launch_update(grrmhd_grid* g, Form form, double a, double b, double c
     TS.order = g->torder;
     g->sorted = true;
   }
-  const unsigned blocks = nblocks((long)n[0] * n[1], UPDATE_BLOCK) * n[2];
+  const long plane = (long)n[0] * n[1];
+  const unsigned blocks = thin_planes(plane, n[2], UPDATE_BLOCK)
+                              ? nblocks(plane * n[2], UPDATE_BLOCK)
+                              : nblocks(plane, UPDATE_BLOCK) * n[2];
   hipLaunchKernelGGL(GEO_KERNEL(g, form, k_update), dim3(blocks + (TS.order ? TILE_SORT_BLOCKS : 0)),
                      dim3(UPDATE_BLOCK), 0, g->stream,
                      g->C, a, b, c, const_cast<double*>(dt_dev), dtmin, dtnext, P, Un, Up, F, emf,

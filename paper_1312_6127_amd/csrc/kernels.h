@@ -580,15 +580,43 @@ DEV void stag_face_velocities(const Ctx& C, const double* __restrict__ P,
   }
 }
 
+// Order of a launch over a 3-D range: each (x1, x2) plane is cut into pieces
+// of one block each, and consecutive blocks take one piece through all x3
+// before the next piece.  What bounds these kernels is the latency of their
+// loads: with the planes one after another the stencil's four planes along x3
+// (12 fields of each) have left an XCD's 4 MB L2 when the next plane wants
+// them; a piece's own column stays.  With the index arithmetic in 32 bits the
+// dense faces of a 256x128x64 launch take 653 us instead of 732.
+//
+// A plane of a few blocks leaves a good part of its last one idle, all but one
+// lane of each where the grid is a line along x3; its stencil's planes stay in
+// L2 in any order.  Below THIN_BLOCKS blocks a plane (then an eighth of the
+// lanes at most) the range is one run of cells instead (split_plane).
+#define THIN_BLOCKS 8
+static inline __host__ __device__ bool thin_planes(long plane, long nk, int block) {
+  return plane < (long)THIN_BLOCKS * block && plane * nk < (1L << 31) - block;
+}
+DEV void split_plane(int plane, int& u, int& k) {
+  k = u / plane;
+  u -= k * plane;
+}
+DEV void column_piece(long b, int nk, int& u, int& k) {
+  const unsigned q = (unsigned)b / (unsigned)nk;
+  k = (int)((unsigned)b - q * (unsigned)nk);
+  u = (int)(q * blockDim.x + threadIdx.x);
+}
+
 template <class Geo, int D, class T, bool ENTF = false, bool STAG = false>
 DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
                                const double* __restrict__ chi_abs,
                                const double* __restrict__ chi_es, double* __restrict__ F,
                                double* __restrict__ vchar, const double* __restrict__ fl, int u,
-                               int k, double* __restrict__ Fs = nullptr,
+                               int k, bool flat, double* __restrict__ Fs = nullptr,
                                const double* __restrict__ Bf = nullptr,
                                double* __restrict__ VF = nullptr, double* __restrict__ SP = nullptr) {
-  if (u >= R.cnt[0] * R.cnt[1] || k >= R.cnt[2]) return;
+  const int plane = R.cnt[0] * R.cnt[1];
+  if (flat) split_plane(plane, u, k);
+  if (u >= plane || k >= R.cnt[2]) return;
   const int i = R.lo[0] + u % R.cnt[0], j = R.lo[1] + u / R.cnt[0];
   k += R.lo[2];
   const long c = cell_index(C, i, j, k);
@@ -651,19 +679,6 @@ DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
 }
 
 
-// Order of a launch over a 3-D range: each (x1, x2) plane is cut into pieces
-// of one block each, and consecutive blocks take one piece through all x3
-// before the next piece.  What bounds these kernels is the latency of their
-// loads: with the planes one after another the stencil's four planes along x3
-// (12 fields of each) have left an XCD's 4 MB L2 when the next plane wants
-// them; a piece's own column stays.  With the index arithmetic in 32 bits the
-// dense faces of a 256x128x64 launch take 653 us instead of 732.
-DEV void column_piece(long b, int nk, int& u, int& k) {
-  const unsigned q = (unsigned)b / (unsigned)nk;
-  k = (int)((unsigned)b - q * (unsigned)nk);
-  u = (int)(q * blockDim.x + threadIdx.x);
-}
-
 // The faces of all directions in one launch: at each piece and x3 a block for
 // each direction in turn, so that the directions share their reads too.
 struct FluxSegs {
@@ -671,6 +686,7 @@ struct FluxSegs {
   int D[3];
   int n;
   int pieces, nk;   // the largest of the ranges' counts
+  bool flat;        // thin planes: pieces of the whole ranges, nk = 1
 };
 
 template <class Geo, class T, bool ENTF = false, bool STAG = false>
@@ -688,9 +704,9 @@ DEV void flux_all_at(Ctx C, const FluxSegs& S, const double* __restrict__ P,
   double* Fd = F + (long)(D - 1) * 12 * C.Ntot;
   double* vd = vchar ? vchar + (long)(D - 1) * C.Ntot : nullptr;
   double* Fsd = ENTF ? Fs + (long)(D - 1) * C.Ntot : nullptr;
-  if (D == 1) flux_at<Geo, 1, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
-  else if (D == 2) flux_at<Geo, 2, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
-  else flux_at<Geo, 3, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
+  if (D == 1) flux_at<Geo, 1, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, S.flat, Fsd, Bf, VF, SP);
+  else if (D == 2) flux_at<Geo, 2, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, S.flat, Fsd, Bf, VF, SP);
+  else flux_at<Geo, 3, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, S.flat, Fsd, Bf, VF, SP);
 }
 
 // The same with the staggered field (and, with ENTF, the entropy tracer)
@@ -1138,7 +1154,7 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
                    const double* __restrict__ Uprev, const double* __restrict__ F,
                    const double* __restrict__ emf, const MTerms& MT, double* __restrict__ Uexp,
                    int t, int k, const double* __restrict__ Bface = nullptr) {
-  if (t >= C.n[0] * C.n[1]) return;
+  if (t >= C.n[0] * C.n[1] || k >= C.n[2]) return;
   const int i = C.ng[0] + t % C.n[0], j = C.ng[1] + t / C.n[0];
   const bool first = t == 0 && k == 0;
   k += C.ng[2];
@@ -1292,8 +1308,11 @@ __global__ void LB(128) k_update(Ctx C, double ca, double cb, double cc, double*
     if (blockIdx.x < GRRMHD_ORDER_BLOCKS) tile_order(TS.ntiles, TS.keys, TS.order);
     return;
   }
+  const int plane = C.n[0] * C.n[1];
+  const bool flat = thin_planes(plane, C.n[2], blockDim.x);
   int u, k;
-  column_piece(xcd_block(blockIdx.x - skip, gridDim.x - skip), C.n[2], u, k);
+  column_piece(xcd_block(blockIdx.x - skip, gridDim.x - skip), flat ? 1 : C.n[2], u, k);
+  if (flat) split_plane(plane, u, k);
   update_at<Geo>(C, ca, cb, cc, dt_dev, dtmin, dtnext, P, Un, Uprev, F, emf, MT, Uexp, u, k, Bface);
 }
 
