@@ -7,8 +7,10 @@
 #define LB(n) __launch_bounds__(n)
 // Three wavefronts per SIMD for the closed forms on MC and PPM faces: 28 bytes
 // of the stencil spill, and a 128x64x32 launch takes 57 us (at the two that
-// 174 registers allow: 65; at four, 188 bytes: 101).  The staggered faces,
-// with more to hold, gain nothing from the third (34 and 35 us at 80x50x20).
+// 174 registers allow: 65; at four, 188 bytes: 101).  Faces with more to hold
+// keep two: the entropy tracer's (k_flux_all_s) spill 100 bytes at three, and a
+// launch takes 85 us at 128x64x32 and 709 at 256x128x64 for 78 and 655; the
+// staggered ones gain nothing from the third (34 and 35 us at 80x50x20).
 #define FLUX_LB __launch_bounds__(64, Geo::closed_faces ? 3 : 1)
 
 // Workgroups are dealt to the 8 XCDs round-robin (workgroup b to XCD b mod 8)
@@ -734,7 +736,7 @@ __global__ void FLUX_LB k_flux_all(Ctx C, FluxSegs S, const double* __restrict__
 // The same with the entropy tracer's face fluxes Fs [3][Ntot] (the full
 // implicit cascade's entropy equation)
 template <class Geo, class T>
-__global__ void FLUX_LB k_flux_all_s(Ctx C, FluxSegs S, const double* __restrict__ P,
+__global__ void LB(64) k_flux_all_s(Ctx C, FluxSegs S, const double* __restrict__ P,
                                             const double* __restrict__ chi_abs,
                                             const double* __restrict__ chi_es,
                                             double* __restrict__ F, double* __restrict__ vchar,
