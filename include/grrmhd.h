@@ -254,7 +254,12 @@ int grrmhd_fixup(grrmhd_grid *g, double *P, double *U, int *status, double *scra
  * [12][N] in/out: U^n must hold the conserved state of P^n at interior
  * cells; on return both hold the new state at interior cells (ghosts of P
  * are stale).  dt_dev: device scalar, read when dt_fixed != 0, otherwise
- * computed from the wave speeds of P^n and written.  status/iters [N]
+ * computed from the wave speeds of P^n and written.  With dt_fixed the result
+ * is grrmhd_step_checkpointed's bit for bit.  A step that computes its dt has
+ * its own order of the same operations: repeated with that dt and dt_fixed, or
+ * put together from the calls above, it gives the same result to rounding, not
+ * to the bit (on a staggered-field grid dt_fixed makes no difference to the
+ * bits).  Either call repeated on the same input repeats its bits.  status/iters [N]
  * (nullable): OR of status bits / sum of Newton steps over the stages.
  * workspace: device buffer of grrmhd_workspace_bytes() (which depends on
  * the scheme).  EINVAL on a staggered-field grid (grrmhd_step_staggered

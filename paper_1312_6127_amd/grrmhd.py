@@ -400,7 +400,8 @@ class Grid:
 
     def step(self, P, U, chi_abs, chi_es, dt, dt_fixed=False, status=None, iters=None):
         """One step of the grid's scheme in place on P, U; dt is a 1-element device
-        tensor."""
+        tensor.  With dt_fixed the bits are step_checkpointed's; a step that
+        computes its dt agrees with one at that dt to rounding."""
         self._sync_stream()
         ws = self.workspace()
         _check(lib().grrmhd_step(self.h, _ptr(P), _ptr(U), _ptr(chi_abs), _ptr(chi_es), _ptr(dt),
