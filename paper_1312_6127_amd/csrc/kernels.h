@@ -403,7 +403,8 @@ DEV void face_closed(const Ctx& C, const M& m, const FaceGeom<M>& g, const doubl
   face_char(g, s0, sd, 1.0 / 3.0, fs.rm, fs.rp);
   const double tau = chi_tot * rho * g.hdx;
   if (3.0 * tau > 4.0) {   // optically thick: c = 4/(3 tau) < 1 in the gas frame
-    const double cl = 4.0 * recip(3.0 * tau);
+    // bounded for recip; c^2 is zero from far below on
+    const double cl = 4.0 * recip(fmin(3.0 * tau, 1e300));
     double lm, lp;
     face_char(g, u0, ud, cl * cl, lm, lp);
     fs.rp = fmin(fs.rp, lp);

@@ -17,7 +17,13 @@
 #pragma once
 #include "implicit.h"
 
-// 1/x to the last bit or two, x normal
+// 1/x to the last bit or two for normal x (up to 1e307); zero, an infinity or a
+// denormal gives NaN.  So the callers' arguments are sums with a term that is
+// bounded away from zero (1 + gamma, (1 - c^2) (u^t)^2 - c^2 g^tt, an enthalpy
+// with its rest mass, a norm set to 1e-300 where it vanishes), bounded where
+// they may overflow (an optical depth), or checked afterwards: an evaluation
+// whose residual is not finite fails, as with the IEEE forms, except that a
+// norm beyond 1e308 fails it too instead of passing for an error of zero.
 DEV double recip(double x) {
 #ifdef __HIP_DEVICE_COMPILE__
   double y = __builtin_amdgcn_rcp(x);
@@ -34,7 +40,8 @@ DEV double quot(double a, double b, double y) {
 }
 DEV double quot(double a, double b) { return quot(a, b, recip(b)); }
 // sqrt(x) and its reciprocal for normal x (Goldschmidt's coupled iteration
-// from the hardware's estimate, then the residual's correction)
+// from the hardware's estimate, then the residual's correction); an infinity
+// gives NaN.  The arguments are 1 + u~^2 and the limiter's polynomials.
 DEV double root(double x, double& inv) {
 #ifdef __HIP_DEVICE_COMPILE__
   const double y = __builtin_amdgcn_rsq(x);
@@ -58,7 +65,9 @@ DEV double root(double x) {
   double i;
   return root(x, i);
 }
-// the same where x may be zero or denormal (the result is then zero)
+// the same where x may be zero or denormal: zero up to 1e-300.  These are
+// norms, to which a larger term is added, and the discriminant of speeds, where
+// 1e-150 of c is nothing
 DEV double root0(double x) { return x > 1e-300 ? root(fmax(x, 1e-300)) : 0.0; }
 
 // v_i = g_ij v^j
