@@ -546,25 +546,24 @@ static void add_faces(FluxSegs& S, const FaceRange& r, int D) {
   S.R[S.n] = r;
   S.D[S.n++] = D;
 }
-// sets the order of the launch in S too
-static dim3 flux_blocks(FluxSegs& S) {
+// blocks of a launch and the order it takes its ranges in (thin: as runs of cells)
+static dim3 flux_blocks(FluxSegs& S, bool& thin) {
   long plane = 0, nk = 0, total = 0;
   for (int s = 0; s < S.n; s++) {
     plane = std::max(plane, (long)S.R[s].cnt[0] * S.R[s].cnt[1]);
     nk = std::max(nk, (long)S.R[s].cnt[2]);
     total = std::max(total, S.R[s].total);
   }
-  S.flat = thin_planes(plane, nk, FLUX_BLOCK);
-  S.pieces = (int)nblocks(S.flat ? total : plane, FLUX_BLOCK);
-  S.nk = S.flat ? 1 : (int)nk;
-  return dim3((unsigned)S.pieces * S.nk * S.n);
+  thin = thin_planes(plane, nk, FLUX_BLOCK);
+  S.nk = thin ? 1 : (int)nk;
+  return dim3(nblocks(thin ? total : plane, FLUX_BLOCK) * S.nk * S.n);
 }
 
 // The faces that set a step's dt keep the dense form: a gradient taken at that
 // dt moves by 1e-6 with its last bit.
-#define STAG_KERNEL(g, ENTF)                                                   \
-  ((g)->C.metric == GRRMHD_KERR_SCHILD ? k_flux_all_stag<KS, double, ENTF>     \
-                                       : k_flux_all_stag<Flat, double, ENTF>)
+#define STAG_KERNEL(g, ENTF, THIN)                                                   \
+  ((g)->C.metric == GRRMHD_KERR_SCHILD ? k_flux_all_stag<KS, double, ENTF, THIN>     \
+                                       : k_flux_all_stag<Flat, double, ENTF, THIN>)
 static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const double* ca, const double* ce,
                          double* F, double* emf, double* vch,
                          unsigned long long* dtmin = nullptr, int keep_flat = 0,
@@ -586,21 +585,22 @@ static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const doubl
     if (r64.total > 0) add_faces(S64, r64, d + 1);
     if (r32.total > 0) add_faces(S32, r32, d + 1);
   }
-  const dim3 b64 = flux_blocks(S64), b32 = flux_blocks(S32);
+  bool t64, t32;
+  const dim3 b64 = flux_blocks(S64, t64), b32 = flux_blocks(S32, t32);
   if (Bf) {
     const double* flp = (const double*)g->flat;
     if (S64.n > 0) {
       if (Fs)
-        hipLaunchKernelGGL(STAG_KERNEL(g, true), b64, dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((t64 ? STAG_KERNEL(g, true, true) : STAG_KERNEL(g, true, false)), b64, dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL(STAG_KERNEL(g, false), b64, dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((t64 ? STAG_KERNEL(g, false, true) : STAG_KERNEL(g, false, false)), b64, dim3(FLUX_BLOCK), 0, g->stream, C, S64, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
     if (S32.n > 0) {
       if (Fs)
-        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, true>), b32, dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((t32 ? k_flux_all_stag<Dense, float, true, true> : k_flux_all_stag<Dense, float, true, false>), b32, dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       else
-        hipLaunchKernelGGL((k_flux_all_stag<Dense, float, false>), b32, dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
+        hipLaunchKernelGGL((t32 ? k_flux_all_stag<Dense, float, false, true> : k_flux_all_stag<Dense, float, false, false>), b32, dim3(FLUX_BLOCK), 0, g->stream, C, S32, P, ca, ce, F, vch, flp, Fs, Bf, VF, SP);
       LAUNCHCHK();
     }
     // four-state corner EMFs at [ng, ng+n] on each active axis
@@ -624,19 +624,25 @@ static int launch_fluxes(grrmhd_grid* g, Form form, const double* P, const doubl
   }
   if (S64.n > 0) {
     if (Fs)
-      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all_s, double), b64, dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL((t64 ? GEO_KERNEL(g, form, k_flux_all_s, double, true)
+                              : GEO_KERNEL(g, form, k_flux_all_s, double, false)),
+                         b64, dim3(FLUX_BLOCK), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL(GEO_KERNEL(g, form, k_flux_all, double), b64, dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL((t64 ? GEO_KERNEL(g, form, k_flux_all, double, true)
+                              : GEO_KERNEL(g, form, k_flux_all, double, false)),
+                         b64, dim3(FLUX_BLOCK), 0,
                          g->stream, C, S64, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }
   if (S32.n > 0) {
     if (Fs)
-      hipLaunchKernelGGL((k_flux_all_s<Dense, float>), b32, dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL((t32 ? k_flux_all_s<Dense, float, true> : k_flux_all_s<Dense, float, false>), b32,
+                         dim3(FLUX_BLOCK), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat, Fs);
     else
-      hipLaunchKernelGGL((k_flux_all<Dense, float>), b32, dim3(FLUX_BLOCK), 0,
+      hipLaunchKernelGGL((t32 ? k_flux_all<Dense, float, true> : k_flux_all<Dense, float, false>), b32,
+                         dim3(FLUX_BLOCK), 0,
                          g->stream, C, S32, P, ca, ce, F, vch, (const double*)g->flat);
     LAUNCHCHK();
   }

@@ -5,31 +5,30 @@
 #pragma once
 #include "adjoint.h"
 
-#define INST_FLUX(X, Geo)                                                                         \
-  X template __global__ void k_flux_all<Geo, double>(Ctx, FluxSegs, const double*, const          \
+#define INST_FLUX(X, Geo, T, Thin)                                                                \
+  X template __global__ void k_flux_all<Geo, T, Thin>(Ctx, FluxSegs, const double*, const         \
       double*, const double*, double*, double*, const double*);                                   \
-  X template __global__ void k_flux_all_s<Geo, double>(Ctx, FluxSegs, const double*, const        \
+  X template __global__ void k_flux_all_s<Geo, T, Thin>(Ctx, FluxSegs, const double*, const       \
       double*, const double*, double*, double*, const double*, double*);
 
-#define INST_FLUX_STAG(X, Geo)                                                                    \
-  X template __global__ void k_flux_all_stag<Geo, double, false>(Ctx, FluxSegs, const             \
+#define INST_FLUX_STAG(X, Geo, T, Thin)                                                           \
+  X template __global__ void k_flux_all_stag<Geo, T, false, Thin>(Ctx, FluxSegs, const            \
       double*, const double*, const double*, double*, double*, const double*, double*, const      \
       double*, double*, double*);                                                                 \
-  X template __global__ void k_flux_all_stag<Geo, double, true>(Ctx, FluxSegs, const              \
+  X template __global__ void k_flux_all_stag<Geo, T, true, Thin>(Ctx, FluxSegs, const             \
       double*, const double*, const double*, double*, double*, const double*, double*, const      \
       double*, double*, double*);
 
-#define INST_FLUX_F32(X, Geo)                                                                     \
-  X template __global__ void k_flux_all<Geo, float>(Ctx, FluxSegs, const double*, const           \
-      double*, const double*, double*, double*, const double*);                                   \
-  X template __global__ void k_flux_all_s<Geo, float>(Ctx, FluxSegs, const double*, const         \
-      double*, const double*, double*, double*, const double*, double*);                          \
-  X template __global__ void k_flux_all_stag<Geo, float, false>(Ctx, FluxSegs, const              \
-      double*, const double*, const double*, double*, double*, const double*, double*, const      \
-      double*, double*, double*);                                                                 \
-  X template __global__ void k_flux_all_stag<Geo, float, true>(Ctx, FluxSegs, const double*,      \
-      const double*, const double*, double*, double*, const double*, double*, const double*,      \
-      double*, double*);
+// the FP64 step's faces; those of the dense form (FP64 and FP32)
+#define INST_FLUX_STEP(X, Thin)                                                                   \
+  INST_FLUX(X, KS, double, Thin)                                                                  \
+  INST_FLUX(X, Flat, double, Thin)                                                                \
+  INST_FLUX_STAG(X, KS, double, Thin)                                                             \
+  INST_FLUX_STAG(X, Flat, double, Thin)
+#define INST_FLUX_DENSE(X, Thin)                                                                  \
+  INST_FLUX(X, Dense, double, Thin)                                                               \
+  INST_FLUX(X, Dense, float, Thin)                                                                \
+  INST_FLUX_STAG(X, Dense, float, Thin)
 
 #define INST_IMPLICIT(X, Geo)                                                                     \
   X template __global__ void k_implicit<Geo>(Ctx, int, const double*, const double*, double,      \
@@ -91,16 +90,16 @@
       double*, double*, double*, const double*, double*);
 
 #ifndef INST_HERE_FLUX
-INST_FLUX(extern, KS)
-INST_FLUX(extern, Flat)
-INST_FLUX(extern, Dense)
+INST_FLUX_STEP(extern, false)
 #endif
-#ifndef INST_HERE_FLUX_STAG
-INST_FLUX_STAG(extern, KS)
-INST_FLUX_STAG(extern, Flat)
+#ifndef INST_HERE_FLUX_THIN
+INST_FLUX_STEP(extern, true)
 #endif
-#ifndef INST_HERE_FLUX_F32
-INST_FLUX_F32(extern, Dense)
+#ifndef INST_HERE_FLUX_DENSE
+INST_FLUX_DENSE(extern, false)
+#endif
+#ifndef INST_HERE_FLUX_DENSE_THIN
+INST_FLUX_DENSE(extern, true)
 #endif
 #ifndef INST_HERE_IMPLICIT
 INST_IMPLICIT(extern, KS)

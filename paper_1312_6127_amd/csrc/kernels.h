@@ -597,10 +597,10 @@ DEV void stag_face_velocities(const Ctx& C, const double* __restrict__ P,
 // lanes at most) the range is one run of cells instead (split_plane).
 #define THIN_BLOCKS 8
 static inline __host__ __device__ bool thin_planes(long plane, long nk, int block) {
-  return plane < (long)THIN_BLOCKS * block && plane * nk < (1L << 31) - block;
+  return nk > 1 && plane < (long)THIN_BLOCKS * block && plane * nk < (1L << 31) - block;
 }
 DEV void split_plane(int plane, int& u, int& k) {
-  k = u / plane;
+  k = (int)((unsigned)u / (unsigned)plane);
   u -= k * plane;
 }
 DEV void column_piece(long b, int nk, int& u, int& k) {
@@ -614,12 +614,10 @@ DEV void flux_at(Ctx C, FaceRange R, const double* __restrict__ P,
                                const double* __restrict__ chi_abs,
                                const double* __restrict__ chi_es, double* __restrict__ F,
                                double* __restrict__ vchar, const double* __restrict__ fl, int u,
-                               int k, bool flat, double* __restrict__ Fs = nullptr,
+                               int k, double* __restrict__ Fs = nullptr,
                                const double* __restrict__ Bf = nullptr,
                                double* __restrict__ VF = nullptr, double* __restrict__ SP = nullptr) {
-  const int plane = R.cnt[0] * R.cnt[1];
-  if (flat) split_plane(plane, u, k);
-  if (u >= plane || k >= R.cnt[2]) return;
+  if (u >= R.cnt[0] * R.cnt[1] || k >= R.cnt[2]) return;
   const int i = R.lo[0] + u % R.cnt[0], j = R.lo[1] + u / R.cnt[0];
   k += R.lo[2];
   const long c = cell_index(C, i, j, k);
@@ -688,11 +686,14 @@ struct FluxSegs {
   FaceRange R[3];
   int D[3];
   int n;
-  int pieces, nk;   // the largest of the ranges' counts
-  bool flat;        // thin planes: pieces of the whole ranges, nk = 1
+  int nk;     // the largest of the ranges' counts along x3
 };
 
-template <class Geo, class T, bool ENTF = false, bool STAG = false>
+// THIN: nk = 1 and the ranges are runs of cells.  A kernel of its own: where a
+// lane's x3 is its block's, the step's launches are 3% faster than where either
+// may be the case (10.0 and 10.4 us on a 128x64 disk, 33.9 and 34.8 on a
+// staggered one of 80x50x20).
+template <class Geo, class T, bool THIN, bool ENTF = false, bool STAG = false>
 DEV void flux_all_at(Ctx C, const FluxSegs& S, const double* __restrict__ P,
                      const double* __restrict__ chi_abs, const double* __restrict__ chi_es,
                      double* __restrict__ F, double* __restrict__ vchar,
@@ -703,17 +704,18 @@ DEV void flux_all_at(Ctx C, const FluxSegs& S, const double* __restrict__ P,
   const unsigned q = b / (unsigned)S.n, s = b - q * (unsigned)S.n;
   int u, k;
   column_piece(q, S.nk, u, k);
+  if constexpr (THIN) split_plane(S.R[s].cnt[0] * S.R[s].cnt[1], u, k);
   const int D = S.D[s];
   double* Fd = F + (long)(D - 1) * 12 * C.Ntot;
   double* vd = vchar ? vchar + (long)(D - 1) * C.Ntot : nullptr;
   double* Fsd = ENTF ? Fs + (long)(D - 1) * C.Ntot : nullptr;
-  if (D == 1) flux_at<Geo, 1, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, S.flat, Fsd, Bf, VF, SP);
-  else if (D == 2) flux_at<Geo, 2, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, S.flat, Fsd, Bf, VF, SP);
-  else flux_at<Geo, 3, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, S.flat, Fsd, Bf, VF, SP);
+  if (D == 1) flux_at<Geo, 1, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
+  else if (D == 2) flux_at<Geo, 2, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
+  else flux_at<Geo, 3, T, ENTF, STAG>(C, S.R[s], P, chi_abs, chi_es, Fd, vd, fl, u, k, Fsd, Bf, VF, SP);
 }
 
 // The same with the staggered field (and, with ENTF, the entropy tracer)
-template <class Geo, class T, bool ENTF>
+template <class Geo, class T, bool ENTF, bool THIN>
 __global__ void LB(64) k_flux_all_stag(Ctx C, FluxSegs S, const double* __restrict__ P,
                                                const double* __restrict__ chi_abs,
                                                const double* __restrict__ chi_es,
@@ -722,28 +724,28 @@ __global__ void LB(64) k_flux_all_stag(Ctx C, FluxSegs S, const double* __restri
                                                double* __restrict__ Fs,
                                                const double* __restrict__ Bf,
                                                double* __restrict__ VF, double* __restrict__ SP) {
-  flux_all_at<Geo, T, ENTF, true>(C, S, P, chi_abs, chi_es, F, vchar, fl, Fs, Bf, VF, SP);
+  flux_all_at<Geo, T, THIN, ENTF, true>(C, S, P, chi_abs, chi_es, F, vchar, fl, Fs, Bf, VF, SP);
 }
 
-template <class Geo, class T>
+template <class Geo, class T, bool THIN>
 __global__ void FLUX_LB k_flux_all(Ctx C, FluxSegs S, const double* __restrict__ P,
                                           const double* __restrict__ chi_abs,
                                           const double* __restrict__ chi_es,
                                           double* __restrict__ F, double* __restrict__ vchar,
                                           const double* __restrict__ fl) {
-  flux_all_at<Geo, T>(C, S, P, chi_abs, chi_es, F, vchar, fl);
+  flux_all_at<Geo, T, THIN>(C, S, P, chi_abs, chi_es, F, vchar, fl);
 }
 
 // The same with the entropy tracer's face fluxes Fs [3][Ntot] (the full
 // implicit cascade's entropy equation)
-template <class Geo, class T>
+template <class Geo, class T, bool THIN>
 __global__ void LB(64) k_flux_all_s(Ctx C, FluxSegs S, const double* __restrict__ P,
                                             const double* __restrict__ chi_abs,
                                             const double* __restrict__ chi_es,
                                             double* __restrict__ F, double* __restrict__ vchar,
                                             const double* __restrict__ fl,
                                             double* __restrict__ Fs) {
-  flux_all_at<Geo, T, true>(C, S, P, chi_abs, chi_es, F, vchar, fl, Fs);
+  flux_all_at<Geo, T, THIN, true>(C, S, P, chi_abs, chi_es, F, vchar, fl, Fs);
 }
 
 // sqrt(-g) S u^t of one cell's primitives p (the entropy tracer; NAN where
