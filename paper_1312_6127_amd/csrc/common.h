@@ -187,6 +187,7 @@ DEV void load_metric(const double* tab, int npos, int pos, M& m) {
   m.load(tab, npos, pos);
 }
 
+DEV void flat_metric(FlatMetric<double>&) {}
 DEV void flat_metric(Metric& m) {
 #pragma unroll
   for (int q = 0; q < 10; q++) m.gcov[q] = m.gcon[q] = 0.0;

@@ -494,8 +494,8 @@ DEV void flux_states(const Ctx& C, int i, int j, long c, long st, T PL[12], T PR
                                iden[q < 8 ? 0 : 1]
                          : T(0.5) * (L.F[q] + Rs.F[q]);
       else
-      f = (den > zero) ? (vmin * Rs.F[q] + vmax * L.F[q] - vmin * vmax * (Rs.U[q] - L.U[q])) / den
-                       : T(0.5) * (L.F[q] + Rs.F[q]);
+        f = (den > zero) ? (vmin * Rs.F[q] + vmax * L.F[q] - vmin * vmax * (Rs.U[q] - L.U[q])) / den
+                         : T(0.5) * (L.F[q] + Rs.F[q]);
     } else {
       f = T(0.5) * (Rs.F[q] + L.F[q] - fmax(vmin, vmax) * (Rs.U[q] - L.U[q]));
     }
@@ -1068,7 +1068,8 @@ DEV void geom_source(const M& m, const double dg[2][10], double gam, const T p[1
 }
 
 // geom_source on the closed forms: the tensors' components contracted as the
-// derivatives are loaded, so that neither set is held whole.  Adds to S.
+// derivatives are loaded, so that neither set is held whole.  Sets the four
+// components that have a source and leaves the rest of S alone.
 template <class M>
 DEV void geom_source_closed(const Ctx& C, const M& m, int pos, const double p[12], double S[12]) {
   const double ia = recip(m.alpha), beta = m.alpha * m.alpha * m.u01;
@@ -1611,7 +1612,8 @@ __global__ void LB(64) k_implicit_list(Ctx C, const double* __restrict__ Uexp,
   }
 }
 
-// Independent flat-space cells: same two-kernel structure.
+// Independent flat-space cells: same two-kernel structure.  Geo: the form of the
+// arithmetic (Dense, whose bits the batch keeps).
 template <class Geo>
 __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ Ui_,
                                         const double* __restrict__ Pg_,
@@ -1626,7 +1628,7 @@ __global__ void LBI k_implicit_batch(Ctx C, long n, const double* __restrict__ U
   Best b;
   int it = 0, trips = 0, st0 = 0;
   if (c < n) {
-    Metric m;
+    typename Geo::template M<double> m;
     flat_metric(m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -1661,6 +1663,7 @@ DEV long list_first(int cnt, long& step) {
 // Extreme cells of a batch (radiation far below the gas: URAD first, then PMHD
 // from scratch), one thread each; those left without an energy
 // solution go on to the cold limit's list K.
+template <class Geo>
 DEV void extreme_cells(const Ctx& C, long n, const double* __restrict__ Ui_,
                        const double* __restrict__ Pg_, const double* __restrict__ dtc,
                        const double* __restrict__ chi_abs, const double* __restrict__ chi_es,
@@ -1671,7 +1674,7 @@ DEV void extreme_cells(const Ctx& C, long n, const double* __restrict__ Ui_,
   long step;
   for (long w = list_first(cnt, step); w < cnt; w += step) {
     const long c = extreme_cell(W, w);
-    Metric m;
+    typename Geo::template M<double> m;
     flat_metric(m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -1685,7 +1688,7 @@ DEV void extreme_cells(const Ctx& C, long n, const double* __restrict__ Ui_,
     store_out(o, c, n, Po, Uo, iters, status, err);
     bool cold = false;
     if ((o.status & GRRMHD_ST_FAIL) && op.cold) {
-      Cell cl;
+      CellT<typename Geo::template M<double>> cl;
       cell_setup(m, Ui, dtc[c], chi_abs[c], chi_es[c], cl);
       cold = cold_allowed(cl, Pg);
     }
@@ -1708,7 +1711,7 @@ __global__ void LB(64) k_implicit_batch_list(Ctx C, long n, const double* __rest
   for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < cnt;
        w += (long)gridDim.x * blockDim.x) {
     const long c = extreme_cell(W, w);
-    Metric m;
+    typename Geo::template M<double> m;
     flat_metric(m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -1740,7 +1743,7 @@ __global__ void LB(64) k_cold_batch_list(Ctx C, long n, const double* __restrict
   long step;
   for (long w = list_first(cnt, step); w < cnt; w += step) {
     const long c = K.list[w];
-    Metric m;
+    typename Geo::template M<double> m;
     flat_metric(m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -1774,7 +1777,7 @@ __global__ void LB(64) k_rest_batch_list(Ctx C, long n, const double* __restrict
        w += (long)gridDim.x * blockDim.x) {
     const long slot = K.list[w];
     const long c = W.list[slot];
-    Metric m;
+    typename Geo::template M<double> m;
     flat_metric(m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -1824,14 +1827,14 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
                                       int* __restrict__ iters, int* __restrict__ status,
                                       double* __restrict__ err, Work W, int* cursor, Work K) {
   if (!C.cascade)
-    extreme_cells(C, n, Ui_, Pg_, dtc, chi_abs, chi_es, Po, Uo, iters, status, err, W, K);
+    extreme_cells<Geo>(C, n, Ui_, Pg_, dtc, chi_abs, chi_es, Po, Uo, iters, status, err, W, K);
   const Phys ph = make_phys(C);
   const Opts o = make_opts(C);
-  Metric m;
+  typename Geo::template M<double> m;
   flat_metric(m);
   const int cnt = *W.counter;
   UradLane L;
-  Cell c;
+  CellT<typename Geo::template M<double>> c;
   MhdIter in;
   long slot = 0;
   int stage = UE_NONE;
@@ -1933,7 +1936,7 @@ __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict_
                                         double* __restrict__ err, Work W, Work K) {
   const Phys ph = make_phys(C);
   const Opts o = make_opts(C);
-  Metric m;
+  typename Geo::template M<double> m;
   flat_metric(m);
   const int cnt = *W.counter;
   for (long slot = (long)blockIdx.x * blockDim.x + threadIdx.x; slot < cnt;
@@ -1942,7 +1945,7 @@ __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict_
     double Ui[12], Pg[12];
 #pragma unroll
     for (int q = 0; q < 12; q++) Ui[q] = Ui_[q * n + item];
-    Cell c;
+    CellT<typename Geo::template M<double>> c;
     cell_setup(m, Ui, dtc[item], chi_abs[item], chi_es[item], c);
     Best best;
     int its;
@@ -2257,10 +2260,10 @@ __global__ void LBP k_implicit_persist(Ctx C, long n, const double* __restrict__
   const Phys ph = make_phys(C);
   const Opts o = make_opts(C);
   const double thr = accept_threshold(o);
-  Metric m;
+  typename Geo::template M<double> m;
   flat_metric(m);
   Lane L;
-  Cell c;
+  CellT<typename Geo::template M<double>> c;
   double U0 = 0.0, UB[3] = {0.0, 0.0, 0.0};
   long item = -1;
   bool active = false, exhausted = false;
@@ -2410,7 +2413,7 @@ __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui
   Lane L;
   if (cidx < n) {
     const Phys ph = make_phys(C);
-    Metric m;
+    typename Geo::template M<double> m;
     flat_metric(m);
     double Ui[12], Pg[12];
 #pragma unroll
@@ -2418,7 +2421,7 @@ __global__ void LB(64) k_iter_start(Ctx C, long n, const double* __restrict__ Ui
       Ui[q] = Ui_[q * n + cidx];
       Pg[q] = Pg_[q * n + cidx];
     }
-    Cell c;
+    CellT<typename Geo::template M<double>> c;
     Prep pr;
     prepare(m, ph, Ui, Pg, dtc[cidx], chi_abs[cidx], chi_es[cidx], c, pr);
     L.status = pr.status;
@@ -2464,12 +2467,12 @@ __global__ void LB(64) k_iter_step(Ctx C, long n, const double* __restrict__ Ui_
       cidx = qin[w];
       const Phys ph = make_phys(C);
       const Opts o = make_opts(C);
-      Metric m;
+      typename Geo::template M<double> m;
       flat_metric(m);
       double Ui[12];
 #pragma unroll
       for (int q = 0; q < 12; q++) Ui[q] = Ui_[q * n + cidx];
-      Cell c;
+      CellT<typename Geo::template M<double>> c;
       cell_setup(m, Ui, dtc[cidx], chi_abs[cidx], chi_es[cidx], c);
       lane_load(L, cidx, n, sd, si);
       double xprev[4] = {L.x[0], L.x[1], L.x[2], L.x[3]};
