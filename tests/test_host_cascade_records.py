@@ -93,3 +93,14 @@ def test_regime_is_decided_once(orc, tmp_path):
     assert vals["extreme"] > 500 and vals["cells"] - vals["extreme"] > 100, vals
     assert vals["split"] > 100, vals
     assert vals["differing"] == 0, vals
+
+
+@pytest.mark.parametrize("steps", [1, 4, 60])
+def test_urad_attempt_in_parts(orc, tmp_path, steps):
+    """1, the long lists' 4 and, as on short lists, all Newton steps of an
+    evaluation's gas inversion a trip."""
+    _batch_file(orc, tmp_path / "batch.bin", 6000)
+    vals = _run(tmp_path, "urad_parts_check.cpp", str(tmp_path / "batch.bin"), str(steps))
+    assert vals["cells"] > 1000 and vals["bisected"] > 50 and vals["rootless"] > 50, vals
+    assert (vals["parts"] > 0) == (steps < 60), vals
+    assert vals["differing"] == 0, vals
