@@ -1198,6 +1198,12 @@ DEV void update_at(Ctx C, double ca, double cb, double cc, double* dt_dev,
       geom_source(m, dg, C.gam, p, S);
     }
   }
+  // The fluxes' loads stay behind the source: overlapped with it the closed
+  // form takes 156 registers, three wavefronts per SIMD, and this kernel lives
+  // on wavefronts in flight (98 and four: 37.6 -> 33.7 us a launch of a
+  // 128x64x32 step, 338 -> 316 at 256x128x64; with the dense source, before, 34
+  // and 314).
+  __builtin_amdgcn_sched_barrier(0);
   for (int d = 0; d < 3 && cc != 0.0; d++) {
     if (C.n[d] == 1) continue;
     const double idx = 1.0 / C.dx[d];
