@@ -2154,7 +2154,8 @@ static int launch_batch(const Ctx& C, long n, const double* U_expl, const double
   // the full cascade's rest for the cells the PMHD and URAD attempts left
   // unaccepted (K holds their record slots), the cold limit inline
   if (C.cascade) {
-    hipLaunchKernelGGL(k_rest_batch_list<Dense>, dim3(list_blocks(n)), dim3(64), 0, s, C, n, U_expl,
+    const unsigned rest = std::max(list_blocks(n), (unsigned)cwaves);
+    hipLaunchKernelGGL(k_rest_batch_list<Dense>, dim3(rest), dim3(64), 0, s, C, n, U_expl,
                        P_guess, dt_cell, chi_abs, chi_es, P_out, U_out, iters, status, err, W, K);
     LAUNCHCHK();
   } else if (C.cold && C.u_floor > 0.0) {

@@ -1043,8 +1043,9 @@ DEV void rec_first(const RecBuf& R, long slot, bool extreme, const Best& b, int 
 DEV bool rec_extreme(const RecBuf& R, long slot) { return (R.i[slot] & REC_EXTREME) != 0; }
 
 // A batch cell's URAD attempt b beside the first attempt in its record: the
-// better one stays there, with its method and all iterations.
-DEV void rec_urad(const RecBuf& R, long slot, Best& b, int iters) {
+// better one stays there, with its method and all iterations.  Returns its e_T
+// (INFINITY: neither).
+DEV double rec_urad(const RecBuf& R, long slot, Best& b, int iters) {
   const int f = R.i[slot];
   const double e0 = (f >> REC_OK & 1) ? R.d[12 * R.cap + slot] : INFINITY;
   if (b.ok && b.eT < e0) {
@@ -1053,9 +1054,10 @@ DEV void rec_urad(const RecBuf& R, long slot, Best& b, int iters) {
     for (int k = 0; k < 3; k++) b.P[5 + k] = b.x[k];
     R.d[13 * R.cap + slot] = b.x[3];
     rec_store(R, slot, b, iters, f >> REC_STATUS);
-  } else {
-    R.i[R.cap + slot] = iters;
+    return b.eT;
   }
+  R.i[R.cap + slot] = iters;
+  return e0;
 }
 
 // B: the cell's explicit field, given where the record may be a URAD attempt's

@@ -1768,7 +1768,12 @@ __global__ void LB(64) k_cold_batch_list(Ctx C, long n, const double* __restrict
 
 // The full cascade's rest (params.cascade = 1) for batch cells the PMHD and
 // URAD attempts left unaccepted: K lists their record slots; each resumes
-// after both attempts (one thread per cell).
+// after both attempts (one thread per cell).  In the order in which the lanes
+// of k_cascade_urad end, neighbours in the list are alike (in the slots' order:
+// 5.15 ms at 65536 cells instead of 4.9, 6.13 at 2^19 instead of 5.7); a list
+// that those lanes take spread over all wavefronts has lost that order, and
+// is spread here too (4099 cells: 1.6 ms; in full wavefronts 4.4, and 4.1 when
+// the attempts ended in full wavefronts).
 template <class Geo>
 __global__ void LB(64) k_rest_batch_list(Ctx C, long n, const double* __restrict__ Ui_,
                                          const double* __restrict__ Pg_,
@@ -1779,8 +1784,8 @@ __global__ void LB(64) k_rest_batch_list(Ctx C, long n, const double* __restrict
                                          int* __restrict__ iters, int* __restrict__ status,
                                          double* __restrict__ err, Work W, Work K) {
   const int cnt = *K.counter;
-  for (long w = (long)blockIdx.x * blockDim.x + threadIdx.x; w < cnt;
-       w += (long)gridDim.x * blockDim.x) {
+  long step;
+  for (long w = list_first(cnt, step); w < cnt; w += step) {
     const long slot = K.list[w];
     const long c = W.list[slot];
     typename Geo::template M<double> m;
@@ -1916,10 +1921,12 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
     const unsigned long long ev_mask = __ballot(doeval);
     useful += __popcll(ev_mask);
     slots += ev_mask ? 64ull : 0ull;
+    bool rest = false;
     if (ended) {
-      rec_urad(W.rec, slot, L.best, L.iters);
+      rest = !(rec_urad(W.rec, slot, L.best, L.iters) < accept_threshold(o));
       active = false;
     }
+    if (C.cascade) wave_append(rest, (int)slot, K.counter, K.list);
     if (!__any(active) && __all(exhausted)) break;
   }
   if ((threadIdx.x & 63) == 0 && useful) {
@@ -1929,8 +1936,8 @@ __global__ void LB(64) k_cascade_urad(Ctx C, long n, const double* __restrict__ 
 }
 
 // Outputs of the cells of k_cascade_urad from their records, one thread each;
-// cells without an acceptable solution go on to the cold limit's list or, with
-// the full cascade, their slots to its rest (K).
+// cells without a solution go on to the cold limit's list (K).  With the full
+// cascade the lanes above have listed the slots that its rest takes.
 template <class Geo>
 __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict__ Ui_,
                                         const double* __restrict__ Pg_,
@@ -1970,11 +1977,8 @@ __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict_
       finalize(c, ph, o, best, bm, st, its, Ui, out);
     }
     store_out(out, item, n, Po, Uo, iters, status, err);
-    bool failed;
-    if (C.cascade) {
-      failed = !done;
-    } else {
-      failed = (out.status & GRRMHD_ST_FAIL) && o.cold;
+    if (!C.cascade) {
+      bool failed = (out.status & GRRMHD_ST_FAIL) && o.cold;
       if (failed) {
         if (done) {   // solved, with u_g <= 0
 #pragma unroll
@@ -1982,8 +1986,8 @@ __global__ void LB(64) k_cascade_finish(Ctx C, long n, const double* __restrict_
         }
         failed = cold_allowed(c, Pg);
       }
+      wave_append(failed, (int)item, K.counter, K.list);
     }
-    wave_append(failed, C.cascade ? (int)slot : (int)item, K.counter, K.list);
   }
 }
 
