@@ -47,8 +47,8 @@ STEP_BYTES_PER_ZONE = 1344
 # They hold for the kernel sources whose digest is KERNEL_DIGEST; otherwise
 # traffic is reported as null and the flop figure as stale.
 FLOPS_PER_TRIP = 933.0
-HBM_BYTES_PER_LAUNCH = 143.6e6
-KERNEL_DIGEST = "f1a16800e7e22f90"
+HBM_BYTES_PER_LAUNCH = 143.3e6
+KERNEL_DIGEST = "e75b6d348060c3a6"
 
 
 def parse():

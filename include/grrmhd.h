@@ -441,11 +441,11 @@ int grrmhd_con2prim_vjp(grrmhd_grid *g, const double *U, const double *P, const 
  * nullable), device memory; n < 2^31.  workspace: device buffer of at least
  * grrmhd_implicit_source_workspace_bytes(n) bytes, 256-byte aligned (work
  * list of the cells that need the full cascade, with the result of their
- * first attempt; list of deferred extreme cells; list of cells for the cold
- * limit; lane statistics).  Same algorithm as grrmhd_implicit_grid.  The
- * cascade's URAD attempts run in a compacting persistent grid (lanes take
- * the next listed cell as soon as theirs ends); extreme cells (URAD first)
- * and then cold cells run one thread each afterwards. */
+ * first attempt, and of the extreme cells; list of cells for the cold limit;
+ * lane statistics: 128 bytes a cell).  Same algorithm as grrmhd_implicit_grid.
+ * The cascade's URAD attempts run in a compacting persistent grid (lanes take
+ * the next listed cell as soon as theirs ends); extreme cells (URAD first) run
+ * one thread each at its start, cold cells after it. */
 size_t grrmhd_implicit_source_workspace_bytes(long n);
 int grrmhd_implicit_source(const grrmhd_params *p, long n, const double *U_expl,
                            const double *P_guess, const double *dt_cell, const double *chi_abs,
