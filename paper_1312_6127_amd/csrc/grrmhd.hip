@@ -309,14 +309,16 @@ extern "C" int grrmhd_init_grid(const grrmhd_params* p, int device, void* hip_st
   g->C.geo_f2 = g->geo + tab * (GE_NCENTER + GE_NFACE);
   hipLaunchKernelGGL(k_geometry, dim3(nblocks(g->C.npos, 256)), dim3(256), 0, g->stream, g->C,
                      p->a, p->R0, g->geo, (double*)g->C.geo_f1, (double*)g->C.geo_f2);
-  // both list lengths (bytes 128..191 of the tail) and the lane statistics
-  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)(tail + 128), 16);
-  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)g->W.stats, STAT_INTS);
-  // no costs known yet: the first launch takes the tiles in any order
-  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, g->tkeys, (int)g->ntiles);
-  // from here on torder holds a permutation of the tiles whatever runs next
-  hipLaunchKernelGGL(k_tile_order, dim3(GRRMHD_ORDER_BLOCKS), dim3(1024), 0, g->stream, g->ntiles,
-                     (const int*)g->tkeys, g->torder);
+  // both list lengths (bytes 128..191 of the tail) to the lane statistics
+  hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, (int*)(tail + 128),
+                     (int)((TAIL_CASCADE - 128) / sizeof(int)));
+  if (g->sorts()) {
+    // no costs known yet: the first launch takes the tiles in any order, and
+    // from here on torder holds a permutation of them whatever runs next
+    hipLaunchKernelGGL(k_zero_ints, dim3(1), dim3(64), 0, g->stream, g->tkeys, (int)g->ntiles);
+    hipLaunchKernelGGL(k_tile_order, dim3(GRRMHD_ORDER_BLOCKS), dim3(1024), 0, g->stream, g->ntiles,
+                       (const int*)g->tkeys, g->torder);
+  }
   hipLaunchKernelGGL(k_dt_init, dim3(1), dim3(64), 0, g->stream, g->dtslot, 1, 1);
   hipLaunchKernelGGL(k_dt_init, dim3(1), dim3(64), 0, g->stream, g->dtstep[0],
                      2 * GRRMHD_DT_SLOTS, GRRMHD_DT_STRIDE);
